@@ -104,28 +104,42 @@ __device__ __forceinline__ void unpack_pair(const PairRaw<D> &r, uint4 *KA, uint
   }
 }
 
-// Query operands of one column (zero when absent), split in three bf16 terms so that the
-// scores keep fp32-level accuracy even for very large logits. The dim order matches the K
-// operand of the cache dtype.
+// One column's query (d_h fp32 values) in registers: 32 bytes per lane and 32-dim block, in the
+// dim order of the cache dtype's K operand. The loads are unconditional 16-byte ones (a caller's
+// array may be aligned to 4 bytes only, which global loads take) from a row that exists; absent
+// columns are zeroed when the operands are built, so no lane branches around its loads.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+template <int D>
+struct QueryRaw {
+  f32x4u v[D / 32][2];
+};
 template <int KVT, int D>
-__device__ __forceinline__ void load_query_ops(const float *qr, bool present, int cq, uint4 *qhi,
-                                               uint4 *qmd, uint4 *qlo) {
-  constexpr int NKB = D / 32;
+__device__ __forceinline__ void load_query(const float *qr, int cq, QueryRaw<D> &r) {
 #pragma unroll
-  for (int kk = 0; kk < NKB; ++kk) {
-    uint32_t h[8], md[8], l[8];
+  for (int kk = 0; kk < D / 32; ++kk) {
+    const int dim = (KVT == 1) ? kk * 32 + 8 * cq : 16 * (4 * (kk >> 1) + cq) + 8 * (kk & 1);
+    r.v[kk][0] = *(const f32x4u *)(qr + dim);
+    r.v[kk][1] = *(const f32x4u *)(qr + dim + 4);
+  }
+}
+
+// Query operands of one column (zero when absent), split in three bf16 terms so that the
+// scores keep fp32-level accuracy even for very large logits.
+template <int D>
+__device__ __forceinline__ void query_ops(const QueryRaw<D> &r, bool present, uint4 *qhi,
+                                          uint4 *qmd, uint4 *qlo) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int dim = (KVT == 1) ? kk * 32 + 8 * cq + i : 16 * (4 * (kk >> 1) + cq) + 8 * (kk & 1) + i;
-      const float v = present ? qr[dim] : 0.f;
-      uint32_t rest;
-      split_hi_lo(v, h[i], rest);
-      split_hi_lo(v - __uint_as_float(h[i] << 16), md[i], l[i]);
+  for (int kk = 0; kk < D / 32; ++kk) {
+    uint32_t h[4], md[4], l[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float x0 = present ? r.v[kk][i >> 1][2 * (i & 1)] : 0.f;
+      const float x1 = present ? r.v[kk][i >> 1][2 * (i & 1) + 1] : 0.f;
+      split3(x0, x1, h[i], md[i], l[i]);
     }
-    qhi[kk] = make_uint4(pack2(h[0], h[1]), pack2(h[2], h[3]), pack2(h[4], h[5]), pack2(h[6], h[7]));
-    qmd[kk] = make_uint4(pack2(md[0], md[1]), pack2(md[2], md[3]), pack2(md[4], md[5]),
-                         pack2(md[6], md[7]));
-    qlo[kk] = make_uint4(pack2(l[0], l[1]), pack2(l[2], l[3]), pack2(l[4], l[5]), pack2(l[6], l[7]));
+    qhi[kk] = make_uint4(h[0], h[1], h[2], h[3]);
+    qmd[kk] = make_uint4(md[0], md[1], md[2], md[3]);
+    qlo[kk] = make_uint4(l[0], l[1], l[2], l[3]);
   }
 }
 
@@ -163,8 +177,7 @@ __device__ __forceinline__ void online_step(const uint4 *KA, const uint4 *KB, co
   float mx = sv[0];
 #pragma unroll
   for (int i = 1; i < 8; ++i) mx = fmaxf(mx, sv[i]);
-  mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-  mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+  mx = column_max(mx);
   const float m_new = fmaxf(m_run, mx);  // finite once any valid token has been seen
   const float alpha = (m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);
   m_run = m_new;
@@ -233,6 +246,7 @@ struct AttnArgs {
   uint16_t *op;   // operand buffer of the output projection (may be null)
   int NT, Bp;
   float *lse;     // [B][nq] log-sum-exp of each softmax, own keys included (may be null)
+  int ginv;       // 65536 / g rounded up: n / g = (n * ginv) >> 16 for n < 16
   int kq;         // verify tokens per candidate: row v = token v % kq of candidate v / kq; q,
                   // k_self, v_self, partials and o are per row, lengths and page table per
                   // candidate, group ranges in rows
@@ -247,6 +261,11 @@ struct AttnArgs {
 // a dimension together, so one 16-byte load per lane feeds 2 (bf16) or 4 (fp8) A operands; B =
 // P^T hi and lo). The wave writes its unnormalised partial (acc, m, l) per q-head.
 // Slots at or beyond L_b are masked in S and zeroed in V (they may hold anything, NaN included).
+// The start of a block (query, lengths, page ids, first pair) is a serial chain that every block
+// pays once: with one branch-guarded 4-byte load per query element and the bf16 split in integer
+// arithmetic it took 1.5-2 us more than with 16-byte loads issued first and the hardware
+// pack-convert (7B batch of 16: 26.9 -> 25.2 us a layer, ragged 32k 67.9 -> 66.4, private pages of
+// the 64-candidate beam 34.6 -> 32.3, shared prefix 52.7 -> 49.9).
 template <int KVT, int D>
 __global__ __launch_bounds__(64 * kMaxKvHeadsMx) void k_attn_mx(AttnArgs a) {
   constexpr int NKB = D / 32;  // 32-dim blocks of q.k
@@ -254,9 +273,23 @@ __global__ __launch_bounds__(64 * kMaxKvHeadsMx) void k_attn_mx(AttnArgs a) {
   constexpr int EB = KVT == 1 ? 2 : 1;
   constexpr size_t TILE = (size_t)kPage * D * EB;
   const int c = blockIdx.x, b = blockIdx.y;  // chunk, candidate
-  const int j = threadIdx.x >> 6;
+  // (the wave index as a scalar, so that tile addresses are scalar too)
+  const int j =
+      __builtin_amdgcn_readfirstlane((int)(blockIdx.z * (blockDim.x >> 6) + (threadIdx.x >> 6)));
   const int nkv = a.nkv, g = a.g, nq = a.nq, kq = a.kq;
   const int L = a.lengths[b];
+  const int lane = threadIdx.x & 63;
+  const int n = lane & 15, cq = lane >> 4;
+  // column n: verify token n / g of this candidate, q-head j g + n % g (kq g <= 16 columns; the
+  // division by multiplication: n < 16, g <= 16)
+  const bool colv = n < kq * g;
+  const int ti = colv ? (n * a.ginv) >> 16 : 0, hh = colv ? n - ti * g : 0;
+  const size_t row = (size_t)b * kq + ti;
+  // the query is the one load that depends on nothing: issued first, split into operands while
+  // the first page pair is in flight
+  QueryRaw<D> qraw;
+  load_query<KVT, D>(a.q + (row * nq + (size_t)j * g + hh) * D, cq, qraw);
+  __builtin_amdgcn_sched_barrier(0);
   const int npages = (L + kPage - 1) / kPage;
   int first = 0;
   for (int gi = 0; gi < a.gt.n; ++gi)
@@ -266,13 +299,12 @@ __global__ __launch_bounds__(64 * kMaxKvHeadsMx) void k_attn_mx(AttnArgs a) {
   const int p0 = first + c * CP;
   if (p0 >= npages) return;
   const int np = min(npages, p0 + CP) - p0;
-  const int lane = threadIdx.x & 63;
-  const int n = lane & 15, cq = lane >> 4;
-  // each wave reads the chunk's page ids itself into lane registers (lane i holds page i and,
-  // for fp8, its scales) and fetches them with scalar lane reads: no LDS, no barrier
-  const int ph_l = lane < np ? a.page_table[(size_t)b * a.max_pages + p0 + lane] : 0;
+  // each wave reads the chunk's page ids itself into lane registers (lane i holds page i, lanes
+  // past the chunk its last page, and for fp8 their scales) and fetches them with scalar lane
+  // reads: no LDS, no barrier
+  const int ph_l = a.page_table[(size_t)b * a.max_pages + p0 + min(lane, np - 1)];
   float ksc_l = 0.f, vsc_l = 0.f;
-  if (KVT == 2 && lane < np) {
+  if (KVT == 2) {
     ksc_l = a.ksc[(size_t)ph_l * nkv + j];
     vsc_l = a.vsc[(size_t)ph_l * nkv + j];
   }
@@ -287,14 +319,10 @@ __global__ __launch_bounds__(64 * kMaxKvHeadsMx) void k_attn_mx(AttnArgs a) {
                           (const uint4 *)(a.vp + ((size_t)pb * nkv + j) * TILE), lane, r);
   };
   PairRaw<D> r0, r1;
-  load_pair(0, r0);  // in flight while the queries are prepared
-
-  // column n: verify token n / g of this candidate, q-head j g + n % g (kq g <= 16 columns)
-  const bool colv = n < kq * g;
-  const int ti = colv ? n / g : 0, hh = colv ? n - (n / g) * g : 0;
-  const size_t row = (size_t)b * kq + ti;
+  load_pair(0, r0);
+  __builtin_amdgcn_sched_barrier(0);
   uint4 q0[NKB], q1[NKB], q2[NKB];
-  load_query_ops<KVT, D>(a.q + (row * nq + (size_t)j * g + hh) * D, colv, cq, q0, q1, q2);
+  query_ops<D>(qraw, colv, q0, q1, q2);
   const float rs = kLog2e / sqrtf((float)D);  // scores in log2 units
   float m_run = -INFINITY, l_run = 0.f;
   floatx4 acc[NDB];
@@ -348,8 +376,7 @@ __global__ __launch_bounds__(64 * kMaxKvHeadsMx) void k_attn_mx(AttnArgs a) {
     chunk_loop(std::integral_constant<bool, false>{});
   else
     chunk_loop(std::integral_constant<bool, true>{});
-  l_run += __shfl_xor(l_run, 16, 64);
-  l_run += __shfl_xor(l_run, 32, 64);
+  l_run = column_sum(l_run);
   if (colv)
     store_partial<D>(a.apart + ((row * nq + (size_t)j * g + hh) * a.nch + ncp + c) * (D + 2), cq,
                      acc, m_run, l_run);
@@ -432,8 +459,11 @@ __global__ __launch_bounds__(64 * kPrefixWaves) void k_prefix_mx(AttnArgs a) {
     s3 = fetch(3);
   }
   uint4 qhi[NKB], qmd[NKB], qlo[NKB];
-  load_query_ops<KVT, D>(a.q + ((size_t)bcand * nq + (size_t)j * g + hh) * D, present, cq, qhi,
-                         qmd, qlo);
+  {
+    QueryRaw<D> qraw;
+    load_query<KVT, D>(a.q + ((size_t)bcand * nq + (size_t)j * g + hh) * D, cq, qraw);
+    query_ops<D>(qraw, present, qhi, qmd, qlo);
+  }
   stash(0, s0);
   __syncthreads();
   const float rs = kLog2e / sqrtf((float)D);  // scores in log2 units
@@ -484,8 +514,7 @@ __global__ __launch_bounds__(64 * kPrefixWaves) void k_prefix_mx(AttnArgs a) {
       step(pb + 3, s3, s0);
     }
   }
-  l_run += __shfl_xor(l_run, 16, 64);
-  l_run += __shfl_xor(l_run, 32, 64);
+  l_run = column_sum(l_run);
   if (present)
     store_partial<D>(a.apart + (((size_t)bcand * nq + (size_t)j * g + hh) * a.nch + c) * (D + 2),
                      cq, acc, m_run, l_run);
@@ -604,6 +633,7 @@ hipError_t launch_attn_mx(const Dims &dm, const Plan &p, const Workspace &w, con
   a.vsc = vsc;
   a.nkv = dm.nkv;
   a.g = dm.g;
+  a.ginv = (65536 + dm.g - 1) / dm.g;
   a.nq = dm.nq;
   a.page_table = page_table;
   a.max_pages = p.max_pages;

@@ -50,6 +50,17 @@ __device__ __forceinline__ void split2(float x0, float x1, uint32_t &hi, uint32_
   lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(rv, bf16x2v));
 }
 
+// Two fp32 values -> packed bf16 pairs hi, mid, lo (nearest-even each, mid of the rest after hi,
+// lo of the rest after mid; the differences are exact): hi + mid + lo carries 24 significant bits.
+__device__ __forceinline__ void split3(float x0, float x1, uint32_t &hi, uint32_t &mid,
+                                       uint32_t &lo) {
+  typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
+  typedef float f32x2v __attribute__((ext_vector_type(2)));
+  const f32x2v xv = {x0, x1};
+  hi = __builtin_bit_cast(uint32_t, __builtin_convertvector(xv, bf16x2v));
+  split2(x0 - __uint_as_float(hi << 16), x1 - __uint_as_float(hi & 0xFFFF0000u), mid, lo);
+}
+
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
@@ -79,6 +90,25 @@ __device__ __forceinline__ float wmax(float v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
   return v;
+}
+
+// v combined over the four lanes l % 16, l % 16 + 16, + 32, + 48 (the lanes of one column of a
+// matrix-core accumulator), in every lane: gfx950's row swaps instead of two LDS permutes. Each
+// swap of a register with itself leaves a row pair's lower rows in one result and its upper rows
+// in the other.
+template <typename F>
+__device__ __forceinline__ float column_reduce(float v, F f) {
+  const uint32_t a = __float_as_uint(v);
+  const auto r = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+  const uint32_t b = __float_as_uint(f(__uint_as_float(r[0]), __uint_as_float(r[1])));
+  const auto t = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+  return f(__uint_as_float(t[0]), __uint_as_float(t[1]));
+}
+__device__ __forceinline__ float column_max(float v) {
+  return column_reduce(v, [](float x, float y) { return fmaxf(x, y); });
+}
+__device__ __forceinline__ float column_sum(float v) {
+  return column_reduce(v, [](float x, float y) { return x + y; });
 }
 
 // Deterministic 256-thread block reductions; every thread receives the result.
