@@ -158,8 +158,9 @@ kvprm_status kvprm_create(const kvprm_model_desc *desc, kvprm_handle *out);
 /* Release a handle (NULL is accepted). */
 kvprm_status kvprm_destroy(kvprm_handle h);
 
-/* Bytes of device workspace kvprm_score and kvprm_attention need for this batch (it depends on
- * batch and max_pages only). */
+/* Bytes of device workspace kvprm_score and kvprm_attention use for this batch (it depends on
+ * batch and max_pages only). For a small batch that includes room for splitting its attention
+ * more finely; a call given less, but enough for 16-page chunks, runs without that. */
 kvprm_status kvprm_workspace_size(kvprm_handle h, const kvprm_batch *batch, size_t *bytes);
 
 /* Eq. (score) for every candidate: scores[b] = P(+) in [0, 1] and, if logits != NULL,
@@ -179,7 +180,8 @@ kvprm_status kvprm_score(kvprm_handle h, const kvprm_kv_cache *cache, const kvpr
  * (code under HIP graph capture that must not allocate, tight serving loops, harnesses that
  * forbid hipMalloc). The workspace is a static device array of KVPRM_STATIC_WORKSPACE_BYTES
  * that the library holds on every GPU it runs on until the process ends; nothing is allocated
- * or freed by the call. It serves batches whose kvprm_workspace_size is at most that size
+ * or freed by the call. It serves batches that fit that size (kvprm_workspace_size, less the
+ * room it includes for splitting a small batch's attention more finely, used where it fits)
  * (8 candidates with up to 32768 cached tokens at the 7B shape need 16 MiB; 64 candidates with
  * 18432 tokens each need 87 MiB and are refused); a larger one returns KVPRM_E_WORKSPACE before
  * anything is enqueued.

@@ -105,13 +105,13 @@ static kvprm_status check_batch(const kvprm_handle h, const kvprm_batch *b, cons
   if (!b) return fail(KVPRM_E_INVALID, "%s: null batch", fn);
   if (b->batch < 0) return fail(KVPRM_E_INVALID, "%s: batch < 0", fn);
   if (b->batch == 0) return KVPRM_OK;
-  if (b->batch > 256) return fail(KVPRM_E_UNSUPPORTED, "%s: at most 256 candidates per call", fn);
+  if (b->batch > kMaxBatch) return fail(KVPRM_E_UNSUPPORTED, "%s: at most 256 candidates per call", fn);
   if (h->dm.wdt == 1 && b->batch > 64)
     return fail(KVPRM_E_UNSUPPORTED, "%s: at most 64 candidates per call with bf16 weights", fn);
   if (!b->page_table || !b->lengths) return fail(KVPRM_E_INVALID, "%s: null page_table or lengths", fn);
   if (b->max_pages < 1) return fail(KVPRM_E_INVALID, "%s: max_pages < 1", fn);
   // chunk slots per candidate: one per chunk of max_pages, plus one where a shared prefix
-  // splits a chunk (chunks of 16 pages at the shortest, 32 on the vector-ALU path)
+  // splits a chunk (16-page chunks; 32 on the vector-ALU path)
   const int max_mp = (kMaxChunks - 2) * (h->dm.kvdt == 0 ? kChunkPagesValu : 16);
   if (b->max_pages > max_mp)
     return fail(KVPRM_E_UNSUPPORTED, "%s: max_pages above %d", fn, max_mp);
@@ -190,9 +190,19 @@ static kvprm_status check_pages_debug(const kvprm_handle h, const kvprm_kv_cache
   return KVPRM_OK;
 }
 
-static size_t ws_bytes_for(const kvprm_handle h, const kvprm_batch *b) {
-  Plan p = make_plan(h->dm, b->batch, b->max_pages);
+static size_t ws_bytes_for(const kvprm_handle h, const kvprm_batch *b, bool lean = false) {
+  Plan p = make_plan(h->dm, b->batch, b->max_pages, 0, 1, lean);
   return carve(h->dm, p, nullptr).bytes;
+}
+
+// The call's plan: with slots for short attention chunks where the workspace holds them (one sized
+// by kvprm_workspace_size does), else the lean one (a workspace kept from another batch may be
+// large enough for that only).
+static Plan plan_for(const kvprm_handle h, const kvprm_batch *b, int rank, int depth,
+                     size_t ws_bytes) {
+  const Plan p = make_plan(h->dm, b->batch, b->max_pages, rank, depth);
+  if (carve(h->dm, p, nullptr).bytes <= ws_bytes) return p;
+  return make_plan(h->dm, b->batch, b->max_pages, rank, depth, true);
 }
 
 kvprm_status kvprm_workspace_size(kvprm_handle h, const kvprm_batch *b, size_t *bytes) {
@@ -205,7 +215,7 @@ kvprm_status kvprm_workspace_size(kvprm_handle h, const kvprm_batch *b, size_t *
 
 static kvprm_status check_ws(const kvprm_handle h, const kvprm_batch *b, void *ws, size_t n,
                              const char *fn) {
-  const size_t need = ws_bytes_for(h, b);
+  const size_t need = ws_bytes_for(h, b, true);
   if (!ws || n < need)
     return fail(KVPRM_E_WORKSPACE, "%s: workspace of %zu bytes needed, %zu given", fn, need,
                 ws ? n : (size_t)0);
@@ -213,7 +223,8 @@ static kvprm_status check_ws(const kvprm_handle h, const kvprm_batch *b, void *w
   return KVPRM_OK;
 }
 
-// Longest chunk (16, 32 or 64 pages) that leaves at least 160 work items for `pages` pages.
+// Shared-prefix chunk: the longest of 16, 32, 64 pages that leaves at least 160 work items for
+// `pages` pages.
 static int chunk_shift_for(long long pages) {
   int sh = 6;
   while (sh > 4 && pages < (160LL << sh)) --sh;
@@ -226,11 +237,11 @@ static int chunk_shift_for(long long pages) {
 // speed. With lengths on the host, the chunk lengths are chosen from the pages each kernel
 // actually reads (private pages; group prefixes times their column blocks and kv-heads), and
 // the chunk grid of the private pages is sized to the longest private range; without them the
-// plan's chunk (from batch and max_pages) serves both.
+// private chunk is that of a batch which fills its page table.
 static GroupTable group_table(const kvprm_handle h, const kvprm_batch *b, const Plan &p) {
   GroupTable gt;
   memset(&gt, 0, sizeof gt);
-  gt.cshift_prefix = gt.cshift_private = p.cshift;
+  gt.cshift_prefix = 4;  // (without a prefix: of no effect)
   const bool share = h->dm.kvdt != 0 && b->num_groups > 0 && b->num_groups <= kMaxGroups;
   const int kq = p.kq;  // group ranges are kept in rows (candidates x verify tokens)
   if (share) {
@@ -253,26 +264,22 @@ static GroupTable group_table(const kvprm_handle h, const kvprm_batch *b, const 
       if (ch > gt.prefix_chunks) gt.prefix_chunks = ch;
     }
   }
-  if (b->lengths_host) {
-    long long priv_total = 0;
-    for (int i = 0; i < b->batch; ++i) {
-      int first = 0;
-      for (int k = 0; k < gt.n; ++k)
-        if (i * kq >= gt.start[k] && i * kq < gt.start[k + 1]) first = gt.prefix_pages[k];
-      priv_total += (b->lengths_host[i] + kPage - 1) / kPage - first;
-    }
-    gt.cshift_private = chunk_shift_for(priv_total);
-    const int CP = 1 << gt.cshift_private;
-    int most = 1;
-    for (int i = 0; i < b->batch; ++i) {
-      int first = 0;
-      for (int k = 0; k < gt.n; ++k)
-        if (i * kq >= gt.start[k] && i * kq < gt.start[k + 1]) first = gt.prefix_pages[k];
-      const int priv = (b->lengths_host[i] + kPage - 1) / kPage - first;
-      const int ch = (priv + CP - 1) / CP;
-      if (ch > most) most = ch;
-    }
-    gt.private_chunks = most;
+  int priv[kMaxBatch], slots[kMaxBatch];  // (check_batch: at most kMaxBatch candidates)
+  for (int i = 0; i < b->batch; ++i) {
+    int first = 0;
+    for (int k = 0; k < gt.n; ++k)
+      if (i * kq >= gt.start[k] && i * kq < gt.start[k + 1]) first = gt.prefix_pages[k];
+    priv[i] = b->lengths_host ? (b->lengths_host[i] + kPage - 1) / kPage - first : b->max_pages;
+    slots[i] = p.nch - ((first + (1 << gt.cshift_prefix) - 1) >> gt.cshift_prefix);
+  }
+  const PrivateChunks pc = private_chunk_rule(h->dm, b->batch, priv, slots);
+  gt.cshift_private = pc.shift;
+  gt.heads_per_block = pc.heads_per_block;
+  const int CP = 1 << pc.shift;
+  gt.private_chunks = 1;
+  for (int i = 0; i < b->batch; ++i) {
+    const int ch = (priv[i] + CP - 1) / CP;
+    if (ch > gt.private_chunks) gt.private_chunks = ch;
   }
   return gt;
 }
@@ -420,8 +427,8 @@ static kvprm_status check_options(const kvprm_handle h, const kvprm_batch *b, co
 }
 
 static size_t ws_bytes_ex(const kvprm_handle h, const kvprm_batch *b, const kvprm_lora *lora,
-                          int32_t depth) {
-  const Plan p = make_plan(h->dm, b->batch, b->max_pages, lora ? lora->rank : 0, depth);
+                          int32_t depth, bool lean = false) {
+  const Plan p = make_plan(h->dm, b->batch, b->max_pages, lora ? lora->rank : 0, depth, lean);
   return carve(h->dm, p, nullptr).bytes;
 }
 
@@ -439,7 +446,7 @@ static kvprm_status score_impl(kvprm_handle h, const kvprm_kv_cache *cache, cons
   if ((st = check_cache(h, cache, fn)) != KVPRM_OK) return st;
   if ((st = check_readout(h, wts, fn)) != KVPRM_OK) return st;
   if (!scores) return fail(KVPRM_E_INVALID, "%s: null scores", fn);
-  const size_t need = ws_bytes_ex(h, b, lora, depth);
+  const size_t need = ws_bytes_ex(h, b, lora, depth, true);
   if (!workspace || ws_bytes < need)
     return fail(KVPRM_E_WORKSPACE, "%s: workspace of %zu bytes needed, %zu given", fn, need,
                 workspace ? ws_bytes : (size_t)0);
@@ -449,7 +456,7 @@ static kvprm_status score_impl(kvprm_handle h, const kvprm_kv_cache *cache, cons
 
   const Dims &dm = h->dm;
   hipStream_t s = (hipStream_t)stream;
-  const Plan p = make_plan(dm, b->batch, b->max_pages, lora ? lora->rank : 0, depth);
+  const Plan p = plan_for(h, b, lora ? lora->rank : 0, depth, ws_bytes);
   const Workspace w = carve(dm, p, workspace);
   const GroupTable gt = group_table(h, b, p);
   if (dm.wdt == 1) {
@@ -540,7 +547,7 @@ kvprm_status kvprm_score_static(kvprm_handle h, const kvprm_kv_cache *cache, con
   kvprm_status st = check_batch(h, b, fn);
   if (st != KVPRM_OK) return st;
   if (b->batch == 0) return ok();
-  const size_t need = ws_bytes_for(h, b);
+  const size_t need = ws_bytes_for(h, b, true);
   if (need > (size_t)KVPRM_STATIC_WORKSPACE_BYTES)
     return fail(KVPRM_E_WORKSPACE, "%s: the batch needs %zu bytes of workspace, the static one holds %zu",
                 fn, need, (size_t)KVPRM_STATIC_WORKSPACE_BYTES);
@@ -616,8 +623,8 @@ static kvprm_status check_grad(const kvprm_handle h, const kvprm_batch *b, const
   return KVPRM_OK;
 }
 
-static size_t grad_ws_bytes(const kvprm_handle h, const kvprm_batch *b) {
-  const Plan p = make_plan(h->dm, b->batch, b->max_pages);
+static size_t grad_ws_bytes(const kvprm_handle h, const kvprm_batch *b, bool lean = false) {
+  const Plan p = make_plan(h->dm, b->batch, b->max_pages, 0, 1, lean);
   return align_up(carve(h->dm, p, nullptr).bytes) + carve_grad(h->dm, p, nullptr).bytes;
 }
 
@@ -648,7 +655,7 @@ static kvprm_status grad_impl(kvprm_handle h, const kvprm_kv_cache *cache, const
   if ((st = check_grad(h, b, fn)) != KVPRM_OK) return st;
   if ((st = check_cache(h, cache, fn)) != KVPRM_OK) return st;
   if ((st = check_readout(h, wts, fn)) != KVPRM_OK) return st;
-  const size_t need = grad_ws_bytes(h, b);
+  const size_t need = grad_ws_bytes(h, b, true);
   if (!workspace || ws_bytes < need)
     return fail(KVPRM_E_WORKSPACE, "%s: workspace of %zu bytes needed, %zu given", fn, need,
                 workspace ? ws_bytes : (size_t)0);
@@ -657,13 +664,14 @@ static kvprm_status grad_impl(kvprm_handle h, const kvprm_kv_cache *cache, const
   if ((st = check_pages_debug(h, cache, b, (hipStream_t)stream, fn, true)) != KVPRM_OK) return st;
   const Dims &dm = h->dm;
   hipStream_t s = (hipStream_t)stream;
-  const Plan p = make_plan(dm, b->batch, b->max_pages);
+  const bool lean = ws_bytes < grad_ws_bytes(h, b);
+  const Plan p = make_plan(dm, b->batch, b->max_pages, 0, 1, lean);
   const Workspace w = carve(dm, p, workspace);
   const GradSave sv = carve_grad(dm, p, (char *)workspace + align_up(w.bytes));
   const GroupTable gt = group_table(h, b, p);
-  // the backward attention walks 16-page chunks (partial slots of the plan are sized for them)
+  // the backward attention walks 16-page chunks (the plan has slots for them)
   const int CP = 16;
-  const int chunks = p.nch - 1;
+  const int chunks = (b->max_pages + CP - 1) / CP;
   const size_t layer_bytes = (size_t)cache->num_pages * dm.nkv * kPage * dm.d * 2;
   for (int t = 0; t < steps; ++t) {
     // scores of the cache as it enters each step; the caller's array holds the first
@@ -767,7 +775,7 @@ kvprm_status kvprm_attention(kvprm_handle h, const kvprm_kv_cache *cache, const 
   if ((st = check_ws(h, b, workspace, ws_bytes, fn)) != KVPRM_OK) return st;
   if ((st = check_pages_debug(h, cache, b, (hipStream_t)stream, fn)) != KVPRM_OK) return st;
   const Dims &dm = h->dm;
-  const Plan p = make_plan(dm, b->batch, b->max_pages);
+  const Plan p = plan_for(h, b, 0, 1, ws_bytes);
   const Workspace w = carve(dm, p, workspace);
   HIP_TRY(launch_attention(dm, p, w, layer, cache->k_pages, cache->v_pages, cache->k_scale,
                            cache->v_scale, cache->num_pages, b->page_table, b->lengths,
@@ -791,7 +799,7 @@ kvprm_status kvprm_attention_partials(kvprm_handle h, const kvprm_kv_cache *cach
   if ((st = check_ws(h, b, workspace, ws_bytes, fn)) != KVPRM_OK) return st;
   if ((st = check_pages_debug(h, cache, b, (hipStream_t)stream, fn)) != KVPRM_OK) return st;
   const Dims &dm = h->dm;
-  const Plan p = make_plan(dm, b->batch, b->max_pages);
+  const Plan p = plan_for(h, b, 0, 1, ws_bytes);
   const Workspace w = carve(dm, p, workspace);
   HIP_TRY(launch_attention(dm, p, w, layer, cache->k_pages, cache->v_pages, cache->k_scale,
                            cache->v_scale, cache->num_pages, b->page_table, b->lengths,

@@ -252,8 +252,9 @@ struct AttnArgs {
                   // candidate, group ranges in rows
 };
 
-// One block per (chunk of pages, candidate b) over the candidate's private pages,
-// one wave per kv-head j, so the n_kv tiles of a page (contiguous in the pool) are read together.
+// One block per (chunk of pages, candidate b, group of kv-heads) over the candidate's private
+// pages, one wave per kv-head j (with every head in one block the n_kv tiles of a page,
+// contiguous in the pool, are read together; the call's GroupTable says how many heads).
 // Each wave walks the chunk two pages (32 tokens) at a time: S = K Q^T on the matrix cores
 // (A = the K tile, 16 tokens x 32 dims; B = the g query heads of j as columns, in three bf16
 // terms), online softmax per head in registers (a lane holds 4 tokens of one head per page),
@@ -548,7 +549,8 @@ __global__ __launch_bounds__(NTHR) void k_merge_mx(AttnArgs a) {
     if (b >= a.gt.start[gi] && b < a.gt.start[gi + 1]) first = a.gt.prefix_pages[gi];
   // shared-prefix chunks, then private chunks
   const int sp = a.gt.cshift_prefix, sv = a.gt.cshift_private;
-  const int nc = ((first + (1 << sp) - 1) >> sp) + ((npages - first + (1 << sv) - 1) >> sv);
+  const int nc =
+      min(a.nch, ((first + (1 << sp) - 1) >> sp) + ((npages - first + (1 << sv) - 1) >> sv));
   const float *base = a.apart + ((size_t)b * a.nq + h) * a.nch * (D + 2);
   float rv[R];
 #pragma unroll
@@ -600,7 +602,18 @@ __global__ __launch_bounds__(NTHR) void k_merge_mx(AttnArgs a) {
     const int c = sub + S * i;
     if (c < nc) acc += f_s[c] * rv[i];
   }
-  for (int c = sub + S * R; c < nc; c += S) acc += f_s[c] * base[(size_t)c * (D + 2) + dd];
+  for (int c0 = sub + S * R; c0 < nc; c0 += S * R) {  // further chunks, R loads in flight
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int c = c0 + S * i;
+      rv[i] = c < nc ? base[(size_t)c * (D + 2) + dd] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int c = c0 + S * i;
+      if (c < nc) acc += f_s[c] * rv[i];
+    }
+  }
   sub_s[sub][dd] = acc;
   __syncthreads();
   if (sub != 0) return;
@@ -664,8 +677,11 @@ hipError_t launch_attn_mx(const Dims &dm, const Plan &p, const Workspace &w, con
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  dim3 grid(gt.private_chunks > 0 ? gt.private_chunks : p.nch - 1, p.Breal);
-#define KVPRM_A(KVT, D) hipLaunchKernelGGL((k_attn_mx<KVT, D>), grid, dim3(64 * dm.nkv), 0, s, a)
+  const int hpb = gt.heads_per_block;
+  if (gt.private_chunks < 1 || hpb < 1 || hpb > kMaxKvHeadsMx || dm.nkv % hpb != 0)
+    return hipErrorInvalidValue;
+  const dim3 grid(gt.private_chunks, p.Breal, dm.nkv / hpb);
+#define KVPRM_A(KVT, D) hipLaunchKernelGGL((k_attn_mx<KVT, D>), grid, dim3(64 * hpb), 0, s, a)
   if (dm.kvdt == 1) {
     if (dm.d == 64) KVPRM_A(1, 64);
     else KVPRM_A(1, 128);
@@ -681,9 +697,8 @@ hipError_t launch_attn_mx(const Dims &dm, const Plan &p, const Workspace &w, con
   // for the large fp8 batch; rows of 32 chunks, as in the ragged 32k batch, take 5.3 us against
   // 5.0-5.1 with 512) or when there are more rows than four 512-thread blocks per compute unit
   // hold (the 64-candidate beam: 1792 rows), so that they all run in one round; 512 otherwise
-  // (a row's chunks: its group prefix's and its private pages'; without host lengths, the
-  // plan's chunk slots)
-  const int row_chunks = gt.private_chunks > 0 ? gt.prefix_chunks + gt.private_chunks : p.nch;
+  // (a row's chunks: its group prefix's and its private pages')
+  const int row_chunks = gt.prefix_chunks + gt.private_chunks;
   const bool small = p.B * dm.nq > 1024 || row_chunks <= (256 / dm.d) * 8;
   const dim3 mgrid(p.B, dm.nq);
   if (dm.d == 64) {

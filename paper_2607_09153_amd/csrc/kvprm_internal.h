@@ -28,15 +28,18 @@ struct GroupTable {
   int colblock_start[kMaxGroups + 1];  // shared-prefix column blocks of the groups, cumulative
   int prefix_chunks;                   // chunks of the longest group prefix
   int private_chunks;                  // chunk grid of the private pages (0 = from max_pages)
+  int heads_per_block;                 // kv-heads (waves) of a private-page block
   int cshift_prefix, cshift_private;   // chunk lengths (1 << shift pages) of the two kernels
 };
 
 // Attention split: each work item covers one chunk of pages of one candidate (and kv-head).
-// The matrix-core kernels take the chunk length from the plan (16, 32 or 64 pages); the
-// vector-ALU kernels use kChunkPagesValu.
+// The matrix-core kernels take the chunk length from the call (4 to 64 pages, see
+// private_chunk_shift); the vector-ALU kernels use kChunkPagesValu.
 constexpr int kChunkPagesValu = 32;
 constexpr int kMaxChunks = 1024;  // chunk partials one merge handles
 constexpr int kMaxKvHeadsMx = 8;  // matrix-core attention: one wave per kv-head in a block
+constexpr int kFineChunks = 128;  // chunks of one candidate at most, in chunks under 16 pages
+constexpr int kMaxBatch = 256;    // candidates of a call
 constexpr int kPage = 16;
 
 // Workspace carve-up (all offsets 256-byte aligned).
@@ -74,7 +77,6 @@ struct Plan {
   // row v is verify token v % kq of candidate v / kq. Breal = candidates.
   int B, max_pages, nch;      // nch = chunk slots per (row, q-head), see make_plan
   int kq, Breal;
-  int cshift;                 // matrix-core attention chunk from (B, max_pages): 1 << cshift pages
   int nss;                    // row blocks of H that carry partial sums of squares
   int rb;                     // rows per such block
   // vector-ALU path
@@ -148,7 +150,15 @@ hipError_t launch_stream_read(const void *buf, size_t bytes, uint32_t *sink, hip
 hipError_t launch_pack_kv(const void *src, void *dst, int64_t ntiles, int d, int eb, bool v,
                           hipStream_t s);
 
-Plan make_plan(const Dims &dm, int B, int max_pages, int lora_rank = 0, int depth = 1);
+// lean: chunk slots for chunks of 16 pages and more only (the smallest workspace)
+Plan make_plan(const Dims &dm, int B, int max_pages, int lora_rank = 0, int depth = 1,
+               bool lean = false);
+// Chunk length of the private pages (1 << shift pages) and the heads per block, see the
+// definition: pages[i] = private pages of candidate i, slots[i] = chunk slots they may take.
+struct PrivateChunks {
+  int shift, heads_per_block;
+};
+PrivateChunks private_chunk_rule(const Dims &dm, int n, const int *pages, const int *slots);
 Workspace carve(const Dims &dm, const Plan &p, void *base);
 
 // Kernel launchers (return hipGetLastError()).

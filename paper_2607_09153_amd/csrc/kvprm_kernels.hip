@@ -103,7 +103,51 @@ static size_t partial_elems(const GemvPlan &g) {
   return (size_t)((g.ksplit + 3) & ~3) * g.rows;
 }
 
-Plan make_plan(const Dims &dm, int Breal, int max_pages, int lora_rank, int depth) {
+// Waves (kv-head x chunk) up to which shorter attention chunks pay: a wave takes about 4 us to
+// start and end and 0.7 us per page pair however idle the chip is, so a small batch is fastest
+// in many short chunks, until the waves' fixed cost and the merge's partials outweigh it. For 8 KiB
+// of keys and values per page and head (bf16, d_h = 128; smaller tiles take proportionally more
+// waves to load the memory system).
+static long long chunk_wave_limit(const Dims &dm) {
+  const int page_bytes = 2 * kPage * dm.d * (dm.kvdt == 2 ? 1 : 2);
+  return 800LL * 8192 / page_bytes;
+}
+
+// The shortest chunk of 4, 8, .. 64 pages whose waves stay within chunk_wave_limit and whose
+// chunks fit the slots (kFineChunks below 16 pages); 64 otherwise. Up to 512 waves (of that page
+// size) each wave is a block of its own, so that the work spreads over the compute units (a
+// unit takes in about 50 GB/s: eight heads in one block share that); beyond, four heads to a
+// block up to 1024 waves, then all heads, whose tiles of one page are contiguous. Measured,
+// attention kernel per layer, one head per block / all heads: 1103 tokens x 8 heads 4.9 us in 4-page chunks (24.7 before, 16-page
+// chunks of 8 waves); 4096 tokens x 4 heads 5.1 (4 pages; 16.2 before); four candidates of
+// 4k-8k 11.8 (8 pages; 17.7 before); 16 x 4096 tokens 23.9 (32 pages; 25.2 in 16 pages x all heads); ragged
+// 8 x 16k-32k 69.1 / 66.4 (64 pages).
+PrivateChunks private_chunk_rule(const Dims &dm, int n, const int *pages, const int *slots) {
+  const long long limit = chunk_wave_limit(dm);
+  PrivateChunks r{6, dm.nkv};
+  long long waves = 0;
+  for (int sh = 2; sh <= 6; ++sh) {
+    long long items = 0;
+    bool fits = true;
+    for (int i = 0; i < n; ++i) {
+      const int ch = (pages[i] + (1 << sh) - 1) >> sh;
+      items += ch;
+      if (ch > slots[i] || (sh < 4 && ch > kFineChunks)) fits = false;
+    }
+    waves = items * dm.nkv;
+    if (waves <= limit && fits) {
+      r.shift = sh;
+      break;
+    }
+  }
+  if (waves <= limit * 512 / 800)
+    r.heads_per_block = 1;
+  else if (waves <= limit * 1024 / 800 && dm.nkv % 4 == 0)
+    r.heads_per_block = 4;
+  return r;
+}
+
+Plan make_plan(const Dims &dm, int Breal, int max_pages, int lora_rank, int depth, bool lean) {
   Plan p{};
   const int B = Breal * depth;  // rows of the pass (verify tokens of all candidates)
   p.B = B;
@@ -111,17 +155,17 @@ Plan make_plan(const Dims &dm, int Breal, int max_pages, int lora_rank, int dept
   p.kq = depth;
   p.max_pages = max_pages;
   p.lora_rank = lora_rank;
-  // Matrix-core attention chunk: the longest of 16, 32, 64 pages that still gives at least 160
-  // work items (of 256 compute units) for a batch that fills its page table (longer chunks
-  // stream longer page runs per wave: measured faster even with some units idle), and at most
-  // kMaxChunks - 2 chunks per candidate.
-  p.cshift = 6;
-  while (p.cshift > 4 && (long long)Breal * max_pages < (160LL << p.cshift)) --p.cshift;
-
-  // chunk slots: chunks of max_pages at the shortest chunk (16 pages: the call may pick shorter
-  // chunks than the plan from the host lengths) plus one (a shared prefix that ends inside a
-  // chunk adds one), for whichever attention path runs
-  const int n_mx = ((max_pages + 15) >> 4) + 1;
+  // chunk slots: chunks of max_pages at 16 pages (a long batch's chunks are no shorter) plus one
+  // (a shared prefix that ends inside a chunk adds one), for whichever attention path runs; more
+  // where the batch is small enough for shorter chunks (private_chunk_rule)
+  int n_mx = ((max_pages + 15) >> 4) + 1;
+  if (!lean) {
+    long long fine = chunk_wave_limit(dm) / ((long long)Breal * dm.nkv);
+    const long long all = (max_pages + 3) >> 2;
+    fine = fine < all ? fine : all;
+    fine = (fine < kFineChunks ? fine : kFineChunks) + 1;
+    if (n_mx < fine) n_mx = (int)fine;
+  }
   const int n_valu = (max_pages + kChunkPagesValu - 1) / kChunkPagesValu + 1;
   p.nch = dm.kvdt == 0 ? n_valu : n_mx;
   size_t m = 0;
