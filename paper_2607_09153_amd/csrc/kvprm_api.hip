@@ -195,16 +195,6 @@ static size_t ws_bytes_for(const kvprm_handle h, const kvprm_batch *b, bool lean
   return carve(h->dm, p, nullptr).bytes;
 }
 
-// The call's plan: with slots for short attention chunks where the workspace holds them (one sized
-// by kvprm_workspace_size does), else the lean one (a workspace kept from another batch may be
-// large enough for that only).
-static Plan plan_for(const kvprm_handle h, const kvprm_batch *b, int rank, int depth,
-                     size_t ws_bytes) {
-  const Plan p = make_plan(h->dm, b->batch, b->max_pages, rank, depth);
-  if (carve(h->dm, p, nullptr).bytes <= ws_bytes) return p;
-  return make_plan(h->dm, b->batch, b->max_pages, rank, depth, true);
-}
-
 kvprm_status kvprm_workspace_size(kvprm_handle h, const kvprm_batch *b, size_t *bytes) {
   if (!h || !bytes) return fail(KVPRM_E_INVALID, "kvprm_workspace_size: null argument");
   kvprm_status st = check_batch(h, b, "kvprm_workspace_size");
@@ -213,12 +203,19 @@ kvprm_status kvprm_workspace_size(kvprm_handle h, const kvprm_batch *b, size_t *
   return ok();
 }
 
-static kvprm_status check_ws(const kvprm_handle h, const kvprm_batch *b, void *ws, size_t n,
-                             const char *fn) {
-  const size_t need = ws_bytes_for(h, b, true);
-  if (!ws || n < need)
-    return fail(KVPRM_E_WORKSPACE, "%s: workspace of %zu bytes needed, %zu given", fn, need,
-                ws ? n : (size_t)0);
+// Checks the workspace and gives the call's plan: with slots for short attention chunks where the
+// workspace holds them (one sized by kvprm_workspace_size does), else the lean one (a workspace
+// kept from another batch may be large enough for that only).
+static kvprm_status plan_for(const kvprm_handle h, const kvprm_batch *b, int rank, int depth,
+                             void *ws, size_t n, Plan *p, const char *fn) {
+  *p = make_plan(h->dm, b->batch, b->max_pages, rank, depth);
+  if (!ws || n < carve(h->dm, *p, nullptr).bytes) {
+    *p = make_plan(h->dm, b->batch, b->max_pages, rank, depth, true);
+    const size_t need = carve(h->dm, *p, nullptr).bytes;
+    if (!ws || n < need)
+      return fail(KVPRM_E_WORKSPACE, "%s: workspace of %zu bytes needed, %zu given", fn, need,
+                  ws ? n : (size_t)0);
+  }
   if (((uintptr_t)ws & 255) != 0) return fail(KVPRM_E_WORKSPACE, "%s: workspace not 256-byte aligned", fn);
   return KVPRM_OK;
 }
@@ -427,8 +424,8 @@ static kvprm_status check_options(const kvprm_handle h, const kvprm_batch *b, co
 }
 
 static size_t ws_bytes_ex(const kvprm_handle h, const kvprm_batch *b, const kvprm_lora *lora,
-                          int32_t depth, bool lean = false) {
-  const Plan p = make_plan(h->dm, b->batch, b->max_pages, lora ? lora->rank : 0, depth, lean);
+                          int32_t depth) {
+  const Plan p = make_plan(h->dm, b->batch, b->max_pages, lora ? lora->rank : 0, depth);
   return carve(h->dm, p, nullptr).bytes;
 }
 
@@ -446,17 +443,13 @@ static kvprm_status score_impl(kvprm_handle h, const kvprm_kv_cache *cache, cons
   if ((st = check_cache(h, cache, fn)) != KVPRM_OK) return st;
   if ((st = check_readout(h, wts, fn)) != KVPRM_OK) return st;
   if (!scores) return fail(KVPRM_E_INVALID, "%s: null scores", fn);
-  const size_t need = ws_bytes_ex(h, b, lora, depth, true);
-  if (!workspace || ws_bytes < need)
-    return fail(KVPRM_E_WORKSPACE, "%s: workspace of %zu bytes needed, %zu given", fn, need,
-                workspace ? ws_bytes : (size_t)0);
-  if (((uintptr_t)workspace & 255) != 0)
-    return fail(KVPRM_E_WORKSPACE, "%s: workspace not 256-byte aligned", fn);
+  Plan p;
+  if ((st = plan_for(h, b, lora ? lora->rank : 0, depth, workspace, ws_bytes, &p, fn)) != KVPRM_OK)
+    return st;
   if ((st = check_pages_debug(h, cache, b, (hipStream_t)stream, fn)) != KVPRM_OK) return st;
 
   const Dims &dm = h->dm;
   hipStream_t s = (hipStream_t)stream;
-  const Plan p = plan_for(h, b, lora ? lora->rank : 0, depth, ws_bytes);
   const Workspace w = carve(dm, p, workspace);
   const GroupTable gt = group_table(h, b, p);
   if (dm.wdt == 1) {
@@ -772,10 +765,10 @@ kvprm_status kvprm_attention(kvprm_handle h, const kvprm_kv_cache *cache, const 
   if (layer < 0 || layer >= h->dm.layers)
     return fail(KVPRM_E_INVALID, "%s: layer %d outside [0, %d)", fn, layer, h->dm.layers);
   if (!q || !k_self || !v_self || !o) return fail(KVPRM_E_INVALID, "%s: null q/k_self/v_self/o", fn);
-  if ((st = check_ws(h, b, workspace, ws_bytes, fn)) != KVPRM_OK) return st;
+  Plan p;
+  if ((st = plan_for(h, b, 0, 1, workspace, ws_bytes, &p, fn)) != KVPRM_OK) return st;
   if ((st = check_pages_debug(h, cache, b, (hipStream_t)stream, fn)) != KVPRM_OK) return st;
   const Dims &dm = h->dm;
-  const Plan p = plan_for(h, b, 0, 1, ws_bytes);
   const Workspace w = carve(dm, p, workspace);
   HIP_TRY(launch_attention(dm, p, w, layer, cache->k_pages, cache->v_pages, cache->k_scale,
                            cache->v_scale, cache->num_pages, b->page_table, b->lengths,
@@ -796,10 +789,10 @@ kvprm_status kvprm_attention_partials(kvprm_handle h, const kvprm_kv_cache *cach
   if (layer < 0 || layer >= h->dm.layers)
     return fail(KVPRM_E_INVALID, "%s: layer %d outside [0, %d)", fn, layer, h->dm.layers);
   if (!q) return fail(KVPRM_E_INVALID, "%s: null q", fn);
-  if ((st = check_ws(h, b, workspace, ws_bytes, fn)) != KVPRM_OK) return st;
+  Plan p;
+  if ((st = plan_for(h, b, 0, 1, workspace, ws_bytes, &p, fn)) != KVPRM_OK) return st;
   if ((st = check_pages_debug(h, cache, b, (hipStream_t)stream, fn)) != KVPRM_OK) return st;
   const Dims &dm = h->dm;
-  const Plan p = plan_for(h, b, 0, 1, ws_bytes);
   const Workspace w = carve(dm, p, workspace);
   HIP_TRY(launch_attention(dm, p, w, layer, cache->k_pages, cache->v_pages, cache->k_scale,
                            cache->v_scale, cache->num_pages, b->page_table, b->lengths,

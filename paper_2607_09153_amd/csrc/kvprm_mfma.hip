@@ -312,8 +312,9 @@ __device__ __forceinline__ float wave_rms_finish(const float *__restrict__ ss, i
 // r_b = 1 / sqrt(mean(x_b^2) + eps) for every candidate, computed by a whole block of NTHR
 // threads from the per-row-block sums of squares ss[i][b] into inv_s[b]: with Bq = B rounded up
 // to a power of two, thread t sums rows t / Bq, t / Bq + NTHR / Bq, ... of candidate t % Bq,
-// and the NTHR / Bq partial sums of each candidate are added in a fixed order, so every block
-// gets identical values. rms_load issues a thread's first 16 loads (unconditional, clamped,
+// and the NTHR / Bq partial sums of each candidate are added in a fixed order (a butterfly over a
+// wave's lanes of one candidate, then the waves in order), so every block gets identical values.
+// (One thread adding them all took 6 us of the 7B gate/up kernel's 49 for a single candidate.) rms_load issues a thread's first 16 loads (unconditional, clamped,
 // zero past the end) so that callers can start them early; rms_finish adds any further rows,
 // reduces, and contains two barriers.
 struct RmsLoads {
@@ -351,11 +352,13 @@ __device__ __forceinline__ void rms_finish(const float *__restrict__ ss, int nss
 #pragma unroll
   for (int u = 0; u < 16; ++u) v += ld.v[u];
   if (b < B) rms_tail(ss, B, b, part + 16 * P, P, nss, v);
-  part_s[t] = v;
+  for (int off = Bq; off < 64; off <<= 1) v += __shfl_xor(v, off, 64);
+  if ((t & 63) < Bq) part_s[(t >> 6) * Bq + b] = v;
   __syncthreads();
   if (t < B) {
     float s = 0.f;
-    for (int k = 0; k < P; ++k) s += part_s[k * Bq + t];
+#pragma unroll
+    for (int k = 0; k < NTHR / 64; ++k) s += part_s[k * Bq + t];
     inv_s[t] = 1.0f / sqrtf(s / (float)H + eps);
   }
   __syncthreads();
@@ -1487,14 +1490,33 @@ hipError_t launch_gateup_fused(const Dims &dm, const Plan &p, const Workspace &w
   a.nseg = 2;
   a.op = w.opD;
   const dim3 grid(dm.F / 16);
+  const int pairs = dm.F / 16;
+  // Few pairs: one per block, its eight waves splitting the input (k_gemv_fused), so that the pairs
+  // spread over the compute units and no wave walks the whole input alone: up to a block per
+  // compute unit, and with more than 16 rows, where a wave of the shared-operand kernel is bound by its
+  // products, up to two. Against the shared-operand kernel in blocks of 4 pairs, us per layer:
+  // 192 pairs x 1024 inputs 11.4 -> 7.5 (1 row), 11.3 -> 7.7 (16), 17.5 -> 11.1 (48 rows);
+  // 128 x 2048 15.5 -> 9.7 (1), 25.0 -> 12.6 (32); 384 x 2560 32.3 -> 23.1 (32 rows), but
+  // 20.3 -> 25.3 (16 rows); 768 x 4096 64 -> 76 (64 rows).
+  if (pairs <= (p.nt >= 4 ? 512 : 256)) {
+    switch (p.nt) {
+      case 1: hipLaunchKernelGGL((k_gemv_fused<2, 1, 8, 4, EPI_SWIGLU>), grid, dim3(512), 0, s, a); break;
+      case 2: hipLaunchKernelGGL((k_gemv_fused<2, 2, 8, 4, EPI_SWIGLU>), grid, dim3(512), 0, s, a); break;
+      case 4: hipLaunchKernelGGL((k_gemv_fused<2, 4, 8, 2, EPI_SWIGLU>), grid, dim3(512), 0, s, a); break;
+      case 6: hipLaunchKernelGGL((k_gemv_fused<2, 6, 8, 1, EPI_SWIGLU>), grid, dim3(512), 0, s, a); break;
+      case 8: hipLaunchKernelGGL((k_gemv_fused<2, 8, 8, 1, EPI_SWIGLU>), grid, dim3(512), 0, s, a); break;
+      default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  }
   // Shared-operand kernel (k_gateup_wide): HALF gate/up tile pairs per block (2 HALF waves),
   // chosen so that every compute unit gets at most one block where possible: with 4 pairs, the
   // 1184 pairs of the 7B shape make 296 blocks, and the 40 compute units holding two set the
-  // kernel's length (beam: 5 pairs, 237 blocks: 8.42 -> 7.90 ms per call).
+  // kernel's length (beam: 5 pairs, 237 blocks: 8.42 -> 7.90 ms per call); 384 and 512 pairs take 2
+  // (19.9 -> 16.7 and 18.0 -> 15.9 us against 4), 768 pairs 3 (64 rows: 64.1 -> 60.9).
   constexpr int UW = 4;  // batch depth
-  const int pairs = dm.F / 16;
   int half = (pairs + 255) / 256;
-  half = half < 4 ? 4 : (half > 8 ? 8 : half);
+  half = half > 8 ? 8 : half;
   const dim3 wgrid((pairs + half - 1) / half);
   const bool wide = (dm.H / 32) % UW == 0;
   // more than 16 candidates: one gate/up pair per wave (k_gateup_pair), as many pairs per block
@@ -1502,6 +1524,7 @@ hipError_t launch_gateup_fused(const Dims &dm, const Plan &p, const Workspace &w
   if (wide && p.nt >= 4) {
 #define KVPRM_GP(NT_)                                                                                 \
   switch (half) {                                                                                  \
+    case 3: hipLaunchKernelGGL((k_gateup_pair<NT_, 3, UW>), wgrid, dim3(192), 0, s, a); break;      \
     case 4: hipLaunchKernelGGL((k_gateup_pair<NT_, 4, UW>), wgrid, dim3(256), 0, s, a); break;      \
     case 5: hipLaunchKernelGGL((k_gateup_pair<NT_, 5, UW>), wgrid, dim3(320), 0, s, a); break;      \
     case 6: hipLaunchKernelGGL((k_gateup_pair<NT_, 6, UW>), wgrid, dim3(384), 0, s, a); break;      \
@@ -1516,6 +1539,8 @@ hipError_t launch_gateup_fused(const Dims &dm, const Plan &p, const Workspace &w
   }
 #define KVPRM_GW(NT_)                                                                                \
   switch (half) {                                                                                 \
+    case 2: hipLaunchKernelGGL((k_gateup_wide<NT_, 4, UW>), wgrid, dim3(256), 0, s, a); break;     \
+    case 3: hipLaunchKernelGGL((k_gateup_wide<NT_, 6, UW>), wgrid, dim3(384), 0, s, a); break;     \
     case 4: hipLaunchKernelGGL((k_gateup_wide<NT_, 8, UW>), wgrid, dim3(512), 0, s, a); break;     \
     case 5: hipLaunchKernelGGL((k_gateup_wide<NT_, 10, UW>), wgrid, dim3(640), 0, s, a); break;    \
     case 6: hipLaunchKernelGGL((k_gateup_wide<NT_, 12, UW>), wgrid, dim3(768), 0, s, a); break;    \
