@@ -111,8 +111,8 @@ static kvprm_status check_batch(const kvprm_handle h, const kvprm_batch *b, cons
   if (!b->page_table || !b->lengths) return fail(KVPRM_E_INVALID, "%s: null page_table or lengths", fn);
   if (b->max_pages < 1) return fail(KVPRM_E_INVALID, "%s: max_pages < 1", fn);
   // chunk slots per candidate: one per chunk of max_pages, plus one where a shared prefix
-  // splits a chunk (16-page chunks; 32 on the vector-ALU path)
-  const int max_mp = (kMaxChunks - 2) * (h->dm.kvdt == 0 ? kChunkPagesValu : 16);
+  // splits a chunk (16-page chunks; 32 with fp32 caches)
+  const int max_mp = (kMaxChunks - 2) * (h->dm.kvdt == 0 ? kChunkPagesF32 : 16);
   if (b->max_pages > max_mp)
     return fail(KVPRM_E_UNSUPPORTED, "%s: max_pages above %d", fn, max_mp);
   const int cap = b->max_pages * h->desc.page_size;
@@ -229,7 +229,7 @@ static int chunk_shift_for(long long pages) {
 }
 
 // Launch table of the attention kernels. The prefix-sharing hint is used by the matrix-core
-// attention only (fp32 caches take the vector-ALU path, which reads every page per candidate)
+// attention only (the fp32 attention reads every page per candidate)
 // and only for up to kMaxGroups groups; otherwise it is ignored, which changes nothing but
 // speed. With lengths on the host, the chunk lengths are chosen from the pages each kernel
 // actually reads (private pages; group prefixes times their column blocks and kv-heads), and
@@ -335,9 +335,6 @@ static kvprm_status score_mx(const kvprm_handle h, const kvprm_kv_cache *cache,
                              const GroupTable &gt, float *scores, float *logits, hipStream_t s,
                              const GradSave *sv = nullptr) {
   const Dims &dm = h->dm;
-  const int EB = dm.kvdt == 0 ? 4 : (dm.kvdt == 1 ? 2 : 1);
-  const size_t layer_bytes = (size_t)cache->num_pages * dm.nkv * kPage * dm.d * EB;
-  const size_t layer_scales = (size_t)cache->num_pages * dm.nkv;
   const int tkb = lora ? lora->rank / 32 : 0;
   const LoraTail none{{nullptr, nullptr, nullptr}, 0};
   auto tail_of = [&](const void *b0, const void *b1, const void *b2) {
@@ -372,13 +369,13 @@ static kvprm_status score_mx(const kvprm_handle h, const kvprm_kv_cache *cache,
       HIP_TRY(launch_lora_a(dm, p, w, LORA_QKV, a_qkv, lora->scale, w.opA, s), "q/k/v adapter");
     }
     HIP_TRY(launch_qkv_mx(dm, p, wl, W.wq, W.wk, W.wv, t_qkv, s), "qkv projection");
-    HIP_TRY(launch_attn_mx(dm, p, w, (const char *)cache->k_pages + layer_bytes * l,
-                           (const char *)cache->v_pages + layer_bytes * l,
-                           cache->k_scale ? cache->k_scale + layer_scales * l : nullptr,
-                           cache->v_scale ? cache->v_scale + layer_scales * l : nullptr,
-                           b->page_table, b->lengths, gt, wl.q, wl.kself, wl.vself, o_save,
-                           w.opO, s, true, lse_save),
+    HIP_TRY(launch_attention(dm, p, w, l, cache->k_pages, cache->v_pages, cache->k_scale,
+                             cache->v_scale, cache->num_pages, b->page_table, b->lengths, gt, wl.q,
+                             s),
             "attention");
+    HIP_TRY(launch_merge_mx(dm, p, w, b->lengths, gt, wl.q, wl.kself, wl.vself, o_save, w.opO, s,
+                            lse_save),
+            "attention merge");
     if (lora && t_o.tkb) {
       const void *a_o[3] = {lora->layers[l].o.a, nullptr, nullptr};
       HIP_TRY(launch_lora_a(dm, p, w, LORA_O, a_o, lora->scale, w.opO, s), "output adapter");
@@ -429,8 +426,8 @@ static size_t ws_bytes_ex(const kvprm_handle h, const kvprm_batch *b, const kvpr
   return carve(h->dm, p, nullptr).bytes;
 }
 
-// Every scoring entry point: validation, then the matrix-core pipeline (bf16 weights) or the
-// vector-ALU one (fp32 weights; no adapter, depth 1).
+// Every scoring entry point: validation, then the bf16 pipeline or the fp32 one (fp32 weights; no
+// adapter, depth 1).
 static kvprm_status score_impl(kvprm_handle h, const kvprm_kv_cache *cache, const kvprm_batch *b,
                                const kvprm_readout_weights *wts, const kvprm_lora *lora,
                                int32_t depth, void *workspace, size_t ws_bytes, float *scores,
@@ -457,30 +454,22 @@ static kvprm_status score_impl(kvprm_handle h, const kvprm_kv_cache *cache, cons
       return st;
     return ok();
   }
-  // vector-ALU pipeline (fp32 weights)
-  HIP_TRY(launch_init(dm, p, w, wts->verify_embed, s), "init");
+  // fp32 pipeline: six launches per layer
+  HIP_TRY(launch_init_f32(dm, p, w, wts->verify_embed, wts->layers[0].attn_norm, b->lengths, s),
+          "init");
   for (int l = 0; l < dm.layers; ++l) {
     const kvprm_layer_weights &W = wts->layers[l];
-    GemvSegs qkv{{W.wq, W.wk, W.wv}, {dm.nq * dm.d, dm.nkv * dm.d, dm.nkv * dm.d}, 3};
-    HIP_TRY(launch_gemv(dm, p, qkv, dm.H, p.kslice_qkv, p.ks_qkv, w.x, W.attn_norm, w.ss, w.part, s),
-            "qkv projection");
-    HIP_TRY(launch_qkv_finish(dm, p, w, b->lengths, s), "rotary");
-    HIP_TRY(launch_attention(dm, p, w, l, cache->k_pages, cache->v_pages, cache->k_scale,
-                             cache->v_scale, cache->num_pages, b->page_table, b->lengths, gt, w.q,
-                             w.kself, w.vself, w.o, s),
+    const void *gamma_next = l + 1 < dm.layers ? wts->layers[l + 1].attn_norm : nullptr;
+    HIP_TRY(launch_qkv_f32(dm, p, w, W.wq, W.wk, W.wv, s), "qkv projection");
+    HIP_TRY(launch_attention(dm, p, w, l, cache->k_pages, cache->v_pages, nullptr, nullptr,
+                             cache->num_pages, b->page_table, b->lengths, gt, w.q, s),
             "attention");
-    GemvSegs wo{{W.wo, nullptr, nullptr}, {dm.H, 0, 0}, 1};
-    HIP_TRY(launch_gemv(dm, p, wo, dm.nq * dm.d, p.kslice_o, p.ks_o, w.o, nullptr, nullptr, w.part, s),
+    HIP_TRY(launch_merge_mx(dm, p, w, b->lengths, gt, w.q, w.kself, w.vself, w.o, nullptr, s),
+            "attention merge");
+    HIP_TRY(launch_resid_f32(dm, p, w, W.wo, w.o, dm.nq * dm.d, W.ffn_norm, s),
             "output projection");
-    HIP_TRY(launch_residual(dm, p, w, p.ks_o, s), "residual");
-    GemvSegs gu{{W.w_gate, W.w_up, nullptr}, {dm.F, dm.F, 0}, 2};
-    HIP_TRY(launch_gemv(dm, p, gu, dm.H, p.kslice_gu, p.ks_gu, w.x, W.ffn_norm, w.ss, w.part, s),
-            "gate/up projection");
-    HIP_TRY(launch_swiglu(dm, p, w, p.ks_gu, s), "swiglu");
-    GemvSegs dn{{W.w_down, nullptr, nullptr}, {dm.H, 0, 0}, 1};
-    HIP_TRY(launch_gemv(dm, p, dn, dm.F, p.kslice_d, p.ks_d, w.hffn, nullptr, nullptr, w.part, s),
-            "down projection");
-    HIP_TRY(launch_residual(dm, p, w, p.ks_d, s), "residual");
+    HIP_TRY(launch_gateup_f32(dm, p, w, W.w_gate, W.w_up, s), "gate/up projection");
+    HIP_TRY(launch_resid_f32(dm, p, w, W.w_down, w.hffn, dm.F, gamma_next, s), "down projection");
   }
   HIP_TRY(launch_head(dm, p, w, wts->final_norm, wts->reward_w, wts->reward_b, scores, logits, s),
           "reward head");
@@ -770,10 +759,14 @@ kvprm_status kvprm_attention(kvprm_handle h, const kvprm_kv_cache *cache, const 
   if ((st = check_pages_debug(h, cache, b, (hipStream_t)stream, fn)) != KVPRM_OK) return st;
   const Dims &dm = h->dm;
   const Workspace w = carve(dm, p, workspace);
+  const GroupTable gt = group_table(h, b, p);
   HIP_TRY(launch_attention(dm, p, w, layer, cache->k_pages, cache->v_pages, cache->k_scale,
-                           cache->v_scale, cache->num_pages, b->page_table, b->lengths,
-                           group_table(h, b, p), q, k_self, v_self, o, (hipStream_t)stream),
+                           cache->v_scale, cache->num_pages, b->page_table, b->lengths, gt, q,
+                           (hipStream_t)stream),
           "attention");
+  HIP_TRY(launch_merge_mx(dm, p, w, b->lengths, gt, q, k_self, v_self, o, nullptr,
+                          (hipStream_t)stream),
+          "attention merge");
   return ok();
 }
 
@@ -796,8 +789,7 @@ kvprm_status kvprm_attention_partials(kvprm_handle h, const kvprm_kv_cache *cach
   const Workspace w = carve(dm, p, workspace);
   HIP_TRY(launch_attention(dm, p, w, layer, cache->k_pages, cache->v_pages, cache->k_scale,
                            cache->v_scale, cache->num_pages, b->page_table, b->lengths,
-                           group_table(h, b, p), q, nullptr, nullptr, nullptr,
-                           (hipStream_t)stream, false),
+                           group_table(h, b, p), q, (hipStream_t)stream),
           "attention partials");
   return ok();
 }

@@ -632,36 +632,65 @@ __global__ __launch_bounds__(NTHR) void k_merge_mx(AttnArgs a) {
   if (a.op) store_operand(a.op, a.NT, a.Bp, h * D + dd, b, ov);
 }
 
-hipError_t launch_attn_mx(const Dims &dm, const Plan &p, const Workspace &w, const char *kp,
-                          const char *vp, const float *ksc, const float *vsc,
-                          const int32_t *page_table, const int32_t *lengths, const GroupTable &gt,
-                          const float *q, const float *kself, const float *vself, float *o,
-                          uint16_t *op, hipStream_t s, bool merge, float *lse) {
+static AttnArgs attn_args(const Dims &dm, const Plan &p, const Workspace &w,
+                          const int32_t *lengths, const GroupTable &gt, const float *q) {
   AttnArgs a;
   memset(&a, 0, sizeof a);
-  a.lse = lse;
-  a.kp = kp;
-  a.vp = vp;
-  a.ksc = ksc;
-  a.vsc = vsc;
   a.nkv = dm.nkv;
   a.g = dm.g;
   a.ginv = (65536 + dm.g - 1) / dm.g;
   a.nq = dm.nq;
-  a.page_table = page_table;
   a.max_pages = p.max_pages;
   a.lengths = lengths;
   a.gt = gt;
   a.nch = p.nch;
   a.q = q;
-  a.kself = kself;
-  a.vself = vself;
   a.apart = w.apart;
-  a.o = o;
-  a.op = op;
   a.NT = p.nt;
   a.Bp = p.bp;
   a.kq = p.kq;
+  return a;
+}
+
+hipError_t launch_merge_mx(const Dims &dm, const Plan &p, const Workspace &w,
+                           const int32_t *lengths, const GroupTable &gt, const float *q,
+                           const float *kself, const float *vself, float *o, uint16_t *op,
+                           hipStream_t s, float *lse) {
+  AttnArgs a = attn_args(dm, p, w, lengths, gt, q);
+  a.kself = kself;
+  a.vself = vself;
+  a.o = o;
+  a.op = op;
+  a.lse = lse;
+  // 256 threads per (row, q-head) when each of their 256 / D chunk subsets has at most 8 of the
+  // row's chunks (16 at d_h = 128: per merge 5.2 -> 5.1 us for the 7B batch of 16, 6.4 -> 5.9 us
+  // for the large fp8 batch; rows of 32 chunks, as in the ragged 32k batch, take 5.3 us against
+  // 5.0-5.1 with 512) or when there are more rows than four 512-thread blocks per compute unit
+  // hold (the 64-candidate beam: 1792 rows), so that they all run in one round; 512 otherwise
+  // (a row's chunks: its group prefix's and its private pages')
+  const int row_chunks = gt.prefix_chunks + gt.private_chunks;
+  const bool small = p.B * dm.nq > 1024 || row_chunks <= (256 / dm.d) * 8;
+  const dim3 mgrid(p.B, dm.nq);
+  if (dm.d == 64) {
+    if (small) hipLaunchKernelGGL((k_merge_mx<64, 256>), mgrid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((k_merge_mx<64, 512>), mgrid, dim3(512), 0, s, a);
+  } else {
+    if (small) hipLaunchKernelGGL((k_merge_mx<128, 256>), mgrid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((k_merge_mx<128, 512>), mgrid, dim3(512), 0, s, a);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_attn_mx(const Dims &dm, const Plan &p, const Workspace &w, const char *kp,
+                          const char *vp, const float *ksc, const float *vsc,
+                          const int32_t *page_table, const int32_t *lengths, const GroupTable &gt,
+                          const float *q, hipStream_t s) {
+  AttnArgs a = attn_args(dm, p, w, lengths, gt, q);
+  a.kp = kp;
+  a.vp = vp;
+  a.ksc = ksc;
+  a.vsc = vsc;
+  a.page_table = page_table;
   if (gt.n > 0) {
     dim3 pgrid(gt.prefix_chunks, dm.nkv, gt.colblock_start[gt.n]);
 #define KVPRM_P(KVT, D) \
@@ -690,24 +719,6 @@ hipError_t launch_attn_mx(const Dims &dm, const Plan &p, const Workspace &w, con
     else KVPRM_A(2, 128);
   }
 #undef KVPRM_A
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !merge) return e;
-  // 256 threads per (row, q-head) when each of their 256 / D chunk subsets has at most 8 of the
-  // row's chunks (16 at d_h = 128: per merge 5.2 -> 5.1 us for the 7B batch of 16, 6.4 -> 5.9 us
-  // for the large fp8 batch; rows of 32 chunks, as in the ragged 32k batch, take 5.3 us against
-  // 5.0-5.1 with 512) or when there are more rows than four 512-thread blocks per compute unit
-  // hold (the 64-candidate beam: 1792 rows), so that they all run in one round; 512 otherwise
-  // (a row's chunks: its group prefix's and its private pages')
-  const int row_chunks = gt.prefix_chunks + gt.private_chunks;
-  const bool small = p.B * dm.nq > 1024 || row_chunks <= (256 / dm.d) * 8;
-  const dim3 mgrid(p.B, dm.nq);
-  if (dm.d == 64) {
-    if (small) hipLaunchKernelGGL((k_merge_mx<64, 256>), mgrid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((k_merge_mx<64, 512>), mgrid, dim3(512), 0, s, a);
-  } else {
-    if (small) hipLaunchKernelGGL((k_merge_mx<128, 256>), mgrid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((k_merge_mx<128, 512>), mgrid, dim3(512), 0, s, a);
-  }
   return hipGetLastError();
 }
 

@@ -33,9 +33,9 @@ struct GroupTable {
 };
 
 // Attention split: each work item covers one chunk of pages of one candidate (and kv-head).
-// The matrix-core kernels take the chunk length from the call (4 to 64 pages, see
-// private_chunk_shift); the vector-ALU kernels use kChunkPagesValu.
-constexpr int kChunkPagesValu = 32;
+// The kernels take the chunk length from the call (4 to 64 pages, fp32 caches 2 to 32; see
+// private_chunk_rule).
+constexpr int kChunkPagesF32 = 32;  // longest chunk of an fp32 cache
 constexpr int kMaxChunks = 1024;  // chunk partials one merge handles
 constexpr int kMaxKvHeadsMx = 8;  // matrix-core attention: one wave per kv-head in a block
 constexpr int kFineChunks = 128;  // chunks of one candidate at most, in chunks under 16 pages
@@ -46,15 +46,18 @@ constexpr int kPage = 16;
 struct Workspace {
   float *x;        // [B][H] residual stream
   float *ss;       // [nss][B] partial sums of squares of x
-  float *part;     // GEMV split-K partials [ksplit][rows][B]
+  float *part;     // split-K partials
   float *q;        // [B][nq][d]
   float *kself;    // [B][nkv][d]
   float *vself;    // [B][nkv][d]
   float *apart;    // attention partials [B][nq][nch][d + 2] (acc..., m, l)
   float *o;        // [B][nq * d]
-  float *hffn;     // [B][F] (vector-ALU path)
+  float *hffn;     // [B][F] SwiGLU output (fp32 pipeline)
   uint16_t *topd;  // adapter operand slots [3][rank / 32][NT][64][8] bf16 (scale * A u)
-  // matrix-core path
+  // fp32 pipeline
+  float *u;        // [B][H] x * gamma of the next RMSNorm
+  double *rope64;  // [B][d/2][2] cos, sin of the verify position
+  // bf16 pipeline
   float *rope;       // [B][d/2][2] cos, sin of the verify position
   uint16_t *opA;     // GEMV operands (bf16 hi/lo): QKV and gate/up input (K = H)
   uint16_t *opO;     //   output projection input (K = n_q d)
@@ -77,12 +80,8 @@ struct Plan {
   // row v is verify token v % kq of candidate v / kq. Breal = candidates.
   int B, max_pages, nch;      // nch = chunk slots per (row, q-head), see make_plan
   int kq, Breal;
-  int nss;                    // row blocks of H that carry partial sums of squares
-  int rb;                     // rows per such block
-  // vector-ALU path
-  int ks_qkv, ks_o, ks_gu, ks_d;  // split-K counts
-  int kslice_qkv, kslice_o, kslice_gu, kslice_d;
-  // matrix-core path
+  int nss;                    // 16-row tiles of H: partial sums of squares
+  // bf16 pipeline
   int nt, bp;                 // operand column tiles and padded batch
   // low-rank adapter (0 = none): the split-K plans of the A-factor products of the q/k/v,
   // output, gate/up and down groups
@@ -162,18 +161,19 @@ PrivateChunks private_chunk_rule(const Dims &dm, int n, const int *pages, const 
 Workspace carve(const Dims &dm, const Plan &p, void *base);
 
 // Kernel launchers (return hipGetLastError()).
-hipError_t launch_init(const Dims &dm, const Plan &p, const Workspace &w, const void *verify_embed,
-                       hipStream_t s);
-// Y partials = W_seg . u, u = in (optionally RMS-normalised with gamma using ss). Up to three
-// row segments with their own weight pointers (e.g. q, k, v).
-struct GemvSegs {
-  const void *w[3];
-  int rows[3];
-  int nseg;
-};
-hipError_t launch_gemv(const Dims &dm, const Plan &p, const GemvSegs &segs, int K, int kslice,
-                       int ksplit, const float *in, const void *gamma, const float *ss,
-                       float *part, hipStream_t s);
+// fp32 pipeline (kvprm_f32.hip)
+hipError_t launch_init_f32(const Dims &dm, const Plan &p, const Workspace &w, const void *ev,
+                           const void *gamma0, const int32_t *lengths, hipStream_t s);
+hipError_t launch_qkv_f32(const Dims &dm, const Plan &p, const Workspace &w, const void *wq,
+                          const void *wk, const void *wv, hipStream_t s);
+hipError_t launch_gateup_f32(const Dims &dm, const Plan &p, const Workspace &w, const void *wg,
+                             const void *wu, hipStream_t s);
+// output and down projections: x += W in, u = x * gamma (if gamma)
+hipError_t launch_resid_f32(const Dims &dm, const Plan &p, const Workspace &w, const void *wt,
+                            const float *in, int K, const void *gamma, hipStream_t s);
+hipError_t launch_attn_f32(const Dims &dm, const Plan &p, const Workspace &w, const float *kp,
+                           const float *vp, const int32_t *page_table, const int32_t *lengths,
+                           const GroupTable &gt, const float *q, hipStream_t s);
 // matrix-core pipeline (bf16 weights)
 // xsave (optional): a copy of the residual stream x as initialised
 hipError_t launch_init_mx(const Dims &dm, const Plan &p, const Workspace &w, const void *ev,
@@ -197,23 +197,22 @@ hipError_t launch_gateup_fused(const Dims &dm, const Plan &p, const Workspace &w
 hipError_t launch_down_fused(const Dims &dm, const Plan &p, const Workspace &w, const void *wd,
                              const void *gamma_next, const LoraTail &tail, hipStream_t s,
                              float *xsave = nullptr);
+// the attention's chunk partials (shared prefixes and private pages) into w.apart ...
 hipError_t launch_attn_mx(const Dims &dm, const Plan &p, const Workspace &w, const char *kp,
                           const char *vp, const float *ksc, const float *vsc,
                           const int32_t *page_table, const int32_t *lengths, const GroupTable &gt,
-                          const float *q, const float *kself, const float *vself, float *o,
-                          uint16_t *op, hipStream_t s, bool merge = true, float *lse = nullptr);
-hipError_t launch_qkv_finish(const Dims &dm, const Plan &p, const Workspace &w,
-                             const int32_t *lengths, hipStream_t s);
+                          const float *q, hipStream_t s);
+// ... and their merge with the own keys (any pipeline), into o, the operand op and lse where given
+hipError_t launch_merge_mx(const Dims &dm, const Plan &p, const Workspace &w,
+                           const int32_t *lengths, const GroupTable &gt, const float *q,
+                           const float *kself, const float *vself, float *o, uint16_t *op,
+                           hipStream_t s, float *lse = nullptr);
+// launch_attn_mx or launch_attn_f32 for one layer of the pools
 hipError_t launch_attention(const Dims &dm, const Plan &p, const Workspace &w, int layer,
                             const void *kpool, const void *vpool, const float *kscale,
                             const float *vscale, int num_pages, const int32_t *page_table,
                             const int32_t *lengths, const GroupTable &gt, const float *q,
-                            const float *kself, const float *vself, float *o, hipStream_t s,
-                            bool merge = true);
-hipError_t launch_residual(const Dims &dm, const Plan &p, const Workspace &w, int ksplit,
-                           hipStream_t s);
-hipError_t launch_swiglu(const Dims &dm, const Plan &p, const Workspace &w, int ksplit,
-                         hipStream_t s);
+                            hipStream_t s);
 hipError_t launch_head(const Dims &dm, const Plan &p, const Workspace &w, const void *final_norm,
                        const void *reward_w, float reward_b, float *scores, float *logits,
                        hipStream_t s);

@@ -1130,7 +1130,7 @@ hipError_t launch_pack_weight(const void *src, void *dst, int64_t rows, int64_t 
 hipError_t launch_init_mx(const Dims &dm, const Plan &p, const Workspace &w, const void *ev,
                           const void *gamma0, const int32_t *lengths, hipStream_t s,
                           float *xsave) {
-  hipLaunchKernelGGL(k_init_mx, dim3(p.nss), dim3(256), 0, s, w.x, w.ss, p.rb, ev, gamma0, dm.wdt,
+  hipLaunchKernelGGL(k_init_mx, dim3(p.nss), dim3(256), 0, s, w.x, w.ss, 16, ev, gamma0, dm.wdt,
                      p.B, dm.H, w.opA, p.nt, p.bp, lengths, p.kq, dm.theta, dm.d, w.rope, xsave);
   return hipGetLastError();
 }
