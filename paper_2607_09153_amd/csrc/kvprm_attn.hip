@@ -552,12 +552,12 @@ __global__ __launch_bounds__(NTHR) void k_merge_mx(AttnArgs a) {
   const int nc =
       min(a.nch, ((first + (1 << sp) - 1) >> sp) + ((npages - first + (1 << sv) - 1) >> sv));
   const float *base = a.apart + ((size_t)b * a.nq + h) * a.nch * (D + 2);
+  // (chunks past the last read the last one again, so that no load is conditional; they are not
+  // added. A row without chunks reads slot 0, which exists)
   float rv[R];
+  const int clast = max(nc, 1) - 1;
 #pragma unroll
-  for (int i = 0; i < R; ++i) {
-    const int c = sub + S * i;
-    rv[i] = c < nc ? base[(size_t)c * (D + 2) + dd] : 0.f;
-  }
+  for (int i = 0; i < R; ++i) rv[i] = base[min(sub + S * i, clast) * (D + 2) + dd];
   float mx = -INFINITY;
   for (int c = t; c < nc; c += NTHR) {
     const float m = base[(size_t)c * (D + 2) + D];

@@ -21,16 +21,6 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
-// Sum over a 256-thread block; every thread gets the result. red must hold 4 floats.
-__device__ __forceinline__ float block_sum256(float v, float *red) {
-  v = wave_sum(v);
-  const int w = threadIdx.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[w] = v;
-  __syncthreads();
-  return (red[0] + red[1]) + (red[2] + red[3]);
-}
-
 // ------------------------------------------------------------------------------- plan
 
 // Split-K plan of a matrix-core GEMV, in whole 32-wide input blocks: about 32 blocks per wave
@@ -175,24 +165,31 @@ Plan make_plan(const Dims &dm, int Breal, int max_pages, int lora_rank, int dept
     // of one more launch. Measured per call: the down projection for every batch size (ragged
     // 32k 4.79-4.82 -> 4.73-4.76 ms, 7B batch of 16 3.86 -> 3.59), q/k/v too for 9-16 rows (3.57),
     // all three for 9-16 rows with at least 512 row tiles (large fp8 24.6 -> 23.7) and for more
-    // than 16 rows (beam 7.92 -> 6.74 with output and down, 6.8 -> 6.75 with q/k/v).
+    // than 16 rows (beam 7.92 -> 6.74 with output and down, 6.8 -> 6.75 with q/k/v). Short products
+    // lose more to the second launch than they gain, us per layer fused / split: q/k/v up to 16 M
+    // weights (H = 1024: 56 / 61 at 48 rows, 47 / 52 at 16; H = 2560, 15.7 M: 122.4 / 124.2 at 64),
+    // the output projection from fewer than 1024 inputs (H = 256: 33.9 / 40.2 at 32 rows), and with
+    // one column tile the down projection of up to 8192 inputs over at least 128 row tiles
+    // (H = 2048, F = 2048: 45.4 / 47.4 at one row; H = 256, F = 1024: 32.8 / 30.8).
     {
       // input blocks per batch of k_resid_split; with one column tile 16 where the input widths
       // divide (ragged 32k 4.75 -> 4.69 ms per call against 8), else 8
       int U = 4;
       if (p.nt == 1) U = (dm.nq * dm.d / 32) % 16 == 0 && (dm.F / 32) % 16 == 0 ? 16 : 8;
-      // bits: 1 down, 2 output, 4 q/k/v
-      const int mask = p.nt >= 4 ? 7 : p.nt == 2 ? (dm.H / 16 >= 512 ? 7 : 5) : 1;
+      const bool down = !(p.nt == 1 && dm.H >= 2048 && dm.F <= 8192);
+      const bool out = p.nt >= 4 ? dm.nq * dm.d >= 1024 : p.nt == 2 && dm.H / 16 >= 512;
+      const long long qkv_weights = (long long)(dm.nq + 2 * dm.nkv) * dm.d * dm.H;
+      const bool qkv = p.nt >= 2 && (pairs > 256 || qkv_weights > 16000000);
       if ((dm.nq * dm.d / 32) % U == 0 && (dm.F / 32) % U == 0) {
         // (8 row tiles per block measured faster than 16: 6.74 against 6.79 ms per call of the
         // 64-candidate beam)
         p.rs_wpb = 8;
         p.rs_u = U;
-        p.rs_d = mask & 1;
-        p.rs_o = (mask >> 1) & 1;
+        p.rs_d = down;
+        p.rs_o = out;
         p.g_rs_o = resid_split_plan(dm.H, dm.nq * dm.d, p.rs_wpb, U);
         p.g_rs_d = resid_split_plan(dm.H, dm.F, p.rs_wpb, U);
-        if ((mask & 4) && (dm.H / 32) % U == 0 && (dm.nq + 2 * dm.nkv) * (dm.d / 2) >= 64) {
+        if (qkv && (dm.H / 32) % U == 0 && (dm.nq + 2 * dm.nkv) * (dm.d / 2) >= 64) {
           p.rs_qkv = 1;
           p.g_rs_qkv = resid_split_plan((dm.nq + 2 * dm.nkv) * dm.d, dm.H, p.rs_wpb, U);
         }
@@ -315,36 +312,51 @@ hipError_t launch_attention(const Dims &dm, const Plan &p, const Workspace &w, i
 
 // z_b = w_r . (x_b / sqrt(mean(x_b^2) + eps) * gamma_f) + b_r; P(+) = sigmoid(z_b). One pass
 // over x_b: sum(x^2) and sum(x gamma_f w_r) together (the RMS scale is a common factor of the
-// dot product), four rows per thread in flight.
-__global__ __launch_bounds__(256) void k_head(const float *x, int H, float eps, const void *gam,
-                                              const void *wr, int wdt, float rb, float *scores,
-                                              float *logits, int kq) {
-  __shared__ float red[4];
+// dot product). One block per candidate, so the kernel is one memory round trip and a reduction:
+// 1024 threads with eight elements each in flight (256 threads walking the row took 9.4 us at
+// H = 3584 and 18.8 at 8192; now 4.5 and 7.0).
+constexpr int kHeadThreads = 1024;
+__global__ __launch_bounds__(kHeadThreads) void k_head(const float *x, int H, float eps,
+                                                       const void *gam, const void *wr, int wdt,
+                                                       float rb, float *scores, float *logits,
+                                                       int kq) {
+  constexpr int U = 8, NW = kHeadThreads / 64;
+  __shared__ float red[2][NW];
   const int b = blockIdx.x;
   const float *xb = x + ((size_t)b * kq + kq - 1) * H;  // the candidate's last verify token
   float sq = 0.f, dot = 0.f;
-  int r = threadIdx.x;
-  for (; r + 3 * 256 < H; r += 4 * 256) {
-    float v[4], gw[4];
+  for (int r0 = threadIdx.x; r0 < H; r0 += U * kHeadThreads) {
+    float v[U], gv[U], wv[U];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      v[u] = xb[r + u * 256];
-      gw[u] = load_scalar(gam, r + u * 256, wdt) * load_scalar(wr, r + u * 256, wdt);
+    for (int u = 0; u < U; ++u) {
+      if (r0 + u * kHeadThreads < H) {
+        v[u] = xb[r0 + u * kHeadThreads];
+        gv[u] = load_scalar(gam, r0 + u * kHeadThreads, wdt);
+        wv[u] = load_scalar(wr, r0 + u * kHeadThreads, wdt);
+      } else {
+        v[u] = gv[u] = wv[u] = 0.f;
+      }
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < U; ++u) {
       sq += v[u] * v[u];
-      dot += v[u] * gw[u];
+      dot += v[u] * (gv[u] * wv[u]);
     }
   }
-  for (; r < H; r += 256) {
-    const float v = xb[r];
-    sq += v * v;
-    dot += v * (load_scalar(gam, r, wdt) * load_scalar(wr, r, wdt));
+  sq = wave_sum(sq);
+  dot = wave_sum(dot);
+  if ((threadIdx.x & 63) == 0) {
+    red[0][threadIdx.x >> 6] = sq;
+    red[1][threadIdx.x >> 6] = dot;
   }
-  sq = block_sum256(sq, red);
-  dot = block_sum256(dot, red);
+  __syncthreads();
   if (threadIdx.x == 0) {
+    sq = dot = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      sq += red[0][w];
+      dot += red[1][w];
+    }
     const float inv = 1.0f / sqrtf(sq / (float)H + eps);
     const float z = dot * inv + rb;
     float pz;
@@ -362,7 +374,7 @@ __global__ __launch_bounds__(256) void k_head(const float *x, int H, float eps, 
 hipError_t launch_head(const Dims &dm, const Plan &p, const Workspace &w, const void *final_norm,
                        const void *reward_w, float reward_b, float *scores, float *logits,
                        hipStream_t s) {
-  hipLaunchKernelGGL(k_head, dim3(p.Breal), dim3(256), 0, s, w.x, dm.H, dm.eps, final_norm,
+  hipLaunchKernelGGL(k_head, dim3(p.Breal), dim3(kHeadThreads), 0, s, w.x, dm.H, dm.eps, final_norm,
                      reward_w, dm.wdt, reward_b, scores, logits, p.kq);
   return hipGetLastError();
 }
