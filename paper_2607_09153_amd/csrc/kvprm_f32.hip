@@ -91,7 +91,7 @@ struct F32Args {
 // the small shapes this path serves, a launch is all latency: fusing the element-wise step and
 // spreading one row tile over eight waves takes the place of one thread per row and separate
 // kernels (two-layer shape H = 256, 4 candidates: 22 launches, 23-53 us per projection, 490 us a
-// call, before; 14 launches and 87 us now).
+// call, before; 14 launches and 63 us now).
 template <int MT, int NG, int WPB, int EPI>
 __global__ __launch_bounds__(64 * WPB) void k_gemv32(F32Args a) {
   constexpr int NC = 16 * NG, P = 64 * WPB / NC;  // candidates, threads per candidate (RMSNorm)
@@ -100,7 +100,8 @@ __global__ __launch_bounds__(64 * WPB) void k_gemv32(F32Args a) {
   static_assert(P >= 1 && NG <= WPB, "one wave per candidate group in the epilogue");
   __shared__ floatx4 red_s[WPB][MT][NG][64];
   __shared__ float part_s[P][NC], inv_s[NC];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int n = lane & 15, c = lane >> 4;
   const int B = a.B, K = a.K, b0 = blockIdx.y * NC;
   int tile[MT];
@@ -132,14 +133,15 @@ __global__ __launch_bounds__(64 * WPB) void k_gemv32(F32Args a) {
   for (int m = 0; m < MT; ++m)
 #pragma unroll
     for (int g = 0; g < NG; ++g) acc[m][g] = floatx4{0.f, 0.f, 0.f, 0.f};
-  // this wave's input blocks [k0, k1), U at a time (clamped loads past the end, not multiplied)
+  // this wave's input blocks [k0, k1), U at a time (wave-uniform bounds)
   const int nkb = K >> 4, per = (nkb + WPB - 1) / WPB;
   const int k0 = min(nkb, wave * per), k1 = min(nkb, k0 + per);
   f32x4u wa[U][MT], ua[U][NG], wb[U][MT], ub[U][NG];
   auto load = [&](int kb, f32x4u(&w)[U][MT], f32x4u(&u)[U][NG]) {
 #pragma unroll
     for (int i = 0; i < U; ++i) {
-      const size_t k = (size_t)min(kb + i, nkb - 1) * 16;
+      if (kb + i >= k1) break;
+      const size_t k = (size_t)(kb + i) * 16;
 #pragma unroll
       for (int m = 0; m < MT; ++m) w[i][m] = *(const f32x4u *)(wp[m] + k);
 #pragma unroll
@@ -149,7 +151,7 @@ __global__ __launch_bounds__(64 * WPB) void k_gemv32(F32Args a) {
   auto mma = [&](int kb, const f32x4u(&w)[U][MT], const f32x4u(&u)[U][NG]) {
 #pragma unroll
     for (int i = 0; i < U; ++i) {
-      if (kb + i >= k1) break;  // wave-uniform
+      if (kb + i >= k1) break;
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
