@@ -158,9 +158,8 @@ kvprm_status kvprm_create(const kvprm_model_desc *desc, kvprm_handle *out);
 /* Release a handle (NULL is accepted). */
 kvprm_status kvprm_destroy(kvprm_handle h);
 
-/* Bytes of device workspace kvprm_score and kvprm_attention use for this batch (it depends on
- * batch and max_pages only). For a small batch that includes room for splitting its attention
- * more finely; a call given less, but enough for 16-page chunks, runs without that. */
+/* Bytes of device workspace kvprm_score and kvprm_attention need for this batch (it depends on
+ * batch and max_pages only). */
 kvprm_status kvprm_workspace_size(kvprm_handle h, const kvprm_batch *batch, size_t *bytes);
 
 /* Eq. (score) for every candidate: scores[b] = P(+) in [0, 1] and, if logits != NULL,

@@ -203,19 +203,14 @@ kvprm_status kvprm_workspace_size(kvprm_handle h, const kvprm_batch *b, size_t *
   return ok();
 }
 
-// Checks the workspace and gives the call's plan: with slots for short attention chunks where the
-// workspace holds them (one sized by kvprm_workspace_size does), else the lean one (a workspace
-// kept from another batch may be large enough for that only).
+// The call's plan, if the workspace holds it.
 static kvprm_status plan_for(const kvprm_handle h, const kvprm_batch *b, int rank, int depth,
-                             void *ws, size_t n, Plan *p, const char *fn) {
-  *p = make_plan(h->dm, b->batch, b->max_pages, rank, depth);
-  if (!ws || n < carve(h->dm, *p, nullptr).bytes) {
-    *p = make_plan(h->dm, b->batch, b->max_pages, rank, depth, true);
-    const size_t need = carve(h->dm, *p, nullptr).bytes;
-    if (!ws || n < need)
-      return fail(KVPRM_E_WORKSPACE, "%s: workspace of %zu bytes needed, %zu given", fn, need,
-                  ws ? n : (size_t)0);
-  }
+                             bool lean, void *ws, size_t n, Plan *p, const char *fn) {
+  *p = make_plan(h->dm, b->batch, b->max_pages, rank, depth, lean);
+  const size_t need = carve(h->dm, *p, nullptr).bytes;
+  if (!ws || n < need)
+    return fail(KVPRM_E_WORKSPACE, "%s: workspace of %zu bytes needed, %zu given", fn, need,
+                ws ? n : (size_t)0);
   if (((uintptr_t)ws & 255) != 0) return fail(KVPRM_E_WORKSPACE, "%s: workspace not 256-byte aligned", fn);
   return KVPRM_OK;
 }
@@ -431,7 +426,7 @@ static size_t ws_bytes_ex(const kvprm_handle h, const kvprm_batch *b, const kvpr
 static kvprm_status score_impl(kvprm_handle h, const kvprm_kv_cache *cache, const kvprm_batch *b,
                                const kvprm_readout_weights *wts, const kvprm_lora *lora,
                                int32_t depth, void *workspace, size_t ws_bytes, float *scores,
-                               float *logits, void *stream, const char *fn) {
+                               float *logits, void *stream, const char *fn, bool lean = false) {
   if (!h) return fail(KVPRM_E_INVALID, "%s: null handle", fn);
   kvprm_status st = check_batch(h, b, fn);
   if (st != KVPRM_OK) return st;
@@ -441,7 +436,8 @@ static kvprm_status score_impl(kvprm_handle h, const kvprm_kv_cache *cache, cons
   if ((st = check_readout(h, wts, fn)) != KVPRM_OK) return st;
   if (!scores) return fail(KVPRM_E_INVALID, "%s: null scores", fn);
   Plan p;
-  if ((st = plan_for(h, b, lora ? lora->rank : 0, depth, workspace, ws_bytes, &p, fn)) != KVPRM_OK)
+  if ((st = plan_for(h, b, lora ? lora->rank : 0, depth, lean, workspace, ws_bytes, &p, fn)) !=
+      KVPRM_OK)
     return st;
   if ((st = check_pages_debug(h, cache, b, (hipStream_t)stream, fn)) != KVPRM_OK) return st;
 
@@ -535,8 +531,10 @@ kvprm_status kvprm_score_static(kvprm_handle h, const kvprm_kv_cache *cache, con
                 fn, need, (size_t)KVPRM_STATIC_WORKSPACE_BYTES);
   void *ws = nullptr;
   if ((st = static_workspace((hipStream_t)stream, &ws, fn)) != KVPRM_OK) return st;
+  // (short attention chunks where their slots fit as well)
+  const bool lean = ws_bytes_for(h, b) > (size_t)KVPRM_STATIC_WORKSPACE_BYTES;
   return score_impl(h, cache, b, wts, nullptr, 1, ws, (size_t)KVPRM_STATIC_WORKSPACE_BYTES, scores,
-                    logits, stream, fn);
+                    logits, stream, fn, lean);
 }
 
 kvprm_status kvprm_workspace_size_lora(kvprm_handle h, const kvprm_batch *b, int32_t rank,
@@ -605,8 +603,8 @@ static kvprm_status check_grad(const kvprm_handle h, const kvprm_batch *b, const
   return KVPRM_OK;
 }
 
-static size_t grad_ws_bytes(const kvprm_handle h, const kvprm_batch *b, bool lean = false) {
-  const Plan p = make_plan(h->dm, b->batch, b->max_pages, 0, 1, lean);
+static size_t grad_ws_bytes(const kvprm_handle h, const kvprm_batch *b) {
+  const Plan p = make_plan(h->dm, b->batch, b->max_pages);
   return align_up(carve(h->dm, p, nullptr).bytes) + carve_grad(h->dm, p, nullptr).bytes;
 }
 
@@ -637,7 +635,7 @@ static kvprm_status grad_impl(kvprm_handle h, const kvprm_kv_cache *cache, const
   if ((st = check_grad(h, b, fn)) != KVPRM_OK) return st;
   if ((st = check_cache(h, cache, fn)) != KVPRM_OK) return st;
   if ((st = check_readout(h, wts, fn)) != KVPRM_OK) return st;
-  const size_t need = grad_ws_bytes(h, b, true);
+  const size_t need = grad_ws_bytes(h, b);
   if (!workspace || ws_bytes < need)
     return fail(KVPRM_E_WORKSPACE, "%s: workspace of %zu bytes needed, %zu given", fn, need,
                 workspace ? ws_bytes : (size_t)0);
@@ -646,18 +644,23 @@ static kvprm_status grad_impl(kvprm_handle h, const kvprm_kv_cache *cache, const
   if ((st = check_pages_debug(h, cache, b, (hipStream_t)stream, fn, true)) != KVPRM_OK) return st;
   const Dims &dm = h->dm;
   hipStream_t s = (hipStream_t)stream;
-  const bool lean = ws_bytes < grad_ws_bytes(h, b);
-  const Plan p = make_plan(dm, b->batch, b->max_pages, 0, 1, lean);
+  const Plan p = make_plan(dm, b->batch, b->max_pages);
   const Workspace w = carve(dm, p, workspace);
   const GradSave sv = carve_grad(dm, p, (char *)workspace + align_up(w.bytes));
   const GroupTable gt = group_table(h, b, p);
-  // the backward attention walks 16-page chunks (the plan has slots for them)
-  const int CP = 16;
-  const int chunks = (b->max_pages + CP - 1) / CP;
+  int pages[kMaxBatch], chunks = 0;
+  for (int i = 0; i < b->batch; ++i)
+    pages[i] = b->lengths_host ? (b->lengths_host[i] + kPage - 1) / kPage : b->max_pages;
+  const int CP = backward_chunk_pages(dm, b->batch, pages, p.nch_bwd);
+  for (int i = 0; i < b->batch; ++i) {
+    const int ch = (pages[i] + CP - 1) / CP;
+    chunks = ch > chunks ? ch : chunks;
+  }
+  if (chunks < 1) chunks = 1;  // (empty caches: a grid of blocks that leave at once)
   const size_t layer_bytes = (size_t)cache->num_pages * dm.nkv * kPage * dm.d * 2;
   for (int t = 0; t < steps; ++t) {
     // scores of the cache as it enters each step; the caller's array holds the first
-    if ((st = score_mx(h, cache, b, wts, nullptr, p, w, gt, t == 0 ? scores : sv.Dh, nullptr, s,
+    if ((st = score_mx(h, cache, b, wts, nullptr, p, w, gt, t == 0 ? scores : sv.scores, nullptr, s,
                        &sv)) != KVPRM_OK)
       return st;
     HIP_TRY(launch_backward(dm, p, w, sv, wts->layers, wts->final_norm, wts->reward_w,
@@ -755,7 +758,7 @@ kvprm_status kvprm_attention(kvprm_handle h, const kvprm_kv_cache *cache, const 
     return fail(KVPRM_E_INVALID, "%s: layer %d outside [0, %d)", fn, layer, h->dm.layers);
   if (!q || !k_self || !v_self || !o) return fail(KVPRM_E_INVALID, "%s: null q/k_self/v_self/o", fn);
   Plan p;
-  if ((st = plan_for(h, b, 0, 1, workspace, ws_bytes, &p, fn)) != KVPRM_OK) return st;
+  if ((st = plan_for(h, b, 0, 1, false, workspace, ws_bytes, &p, fn)) != KVPRM_OK) return st;
   if ((st = check_pages_debug(h, cache, b, (hipStream_t)stream, fn)) != KVPRM_OK) return st;
   const Dims &dm = h->dm;
   const Workspace w = carve(dm, p, workspace);
@@ -783,7 +786,7 @@ kvprm_status kvprm_attention_partials(kvprm_handle h, const kvprm_kv_cache *cach
     return fail(KVPRM_E_INVALID, "%s: layer %d outside [0, %d)", fn, layer, h->dm.layers);
   if (!q) return fail(KVPRM_E_INVALID, "%s: null q", fn);
   Plan p;
-  if ((st = plan_for(h, b, 0, 1, workspace, ws_bytes, &p, fn)) != KVPRM_OK) return st;
+  if ((st = plan_for(h, b, 0, 1, false, workspace, ws_bytes, &p, fn)) != KVPRM_OK) return st;
   if ((st = check_pages_debug(h, cache, b, (hipStream_t)stream, fn)) != KVPRM_OK) return st;
   const Dims &dm = h->dm;
   const Workspace w = carve(dm, p, workspace);

@@ -53,17 +53,22 @@ __device__ __forceinline__ float sum_lanes(float v) {
   return v;
 }
 
-// Sum over a block of NTHR threads (multiple of 64); every thread gets the result.
+// Sums of u and v over a block of NTHR threads (multiple of 64), in place in every thread.
 template <int NTHR>
-__device__ __forceinline__ float block_sum(float v, float *red) {
+__device__ __forceinline__ void block_sum2(float &u, float &v, float (*red)[NTHR / 64]) {
+  u = wave_sum(u);
   v = wave_sum(v);
+  if ((threadIdx.x & 63) == 0) {
+    red[0][threadIdx.x >> 6] = u;
+    red[1][threadIdx.x >> 6] = v;
+  }
   __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  float s = 0.f;
+  u = v = 0.f;
 #pragma unroll
-  for (int w = 0; w < NTHR / 64; ++w) s += red[w];
-  return s;
+  for (int w = 0; w < NTHR / 64; ++w) {
+    u += red[0][w];
+    v += red[1][w];
+  }
 }
 
 __device__ __forceinline__ uint4 ld_nt(const uint4 *p) {
@@ -92,10 +97,15 @@ __device__ __forceinline__ floatx4 mma16(const uint2 &a, const uint2 &b, const f
                                                    __builtin_bit_cast(shortx4, b), c, 0, 0, 0);
 }
 
-// x = hi + lo with hi, lo bf16 (nearest-even each): hi * y + lo * y keeps ~16 bits of x
-__device__ __forceinline__ void split_bf16(float x, uint32_t &hi, uint32_t &lo) {
-  hi = bf16_round(x);
-  lo = bf16_round(x - bf(hi));
+// Two fp32 values as packed bf16 pairs hi and lo = the rest after hi (the hardware pack-convert,
+// nearest-even)
+__device__ __forceinline__ void split_pair(float x0, float x1, uint32_t &hi, uint32_t &lo) {
+  typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
+  typedef float f32x2v __attribute__((ext_vector_type(2)));
+  const f32x2v xv = {x0, x1};
+  hi = __builtin_bit_cast(uint32_t, __builtin_convertvector(xv, bf16x2v));
+  const f32x2v rv = {x0 - __uint_as_float(hi << 16), x1 - __uint_as_float(hi & 0xFFFF0000u)};
+  lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(rv, bf16x2v));
 }
 
 }  // namespace
@@ -105,25 +115,35 @@ __device__ __forceinline__ void split_bf16(float x, uint32_t &hi, uint32_t &lo) 
 // Reward head backward for one candidate per block: z = w_r . (x r gamma) + b_r with
 // r = 1/sqrt(mean(x^2) + eps); the loss -log sigmoid(z) has dz = sigmoid(z) - 1, and
 // dx = dz (r gamma w_r - (r^3 / H) x sum_i gamma_i w_r,i x_i).
-__global__ __launch_bounds__(256) void k_head_bwd(const float *x, const void *gam, const void *wr,
-                                                  float rb, int H, float eps, float *dx,
-                                                  float *dxT, int B) {
-  __shared__ float red[4];
+// (1024 threads, four elements each in flight: 7.1 -> 5.0 us at H = 3584 against 256 threads.)
+__global__ __launch_bounds__(1024) void k_head_bwd(const float *x, const void *gam, const void *wr,
+                                                   float rb, int H, float eps, float *dx,
+                                                   float *dxT, int B) {
+  constexpr int U = 4;
+  __shared__ float red[2][16];
   const int b = blockIdx.x;
   const float *xb = x + (size_t)b * H;
   float sq = 0.f, dot = 0.f;
-  for (int i = threadIdx.x; i < H; i += 256) {
-    const float v = xb[i];
-    sq += v * v;
-    dot += v * ldw(gam, i) * ldw(wr, i);
+  for (int i0 = threadIdx.x; i0 < H; i0 += U * 1024) {
+    float v[U], gw[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u * 1024;
+      v[u] = i < H ? xb[i] : 0.f;
+      gw[u] = i < H ? ldw(gam, i) * ldw(wr, i) : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      sq += v[u] * v[u];
+      dot += v[u] * gw[u];
+    }
   }
-  sq = block_sum<256>(sq, red);
-  dot = block_sum<256>(dot, red);
+  block_sum2<1024>(sq, dot, red);
   const float r = 1.0f / sqrtf(sq / (float)H + eps);
   const float z = dot * r + rb;
   const float dz = 1.0f / (1.0f + expf(-z)) - 1.0f;
   const float c = r * r * r / (float)H * dot;
-  for (int i = threadIdx.x; i < H; i += 256) {
+  for (int i = threadIdx.x; i < H; i += 1024) {
     const float v = dz * (r * ldw(gam, i) * ldw(wr, i) - c * xb[i]);
     dx[(size_t)b * H + i] = v;
     dxT[(size_t)i * kDPad + b] = v;
@@ -132,41 +152,54 @@ __global__ __launch_bounds__(256) void k_head_bwd(const float *x, const void *ga
 
 // RMSNorm backward plus the residual path, one candidate per block:
 // out = res + r (gamma dy) - (r^3 / H) x sum_i gamma_i dy_i x_i (out may be res), also written
-// transposed to outT [H][kDPad]. Each thread keeps its inputs in registers between the two
-// passes (H <= kGradMaxHidden).
-constexpr int kRmsPer = kGradMaxHidden / 1024;
+// transposed to outT [H][kDPad]. Each thread keeps its PER inputs in registers between the two
+// passes (H <= 1024 PER; PER = 4, 8 or 16, kGradMaxHidden at most), every load issued at entry.
+template <int PER>
 __global__ __launch_bounds__(1024) void k_rms_bwd(const float *x, const void *gam, const float *dy,
                                                   const float *res, float *out, float *outT, int B,
                                                   int H, float eps) {
-  __shared__ float red[16];
+  __shared__ float red[2][16];
   const int b = blockIdx.x;
   const size_t o = (size_t)b * H;
-  float xv[kRmsPer], gd[kRmsPer];
+  float xv[PER], gd[PER], rv[PER];
   float sq = 0.f, dot = 0.f;
 #pragma unroll
-  for (int k = 0; k < kRmsPer; ++k) {
-    const int i = threadIdx.x + k * 1024;
-    xv[k] = i < H ? x[o + i] : 0.f;
-    gd[k] = i < H ? ldw(gam, i) * dy[o + i] : 0.f;
+  for (int k = 0; k < PER; ++k) {
+    const int i = threadIdx.x + k * 1024, ic = min(i, H - 1);
+    xv[k] = x[o + ic];
+    gd[k] = ldw(gam, ic) * dy[o + ic];
+    rv[k] = res[o + ic];
   }
 #pragma unroll
-  for (int k = 0; k < kRmsPer; ++k) {
-    sq += xv[k] * xv[k];
-    dot += gd[k] * xv[k];
+  for (int k = 0; k < PER; ++k) {
+    const bool in = (int)threadIdx.x + k * 1024 < H;
+    sq += in ? xv[k] * xv[k] : 0.f;
+    dot += in ? gd[k] * xv[k] : 0.f;
   }
-  sq = block_sum<1024>(sq, red);
-  dot = block_sum<1024>(dot, red);
+  block_sum2<1024>(sq, dot, red);
   const float r = 1.0f / sqrtf(sq / (float)H + eps);
   const float c = r * r * r / (float)H * dot;
 #pragma unroll
-  for (int k = 0; k < kRmsPer; ++k) {
+  for (int k = 0; k < PER; ++k) {
     const int i = threadIdx.x + k * 1024;
     if (i < H) {
-      const float v = res[o + i] + r * gd[k] - c * xv[k];
+      const float v = rv[k] + r * gd[k] - c * xv[k];
       out[o + i] = v;
       outT[(size_t)i * kDPad + b] = v;
     }
   }
+}
+
+static hipError_t rms_bwd(const float *x, const void *gam, const float *dy, const float *res,
+                          float *out, float *outT, int B, int H, float eps, hipStream_t s) {
+  static_assert(kGradMaxHidden <= 16 * 1024, "inputs per thread");
+  if (H <= 4 * 1024)
+    hipLaunchKernelGGL(k_rms_bwd<4>, dim3(B), dim3(1024), 0, s, x, gam, dy, res, out, outT, B, H, eps);
+  else if (H <= 8 * 1024)
+    hipLaunchKernelGGL(k_rms_bwd<8>, dim3(B), dim3(1024), 0, s, x, gam, dy, res, out, outT, B, H, eps);
+  else
+    hipLaunchKernelGGL(k_rms_bwd<16>, dim3(B), dim3(1024), 0, s, x, gam, dy, res, out, outT, B, H, eps);
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------------------- W^T d
@@ -224,7 +257,10 @@ __global__ __launch_bounds__(256) void k_tgemv_mx(TgemvArgs a) {
   if (act) load(t0, wa);  // in flight while d is staged
   // staging: item (tile tl, row group q) reads rows 16 (t0 + tl) + 4q .. + 3 and writes the hi
   // and lo operands of every candidate for lanes 16 q + m and 16 q + 8 + m
-  for (int it = threadIdx.x; it < NT * 4; it += 256) {
+  // (the split's tiles and the 2U zero ones that the last batches reach, no more: a short split
+  // staged the whole window before)
+  const int staged = min(NT, t1 - t0 + 2 * U);
+  for (int it = threadIdx.x; it < staged * 4; it += 256) {
     const int tl = it >> 2, q = it & 3;
     float dv[4][8];
     const bool live = tl < t1 - t0;
@@ -241,15 +277,12 @@ __global__ __launch_bounds__(256) void k_tgemv_mx(TgemvArgs a) {
     }
 #pragma unroll
     for (int m = 0; m < 8; ++m) {
-      uint32_t hi[4], lo[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float v = m < a.B ? dv[i][m] : 0.f;
-        hi[i] = bf16_round(v);
-        lo[i] = bf16_round(v - bf(hi[i]));
-      }
-      dop_s[tl][16 * q + m] = make_uint2(hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16));
-      dop_s[tl][16 * q + 8 + m] = make_uint2(lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16));
+      uint32_t h0, h1, l0, l1;
+      const bool ok = m < a.B;
+      split_pair(ok ? dv[0][m] : 0.f, ok ? dv[1][m] : 0.f, h0, l0);
+      split_pair(ok ? dv[2][m] : 0.f, ok ? dv[3][m] : 0.f, h1, l1);
+      dop_s[tl][16 * q + m] = make_uint2(h0, h1);
+      dop_s[tl][16 * q + 8 + m] = make_uint2(l0, l1);
     }
   }
   __syncthreads();
@@ -320,6 +353,7 @@ __global__ __launch_bounds__(256) void k_tgemv_sum(const float *part, int nsplit
   const int e = blockIdx.x * 256 + threadIdx.x;
   if (e >= B * K) return;
   float s = 0.f;
+#pragma unroll 8
   for (int i = 0; i < nsplit; ++i) s += part[(size_t)i * B * K + e];
   if (!SWIGLU) {
     out[e] = s;
@@ -336,38 +370,37 @@ __global__ __launch_bounds__(256) void k_tgemv_sum(const float *part, int nsplit
 
 // ------------------------------------------------------------------------------- attention
 
-// The verify token's own key, per (candidate, kv-head j): for the g heads h of j,
-// Dh = do_h . o_h, p = exp(q_h . k_self / sqrt(d) - lse_h), ds = p (do_h . v_self - Dh);
-// dk_self = sum_h ds q_h / sqrt(d), dv_self = sum_h p do_h, dq_h = ds k_self / sqrt(d).
-// One thread per dimension.
-template <int D>
-__global__ __launch_bounds__(D) void k_attn_bwd_self(const float *q, const float *ks,
-                                                     const float *vs, const float *o,
-                                                     const float *lse, const float *dout, int nq,
-                                                     int nkv, float *Dh, float *dq_self,
-                                                     float *dk_self, float *dv_self) {
-  __shared__ float red[D / 64];
-  const int b = blockIdx.x, j = blockIdx.y, m = threadIdx.x;
-  const int g = nq / nkv;
-  const float sc = 1.0f / sqrtf((float)D);
-  const float kv = ks[((size_t)b * nkv + j) * D + m], vv = vs[((size_t)b * nkv + j) * D + m];
-  float dk = 0.f, dv = 0.f;
-  for (int hh = 0; hh < g; ++hh) {
-    const int h = j * g + hh;
-    const size_t r = ((size_t)b * nq + h) * D + m;
-    const float qv = q[r], dov = dout[r];
-    const float Dv = block_sum<D>(dov * o[r], red);
-    const float s = block_sum<D>(qv * kv, red) * sc;
-    const float dp = block_sum<D>(dov * vv, red);
-    const float p = expf(s - lse[(size_t)b * nq + h]);
-    const float ds = p * (dp - Dv);
-    dk += ds * qv * sc;
-    dv += p * dov;
-    dq_self[r] = ds * kv * sc;
-    if (m == 0) Dh[(size_t)b * nq + h] = Dv;
+// The verify token's own key of kv-head j of candidate b, for its q-heads [h0, h1) (at most 16):
+// Dh = do_h . o_h, p = exp(q_h . k_self / sqrt(d) - lse_h), ds = p (do_h . v_self - Dh) into
+// p_s[h - h0], ds_s[h - h0], one wave per head. Ends with a barrier; every thread calls it.
+template <int D, int NTHR>
+__device__ __forceinline__ void own_key(const float *q, const float *ks, const float *vs,
+                                        const float *o, const float *lse, const float *dout, int b,
+                                        int j, int h0, int h1, int nq, int nkv, float *p_s,
+                                        float *ds_s) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const float *kr = ks + ((size_t)b * nkv + j) * D, *vr = vs + ((size_t)b * nkv + j) * D;
+  for (int h = h0 + wave; h < h1; h += NTHR / 64) {
+    const size_t r = ((size_t)b * nq + h) * D;
+    float Dv = 0.f, s = 0.f, dp = 0.f;
+#pragma unroll
+    for (int u = 0; u < D / 64; ++u) {
+      const int m = lane + 64 * u;
+      const float dov = dout[r + m];
+      Dv += dov * o[r + m];
+      s += q[r + m] * kr[m];
+      dp += dov * vr[m];
+    }
+    Dv = wave_sum(Dv);
+    s = wave_sum(s);
+    dp = wave_sum(dp);
+    if (lane == 0) {
+      const float p = expf(s * (1.0f / sqrtf((float)D)) - lse[(size_t)b * nq + h]);
+      p_s[h - h0] = p;
+      ds_s[h - h0] = p * (dp - Dv);
+    }
   }
-  dk_self[((size_t)b * nkv + j) * D + m] = dk;
-  dv_self[((size_t)b * nkv + j) * D + m] = dv;
+  __syncthreads();
 }
 
 struct AttnBwdArgs {
@@ -378,7 +411,7 @@ struct AttnBwdArgs {
   int max_pages;
   const int32_t *lengths;
   int nkv, nq, CP, nch;        // chunk length in pages, chunk slots per (candidate, head)
-  const float *q, *dout, *lse, *Dh;  // [B][nq][D], [B][nq][D], [B][nq], [B][nq]
+  const float *q, *o, *dout, *lse;  // [B][nq][D] (o, dout: attention output, its gradient), [B][nq]
   float *dq_part;              // [B][nq][nch][D]
 };
 
@@ -410,6 +443,7 @@ __global__ __launch_bounds__(64 * W) void k_attn_bwd_mx(AttnBwdArgs a) {
   __shared__ uint4 kt_s[W][TL * 64];         // the page's K tile as stored
   __shared__ uint4 vt_s[W][TL * 64];         // the page's V tile as stored
   __shared__ uint16_t ds_s[W][2][16 * DST];  // dS^T hi, lo: [head][token]
+  __shared__ float Dh_s[16];
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int n = lane & 15, c = lane >> 4;
   const int b = blockIdx.y, j = blockIdx.z;
@@ -419,62 +453,77 @@ __global__ __launch_bounds__(64 * W) void k_attn_bwd_mx(AttnBwdArgs a) {
   if ((int)blockIdx.x * W * a.CP >= npages) return;  // the whole block
   const float sc = 1.0f / sqrtf((float)D);
   const size_t hb = (size_t)b * nq + (size_t)j * g;  // row of the first q-head of kv-head j
+  // (absent heads read head 0's rows and are zeroed after the load: no load is conditional)
   for (int e = threadIdx.x; e < NDB * 64; e += 64 * W) {
     const int nb = e >> 6, ln = e & 63;
     const int m = 16 * nb + (ln & 15), c4 = 4 * (ln >> 4);
-    uint32_t qh[4], ql[4], oh[4], ol[4];
+    float qv[4], ov[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const bool hv = c4 + i < g;
       const size_t r = (hb + (hv ? c4 + i : 0)) * D + m;
-      split_bf16(hv ? a.q[r] * sc : 0.f, qh[i], ql[i]);
-      split_bf16(hv ? a.dout[r] : 0.f, oh[i], ol[i]);
+      const float x = a.q[r], y = a.dout[r];
+      qv[i] = hv ? x * sc : 0.f;
+      ov[i] = hv ? y : 0.f;
     }
-    qT_s[nb][ln] = make_uint4(qh[0] | qh[1] << 16, qh[2] | qh[3] << 16, ql[0] | ql[1] << 16,
-                              ql[2] | ql[3] << 16);
-    dO_s[nb][ln] = make_uint4(oh[0] | oh[1] << 16, oh[2] | oh[3] << 16, ol[0] | ol[1] << 16,
-                              ol[2] | ol[3] << 16);
+    uint4 w;
+    split_pair(qv[0], qv[1], w.x, w.z);
+    split_pair(qv[2], qv[3], w.y, w.w);
+    qT_s[nb][ln] = w;
+    split_pair(ov[0], ov[1], w.x, w.z);
+    split_pair(ov[2], ov[3], w.y, w.w);
+    dO_s[nb][ln] = w;
   }
   // q (three terms) and dO (two) with the dims as reduction index, lane = head n
   for (int e = threadIdx.x; e < NKB * 64; e += 64 * W) {
     const int kk = e >> 6, ln = e & 63, hn = ln & 15, c8 = 8 * (ln >> 4);
     const bool hv = hn < g;
-    const float *qr = a.q + (hb + (hv ? hn : 0)) * D + 32 * kk + c8;
-    const float *orow = a.dout + (hb + (hv ? hn : 0)) * D + 32 * kk + c8;
-    uint32_t h[8], md[8], lo[8], oh[8], ol[8];
+    const size_t r = (hb + (hv ? hn : 0)) * D + 32 * kk + c8;
+    float qv[8], ov[8];
+    *(float4 *)&qv[0] = *(const float4 *)(a.q + r);
+    *(float4 *)&qv[4] = *(const float4 *)(a.q + r + 4);
+    *(float4 *)&ov[0] = *(const float4 *)(a.dout + r);
+    *(float4 *)&ov[4] = *(const float4 *)(a.dout + r + 4);
+    uint32_t h[4], md[4], lo[4], oh[4], ol[4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float qv = hv ? qr[i] : 0.f;
+    for (int i = 0; i < 4; ++i) {
+      const float x0 = hv ? qv[2 * i] : 0.f, x1 = hv ? qv[2 * i + 1] : 0.f;
       uint32_t rest;
-      split_bf16(qv, h[i], rest);
-      split_bf16(qv - bf(h[i]), md[i], lo[i]);
-      split_bf16(hv ? orow[i] : 0.f, oh[i], ol[i]);
+      split_pair(x0, x1, h[i], rest);
+      split_pair(x0 - bf(h[i] & 0xFFFFu), x1 - __uint_as_float(h[i] & 0xFFFF0000u), md[i], lo[i]);
+      split_pair(hv ? ov[2 * i] : 0.f, hv ? ov[2 * i + 1] : 0.f, oh[i], ol[i]);
     }
-    qa_s[0][kk][ln] = make_uint4(h[0] | h[1] << 16, h[2] | h[3] << 16, h[4] | h[5] << 16, h[6] | h[7] << 16);
-    qa_s[1][kk][ln] = make_uint4(md[0] | md[1] << 16, md[2] | md[3] << 16, md[4] | md[5] << 16,
-                                 md[6] | md[7] << 16);
-    qa_s[2][kk][ln] = make_uint4(lo[0] | lo[1] << 16, lo[2] | lo[3] << 16, lo[4] | lo[5] << 16,
-                                 lo[6] | lo[7] << 16);
-    oa_s[0][kk][ln] = make_uint4(oh[0] | oh[1] << 16, oh[2] | oh[3] << 16, oh[4] | oh[5] << 16,
-                                 oh[6] | oh[7] << 16);
-    oa_s[1][kk][ln] = make_uint4(ol[0] | ol[1] << 16, ol[2] | ol[3] << 16, ol[4] | ol[5] << 16,
-                                 ol[6] | ol[7] << 16);
+    qa_s[0][kk][ln] = make_uint4(h[0], h[1], h[2], h[3]);
+    qa_s[1][kk][ln] = make_uint4(md[0], md[1], md[2], md[3]);
+    qa_s[2][kk][ln] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+    oa_s[0][kk][ln] = make_uint4(oh[0], oh[1], oh[2], oh[3]);
+    oa_s[1][kk][ln] = make_uint4(ol[0], ol[1], ol[2], ol[3]);
+  }
+  // D_h = do_h . o_h, 32 lanes per head
+  for (int e = threadIdx.x; e < 16 * 32; e += 64 * W) {
+    const int hn = e >> 5, l = e & 31;
+    float v = 0.f;
+    if (hn < g) {
+      const size_t r = (hb + hn) * D;
+#pragma unroll
+      for (int u = 0; u < D / 32; ++u) v += a.dout[r + l + 32 * u] * a.o[r + l + 32 * u];
+    }
+    v = sum_lanes<32>(v);
+    if (l == 0) Dh_s[hn] = v;
   }
   float lse2[4], Dh4[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int h = 4 * c + i;
-    lse2[i] = h < g ? a.lse[hb + h] * kLog2e : 0.f;
-    Dh4[i] = h < g ? a.Dh[hb + h] : 0.f;
-  }
+  for (int i = 0; i < 4; ++i) lse2[i] = 4 * c + i < g ? a.lse[hb + 4 * c + i] * kLog2e : 0.f;
   floatx4 dq[NDB];
 #pragma unroll
   for (int nb = 0; nb < NDB; ++nb) dq[nb] = floatx4{0.f, 0.f, 0.f, 0.f};
   __syncthreads();  // block operands ready; no other barrier below (every LDS region after this
                     // is private to one wave, whose LDS accesses execute in program order)
+#pragma unroll
+  for (int i = 0; i < 4; ++i) Dh4[i] = Dh_s[4 * c + i];
   const int chunk = blockIdx.x * W + wv;
   const int pw0 = chunk * a.CP, pw1 = min(npages, pw0 + a.CP);
-  if (pw0 >= pw1) return;
+  if (pw0 >= pw1 || chunk >= a.nch) return;
   uint4 *ks = kt_s[wv], *vs = vt_s[wv];
   const uint16_t *ks16 = (const uint16_t *)ks, *vs16 = (const uint16_t *)vs;
   uint16_t *dsh = ds_s[wv][0], *dsl = ds_s[wv][1];
@@ -533,21 +582,24 @@ __global__ __launch_bounds__(64 * W) void k_attn_bwd_mx(AttnBwdArgs a) {
     }
     const int t0 = pi * kPage;
     const bool tv = t0 + n < L;
-    uint32_t ph[4], pl[4], sh[4], sl[4];
+    float pv[4], dsv[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const bool ok = tv && 4 * c + i < g;
       const float p = ok ? __builtin_amdgcn_exp2f(st[i] * rs2 - lse2[i]) : 0.f;
-      const float ds = ok ? p * (dpt[i] - Dh4[i]) : 0.f;
-      split_bf16(p, ph[i], pl[i]);
-      split_bf16(ds, sh[i], sl[i]);
-      dsh[(4 * c + i) * DST + n] = (uint16_t)sh[i];
-      dsl[(4 * c + i) * DST + n] = (uint16_t)sl[i];
+      pv[i] = p;
+      dsv[i] = ok ? p * (dpt[i] - Dh4[i]) : 0.f;
     }
-    const uint2 Ph = make_uint2(ph[0] | ph[1] << 16, ph[2] | ph[3] << 16);
-    const uint2 Pl = make_uint2(pl[0] | pl[1] << 16, pl[2] | pl[3] << 16);
-    const uint2 Sh = make_uint2(sh[0] | sh[1] << 16, sh[2] | sh[3] << 16);
-    const uint2 Sl = make_uint2(sl[0] | sl[1] << 16, sl[2] | sl[3] << 16);
+    uint2 Ph, Pl, Sh, Sl;
+    split_pair(pv[0], pv[1], Ph.x, Pl.x);
+    split_pair(pv[2], pv[3], Ph.y, Pl.y);
+    split_pair(dsv[0], dsv[1], Sh.x, Sl.x);
+    split_pair(dsv[2], dsv[3], Sh.y, Sl.y);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      dsh[(4 * c + i) * DST + n] = (uint16_t)((i < 2 ? Sh.x : Sh.y) >> (16 * (i & 1)));
+      dsl[(4 * c + i) * DST + n] = (uint16_t)((i < 2 ? Sl.x : Sl.y) >> (16 * (i & 1)));
+    }
     // dV, two 16-dim blocks at a time: lane = dim 16 nb + n, rows = slots 4c .. 4c+3, which is
     // the lane's own 16-byte piece t of the V tile
 #pragma unroll
@@ -637,21 +689,22 @@ __global__ __launch_bounds__(64 * W) void k_attn_bwd_mx(AttnBwdArgs a) {
 }
 
 // dq of every head (the own-key term, then the chunk partials: four groups of consecutive
-// chunks, each added in order by its own threads, the groups in order), the rotary backward of
-// dq and dk_self (the transposed rotation by the same angles), and the stacked d vector of the
-// q/k/v products: rows [0, nq d) dq, then n_kv d of dk, then n_kv d of dv; layout
+// chunks, each added in order by its own threads, the groups in order), dk and dv of the verify
+// token's own key, the rotary backward of dq and dk (the transposed rotation by the same angles),
+// and the stacked d vector of the q/k/v products: rows [0, nq d) dq, then n_kv d of dk, then n_kv d of dv; layout
 // [row][kDPad].
 template <int D>
-__global__ __launch_bounds__(2 * D) void k_attn_bwd_merge(const float *dq_part, int nch,
-                                                          const int32_t *lengths, int CP,
-                                                          const float *dq_self,
-                                                          const float *dk_self,
-                                                          const float *dv_self, const float *rope,
-                                                          int nq, int nkv, int B, float *dqkv) {
+__global__ __launch_bounds__(2 * D) void k_attn_bwd_merge(
+    const float *dq_part, int nch, const int32_t *lengths, int CP, const float *q, const float *ks,
+    const float *vs, const float *o, const float *lse, const float *dout, const float *rope, int nq,
+    int nkv, int B, float *dqkv) {
   constexpr int HD = D / 2, NGRP = 4;  // threads: NGRP groups of HD (dims i and i + HD)
   __shared__ float red_s[NGRP][2][HD];
+  __shared__ float p_s[16], ds_s[16];
   const int b = blockIdx.x, h = blockIdx.y;  // h < nq: q-head; else kv-head (block-uniform)
   const int i = threadIdx.x % HD, grp = threadIdx.x / HD;
+  const int g = nq / nkv;
+  const float sc = 1.0f / sqrtf((float)D);
   const float cs = rope[((size_t)b * HD + i) * 2], sn = rope[((size_t)b * HD + i) * 2 + 1];
   float y1, y2;
   size_t row;
@@ -659,7 +712,7 @@ __global__ __launch_bounds__(2 * D) void k_attn_bwd_merge(const float *dq_part, 
     // chunk partials: group grp adds its quarter of the chunks in order, eight loads in flight;
     // then the quarters are added in group order
     const int L = lengths[b];
-    const int nc = ((L + kPage - 1) / kPage + CP - 1) / CP;
+    const int nc = min(nch, ((L + kPage - 1) / kPage + CP - 1) / CP);
     const int per = (nc + NGRP - 1) / NGRP;
     const int c0 = min(nc, grp * per), c1 = min(nc, c0 + per);
     const float *pp = dq_part + ((size_t)b * nq + h) * nch * D;
@@ -684,30 +737,37 @@ __global__ __launch_bounds__(2 * D) void k_attn_bwd_merge(const float *dq_part, 
     }
     red_s[grp][0][i] = a1;
     red_s[grp][1][i] = a2;
-    __syncthreads();
+    own_key<D, 2 * D>(q, ks, vs, o, lse, dout, b, h / g, h, h + 1, nq, nkv, p_s, ds_s);
     if (grp != 0) return;
-    y1 = dq_self[((size_t)b * nq + h) * D + i];
-    y2 = dq_self[((size_t)b * nq + h) * D + i + HD];
+    const float *kr = ks + ((size_t)b * nkv + h / g) * D;
+    y1 = ds_s[0] * kr[i] * sc;
+    y2 = ds_s[0] * kr[i + HD] * sc;
 #pragma unroll
     for (int k = 0; k < NGRP; ++k) {
       y1 += red_s[k][0][i];
       y2 += red_s[k][1][i];
     }
     row = (size_t)h * D;
-  } else if (grp != 0) {
-    return;
-  } else if (h < nq + nkv) {
-    const int j = h - nq;
-    y1 = dk_self[((size_t)b * nkv + j) * D + i];
-    y2 = dk_self[((size_t)b * nkv + j) * D + i + HD];
-    row = (size_t)nq * D + (size_t)j * D;
   } else {
-    const int j = h - nq - nkv;
-    dqkv[((size_t)(nq + nkv) * D + (size_t)j * D + i) * kDPad + b] =
-        dv_self[((size_t)b * nkv + j) * D + i];
-    dqkv[((size_t)(nq + nkv) * D + (size_t)j * D + i + HD) * kDPad + b] =
-        dv_self[((size_t)b * nkv + j) * D + i + HD];
-    return;
+    // dk_self = sum_h ds q_h / sqrt(d) (then rotated back), dv_self = sum_h p do_h
+    const bool key = h < nq + nkv;
+    const int j = key ? h - nq : h - nq - nkv;
+    own_key<D, 2 * D>(q, ks, vs, o, lse, dout, b, j, j * g, j * g + g, nq, nkv, p_s, ds_s);
+    if (grp != 0) return;
+    y1 = y2 = 0.f;
+    const float *src = key ? q : dout;
+    for (int hh = 0; hh < g; ++hh) {
+      const size_t r = ((size_t)b * nq + (size_t)j * g + hh) * D + i;
+      const float f = key ? ds_s[hh] * sc : p_s[hh];
+      y1 += f * src[r];
+      y2 += f * src[r + HD];
+    }
+    row = (size_t)(key ? nq : nq + nkv) * D + (size_t)j * D;
+    if (!key) {
+      dqkv[(row + i) * kDPad + b] = y1;
+      dqkv[(row + i + HD) * kDPad + b] = y2;
+      return;
+    }
   }
   // forward: (a, c) -> (a cos - c sin, c cos + a sin); backward is the transpose
   dqkv[(row + i) * kDPad + b] = y1 * cs + y2 * sn;
@@ -778,7 +838,7 @@ hipError_t launch_backward(const Dims &dm, const Plan &p, const Workspace &w, co
   do {                                      \
     if ((e = hipGetLastError()) != hipSuccess) return e; \
   } while (0)
-  hipLaunchKernelGGL(k_head_bwd, dim3(B), dim3(256), 0, s, w.x, final_norm, reward_w, reward_b, H,
+  hipLaunchKernelGGL(k_head_bwd, dim3(B), dim3(1024), 0, s, w.x, final_norm, reward_w, reward_b, H,
                      dm.eps, sv.dx, sv.dxT, B);
   KVPRM_CHECK();
   const size_t qd = (size_t)B * nq * D, kd = (size_t)B * nkv * D;
@@ -798,24 +858,17 @@ hipError_t launch_backward(const Dims &dm, const Plan &p, const Workspace &w, co
       const int rgu[3] = {F, F, 0};
       if ((e = tgemv(p, wgu, rgu, 2, H, sv.dgu, sv.part, sv.du, nullptr, false, s)) != hipSuccess)
         return e;
-      hipLaunchKernelGGL(k_rms_bwd, dim3(B), dim3(1024), 0, s, x_mid, W.ffn_norm, sv.du, sv.dx,
-                         sv.dxm, sv.dxmT, B, H, dm.eps);
-      KVPRM_CHECK();
+      if ((e = rms_bwd(x_mid, W.ffn_norm, sv.du, sv.dx, sv.dxm, sv.dxmT, B, H, dm.eps, s)) !=
+          hipSuccess)
+        return e;
     }
-    // attention: do = W_o^T dx_mid; the own key; the cached keys and values; dq -> du1 -> dx
+    // attention: do = W_o^T dx_mid; the cached keys and values; the own key, dq -> du1 -> dx
     {
       const void *wo[3] = {W.wo, nullptr, nullptr};
       const int ro[3] = {H, 0, 0};
       if ((e = tgemv(p, wo, ro, 1, nq * D, sv.dxmT, sv.part, sv.dout, nullptr, false, s)) !=
           hipSuccess)
         return e;
-      if (D == 64)
-        hipLaunchKernelGGL(k_attn_bwd_self<64>, dim3(B, nkv), dim3(64), 0, s, q, ks, vs, o, lse,
-                           sv.dout, nq, nkv, sv.Dh, sv.dq_self, sv.dk_self, sv.dv_self);
-      else
-        hipLaunchKernelGGL(k_attn_bwd_self<128>, dim3(B, nkv), dim3(128), 0, s, q, ks, vs, o, lse,
-                           sv.dout, nq, nkv, sv.Dh, sv.dq_self, sv.dk_self, sv.dv_self);
-      KVPRM_CHECK();
       AttnBwdArgs a;
       memset(&a, 0, sizeof a);
       a.kp = kpool + layer_bytes * l;
@@ -829,11 +882,11 @@ hipError_t launch_backward(const Dims &dm, const Plan &p, const Workspace &w, co
       a.nkv = nkv;
       a.nq = nq;
       a.CP = CP;
-      a.nch = p.nch;
+      a.nch = p.nch_bwd;
       a.q = q;
+      a.o = o;
       a.dout = sv.dout;
       a.lse = lse;
-      a.Dh = sv.Dh;
       a.dq_part = sv.dq_part;
       constexpr int WB = 8;  // waves (chunks) per block of the matrix-core backward
       const dim3 grid((chunks + WB - 1) / WB, B, nkv);
@@ -844,20 +897,20 @@ hipError_t launch_backward(const Dims &dm, const Plan &p, const Workspace &w, co
       KVPRM_CHECK();
       if (D == 64)
         hipLaunchKernelGGL(k_attn_bwd_merge<64>, dim3(B, nq + 2 * nkv), dim3(128), 0, s,
-                           sv.dq_part, p.nch, lengths, CP, sv.dq_self, sv.dk_self, sv.dv_self,
-                           w.rope, nq, nkv, B, sv.dqkv);
+                           sv.dq_part, p.nch_bwd, lengths, CP, q, ks, vs, o, lse, sv.dout, w.rope,
+                           nq, nkv, B, sv.dqkv);
       else
         hipLaunchKernelGGL(k_attn_bwd_merge<128>, dim3(B, nq + 2 * nkv), dim3(256), 0, s,
-                           sv.dq_part, p.nch, lengths, CP, sv.dq_self, sv.dk_self, sv.dv_self,
-                           w.rope, nq, nkv, B, sv.dqkv);
+                           sv.dq_part, p.nch_bwd, lengths, CP, q, ks, vs, o, lse, sv.dout, w.rope,
+                           nq, nkv, B, sv.dqkv);
       KVPRM_CHECK();
       const void *wqkv[3] = {W.wq, W.wk, W.wv};
       const int rqkv[3] = {nq * D, nkv * D, nkv * D};
       if ((e = tgemv(p, wqkv, rqkv, 3, H, sv.dqkv, sv.part, sv.du, nullptr, false, s)) != hipSuccess)
         return e;
-      hipLaunchKernelGGL(k_rms_bwd, dim3(B), dim3(1024), 0, s, x_in, W.attn_norm, sv.du, sv.dxm,
-                         sv.dx, sv.dxT, B, H, dm.eps);
-      KVPRM_CHECK();
+      if ((e = rms_bwd(x_in, W.attn_norm, sv.du, sv.dxm, sv.dx, sv.dxT, B, H, dm.eps, s)) !=
+          hipSuccess)
+        return e;
     }
   }
 #undef KVPRM_CHECK

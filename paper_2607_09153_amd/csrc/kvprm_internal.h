@@ -79,6 +79,8 @@ struct Plan {
   // B = rows of the pass: candidates x verify tokens per candidate (kq, the depth-k readout);
   // row v is verify token v % kq of candidate v / kq. Breal = candidates.
   int B, max_pages, nch;      // nch = chunk slots per (row, q-head), see make_plan
+  int nch_bwd;                // chunk slots of the backward attention per (row, q-head)
+  size_t slots, slots_bwd;    // room for slots over all candidates (at least Breal nch, nch_bwd)
   int kq, Breal;
   int nss;                    // 16-row tiles of H: partial sums of squares
   // bf16 pipeline
@@ -122,11 +124,9 @@ struct GradSave {
   float *du;                     // [B][H]
   float *dgu;                    // [2F][kDPad]
   float *dout;                   // [B][n_q d]
-  float *Dh;                     // [B][n_q]
-  float *dq_self;                // [B][n_q][d]
-  float *dk_self, *dv_self;      // [B][n_kv][d]
+  float *scores;                 // [B] P(+) of the steps whose scores the caller does not get
   float *dqkv;                   // [(n_q + 2 n_kv) d][kDPad]
-  float *dq_part;                // [B][n_q][nch][d]
+  float *dq_part;                // [B][n_q][nch_bwd][d]
   float *part;                   // transposed-product split partials
   size_t bytes;
 };
@@ -158,6 +158,8 @@ struct PrivateChunks {
   int shift, heads_per_block;
 };
 PrivateChunks private_chunk_rule(const Dims &dm, int n, const int *pages, const int *slots);
+// Chunk length of the backward attention, in pages.
+int backward_chunk_pages(const Dims &dm, int n, const int *pages, int slots);
 Workspace carve(const Dims &dm, const Plan &p, void *base);
 
 // Kernel launchers (return hipGetLastError()).

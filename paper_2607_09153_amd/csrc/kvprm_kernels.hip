@@ -3,6 +3,8 @@
 // attention live in kvprm_mfma.hip and kvprm_attn.hip (bf16 weights) and kvprm_f32.hip (fp32).
 #include <math.h>
 
+#include <algorithm>
+
 #include "kvprm_internal.h"
 
 namespace kvprm {
@@ -114,6 +116,26 @@ PrivateChunks private_chunk_rule(const Dims &dm, int n, const int *pages, const 
   return r;
 }
 
+// The backward attention runs eight waves (chunks) to a block and one block per compute unit
+// (LDS), so that up to 2048 waves run at once; the chunk is the shortest of 2, 4, 8, 16 pages that
+// keeps to that (a page takes a wave 4-5 us). Per layer, 7B shape: one candidate of 6000 tokens
+// 74.9 us in 16-page chunks, 19.2 in 2; four of 4k-8k 82.3 -> 36.6 in 4; eight of 4k-8k
+// 98.5 -> 65.2 in 8; eight of 16k-32k 275.6 in 16 (280.7 in 4).
+constexpr long long kBackwardWaves = 2048;
+int backward_chunk_pages(const Dims &dm, int n, const int *pages, int slots) {
+  for (int CP = 2; CP < 16; CP *= 2) {
+    long long items = 0;
+    bool fits = true;
+    for (int i = 0; i < n; ++i) {
+      const int ch = (pages[i] + CP - 1) / CP;
+      items += ch;
+      if (ch > slots) fits = false;
+    }
+    if (fits && items * dm.nkv <= kBackwardWaves) return CP;
+  }
+  return 16;
+}
+
 Plan make_plan(const Dims &dm, int Breal, int max_pages, int lora_rank, int depth, bool lean) {
   Plan p{};
   const int B = Breal * depth;  // rows of the pass (verify tokens of all candidates)
@@ -125,17 +147,24 @@ Plan make_plan(const Dims &dm, int Breal, int max_pages, int lora_rank, int dept
   // chunk slots: chunks of max_pages at 16 pages (a long batch's chunks are no shorter) plus one
   // (a shared prefix that ends inside a chunk adds one), for whichever attention path runs; more
   // where the batch is small enough for shorter chunks (private_chunk_rule).
-  // (fp32: 32-page chunks and shorter)
+  // (fp32: 32-page chunks and shorter.) The room for all candidates' slots is a bound that never
+  // falls with the batch or max_pages, so that a workspace serves every smaller batch too.
   const int longest = dm.kvdt == 0 ? kChunkPagesF32 : 16, shortest = dm.kvdt == 0 ? 2 : 4;
-  int n = (max_pages + longest - 1) / longest + 1;
+  p.nch = (max_pages + longest - 1) / longest + 1;
+  p.slots = (size_t)Breal * p.nch;
+  // the backward attention's: 16-page chunks, shorter for a small batch (backward_chunk_pages)
+  p.nch_bwd = (max_pages + 15) / 16;
+  p.slots_bwd = (size_t)Breal * p.nch_bwd;
   if (!lean) {
-    long long fine = chunk_wave_limit(dm) / ((long long)Breal * dm.nkv);
-    const long long all = (max_pages + shortest - 1) / shortest;
-    fine = fine < all ? fine : all;
-    fine = (fine < kFineChunks ? fine : kFineChunks) + 1;
-    if (n < fine) n = (int)fine;
+    auto fine = [&](long long waves, long long most, int *n, size_t *slots, int more) {
+      const long long total = waves / dm.nkv, each = std::min(most, total / Breal) + more;
+      if (*n < each) *n = (int)each;
+      *slots = std::max(*slots, (size_t)(std::min(total, Breal * most) + (long long)Breal * more));
+    };
+    fine(chunk_wave_limit(dm), std::min(kFineChunks, (max_pages + shortest - 1) / shortest), &p.nch,
+         &p.slots, 1);
+    fine(kBackwardWaves, (max_pages + 1) / 2, &p.nch_bwd, &p.slots_bwd, 0);
   }
-  p.nch = n;
   size_t m = 0;
   if (dm.wdt == 1) {
     // split-K partials: the adapter's A-factor products and the split projections
@@ -224,7 +253,7 @@ Workspace carve(const Dims &dm, const Plan &p, void *base) {
   w.q = take(B * dm.nq * dm.d);
   w.kself = take(B * dm.nkv * dm.d);
   w.vself = take(B * dm.nkv * dm.d);
-  w.apart = take(B * dm.nq * (size_t)p.nch * (dm.d + 2));
+  w.apart = take(p.slots * p.kq * dm.nq * (dm.d + 2));
   w.o = take(B * dm.nq * dm.d);
   w.hffn = take(B * dm.F);
   if (dm.wdt == 1) {
@@ -270,12 +299,9 @@ GradSave carve_grad(const Dims &dm, const Plan &p, void *base) {
   g.du = take(B * H);
   g.dgu = take(2 * F * kDPad);
   g.dout = take(B * nq * d);
-  g.Dh = take(B * nq);
-  g.dq_self = take(B * nq * d);
-  g.dk_self = take(B * nkv * d);
-  g.dv_self = take(B * nkv * d);
+  g.scores = take(B);
   g.dqkv = take((nq + 2 * nkv) * d * kDPad);
-  g.dq_part = take(B * nq * (size_t)p.nch * d);
+  g.dq_part = take(p.slots_bwd * nq * d);
   // split partials of the four transposed products
   size_t part = 0;
   const size_t cand[4][2] = {{F, H / 16}, {H, 2 * F / 16}, {nq * d, H / 16},

@@ -1,11 +1,8 @@
 """The attention step at every chunk length its rule can pick (4 to 64 pages, one, four or all
 kv-heads to a block): lengths on both sides of a chunk's edges, alone and ragged, with and without
-lengths on the host, and in the smallest workspace the call accepts, against the fp64 oracle.
+lengths on the host, against the fp64 oracle, in exactly the workspace the call asks for.
 Bar as in the attention parity tests: 2e-5 of the largest output (fp32 sums, probabilities and
 queries in two and three bf16 terms)."""
-import re
-import sys
-
 import numpy as np
 import pytest
 import torch
@@ -52,29 +49,24 @@ def test_attention_at_every_chunk_length(nq, nkv, d, dtype, lengths):
     try:
         for host in (True, False):
             batch = dw.batch(m, lengths_host=host)
-            full = m.kvprm_workspace_size(h, batch)
-            ws = torch.empty(full, dtype=torch.uint8, device="cuda")
+            n = m.kvprm_workspace_size(h, batch)
+            guard = 4096
+            ws = torch.full((n + guard,), 0x5A, dtype=torch.uint8, device="cuda")
             o = torch.full(q.shape, float("nan"), device="cuda")
 
-            def call(n):
+            def call(nbytes):
                 m.kvprm_attention(h, dw.cache(m), batch, 0, qd.data_ptr(), kd.data_ptr(),
-                                  vd.data_ptr(), ws.data_ptr(), n, o.data_ptr(), st)
+                                  vd.data_ptr(), ws.data_ptr(), nbytes, o.data_ptr(), st)
 
             with pytest.raises(m.KvprmError) as e:
-                call(0)
+                call(n - 1)
             assert e.value.status == m.KVPRM_E_WORKSPACE
-            least = int(re.search(r"workspace of (\d+) bytes needed", m.kvprm_last_error()).group(1))
-            assert least <= full
-            with pytest.raises(m.KvprmError):
-                call(least - 1)
-            for n in (full, least):
-                o.fill_(float("nan"))
-                call(n)
-                torch.cuda.synchronize()
-                got = o.cpu().numpy().astype(np.float64)
-                assert np.all(np.isfinite(got))
-                err = np.max(np.abs(got - ref))
-                print(f"  host lengths {host}, workspace {n}: max|do| = {err:.2e}", flush=True)
-                assert err <= bar
+            call(n)
+            torch.cuda.synchronize()
+            got = o.cpu().numpy().astype(np.float64)
+            assert np.all(np.isfinite(got)) and torch.all(ws[n:] == 0x5A)
+            err = np.max(np.abs(got - ref))
+            print(f"  host lengths {host}: max|do| = {err:.2e}", flush=True)
+            assert err <= bar
     finally:
         m.kvprm_destroy(h)
