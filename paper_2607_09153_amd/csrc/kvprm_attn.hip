@@ -558,6 +558,8 @@ __global__ __launch_bounds__(NTHR) void k_merge_mx(AttnArgs a) {
   const int clast = max(nc, 1) - 1;
 #pragma unroll
   for (int i = 0; i < R; ++i) rv[i] = base[min(sub + S * i, clast) * (D + 2) + dd];
+  // (the first own value, used at the end: its load belongs to the first round trip)
+  const float v0 = a.vself[((size_t)cand * kq * a.nkv + j) * D + dd];
   float mx = -INFINITY;
   for (int c = t; c < nc; c += NTHR) {
     const float m = base[(size_t)c * (D + 2) + D];
@@ -624,7 +626,7 @@ __global__ __launch_bounds__(NTHR) void k_merge_mx(AttnArgs a) {
   for (int i = 0; i <= tok; ++i) {
     const float es = expf(sself_s[i] - M);
     es_sum += es;
-    tot += es * a.vself[((row0 + i) * a.nkv + j) * D + dd];
+    tot += es * (i == 0 ? v0 : a.vself[((row0 + i) * a.nkv + j) * D + dd]);
   }
   const float ov = tot / (lsum + es_sum);
   if (a.lse && dd == 0) a.lse[(size_t)b * a.nq + h] = M + logf(lsum + es_sum);

@@ -128,6 +128,26 @@ __global__ __launch_bounds__(64 * WPB) void k_gemv32(F32Args a) {
     const int b = min(b0 + (int)threadIdx.x % NC, B - 1);
     for (int i = threadIdx.x / NC; i < a.H / 16; i += P) sq += a.ss[(size_t)i * B + b];
   }
+  // what the epilogue reads besides (wave g: rows 4c .. 4c+3 of candidate n of group g), loaded now
+  // so that no memory round trip is left for the end
+  const int b = b0 + 16 * wave + n;
+  const bool ok = wave < NG && b < B;
+  const int bc = ok ? b : B - 1;
+  const int r0 = tile[0] * 16 + 4 * c;
+  floatx4 xv = {0.f, 0.f, 0.f, 0.f}, gm = xv;
+  double rope[4][2];
+  if (wave < NG && EPI == F32_RESID) {
+    xv = *(const floatx4 *)(a.x + (size_t)bc * a.H + r0);
+    if (a.gamma) gm = *(const f32x4u *)(a.gamma + r0);
+  }
+  if (wave < NG && EPI == F32_ROPE) {
+    const double *rp = a.rope + ((size_t)bc * (a.d / 2) + r0 % a.d) * 2;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      rope[i][0] = rp[2 * i];
+      rope[i][1] = rp[2 * i + 1];
+    }
+  }
   floatx4 acc[MT][NG];
 #pragma unroll
   for (int m = 0; m < MT; ++m)
@@ -197,12 +217,7 @@ __global__ __launch_bounds__(64 * WPB) void k_gemv32(F32Args a) {
       for (int i = 0; i < 4; ++i) y[m][i] += v[i];
     }
   }
-  const int b = b0 + 16 * wave + n;
-  const bool ok = b < B;
-  const int bc = ok ? b : B - 1;
   if (EPI == F32_RESID) {
-    const int r = tile[0] * 16 + 4 * c;
-    floatx4 xv = *(const floatx4 *)(a.x + (size_t)bc * a.H + r);
     float s = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -211,12 +226,11 @@ __global__ __launch_bounds__(64 * WPB) void k_gemv32(F32Args a) {
     }
     s = column_sum(s);  // the tile's 16 rows
     if (!ok) return;
-    *(floatx4 *)(a.x + (size_t)b * a.H + r) = xv;
+    *(floatx4 *)(a.x + (size_t)b * a.H + r0) = xv;
     if (a.gamma) {
-      floatx4 uv;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) uv[i] = xv[i] * a.gamma[r + i];
-      *(floatx4 *)(a.u + (size_t)b * a.H + r) = uv;
+      for (int i = 0; i < 4; ++i) gm[i] *= xv[i];
+      *(floatx4 *)(a.u + (size_t)b * a.H + r0) = gm;
     }
     if (c == 0) a.ss[(size_t)tile[0] * B + b] = s;
     return;
@@ -230,21 +244,24 @@ __global__ __launch_bounds__(64 * WPB) void k_gemv32(F32Args a) {
       const float gv = y[0][i] * inv, uv = y[MT - 1][i] * inv;
       hv[i] = gv / (1.0f + expf(-gv)) * uv;
     }
-    *(floatx4 *)(a.h + (size_t)b * a.F + tile[0] * 16 + 4 * c) = hv;
+    *(floatx4 *)(a.h + (size_t)b * a.F + r0) = hv;
   } else {
-    const int d = a.d, hd = d / 2, head = tile[0] / (d / 16);
+    const int d = a.d, head = tile[0] / (d / 16);
     const bool rot = head < a.nq + a.nkv;
     float *dst = head < a.nq ? a.q + ((size_t)b * a.nq + head) * d
                  : rot       ? a.ks + ((size_t)b * a.nkv + head - a.nq) * d
                              : a.vs + ((size_t)b * a.nkv + head - a.nq - a.nkv) * d;
+    floatx4 o1, o2;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int di = tile[0] * 16 + 4 * c + i - head * d;  // dimension in the first half
       const float y1 = y[0][i] * inv, y2 = y[MT - 1][i] * inv;
-      const double cs = a.rope[((size_t)b * hd + di) * 2], sn = a.rope[((size_t)b * hd + di) * 2 + 1];
-      dst[di] = rot ? (float)((double)y1 * cs - (double)y2 * sn) : y1;
-      dst[di + hd] = rot ? (float)((double)y2 * cs + (double)y1 * sn) : y2;
+      const double cs = rope[i][0], sn = rope[i][1];
+      o1[i] = rot ? (float)((double)y1 * cs - (double)y2 * sn) : y1;
+      o2[i] = rot ? (float)((double)y2 * cs + (double)y1 * sn) : y2;
     }
+    dst += r0 - head * d;  // the lane's first dimension (first half)
+    *(floatx4 *)dst = o1;
+    *(floatx4 *)(dst + d / 2) = o2;
   }
 }
 

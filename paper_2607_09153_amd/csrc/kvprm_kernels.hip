@@ -111,7 +111,7 @@ PrivateChunks private_chunk_rule(const Dims &dm, int n, const int *pages, const 
   }
   if (waves <= limit * 512 / 800)
     r.heads_per_block = 1;
-  else if (waves <= limit * 1024 / 800 && dm.nkv % 4 == 0)
+  else if (waves <= 1024 && dm.nkv % 4 == 0)
     r.heads_per_block = 4;
   return r;
 }

@@ -252,116 +252,68 @@ static int ksum_nmax(int ksp) {
 }
 
 
-// v += ss[i][b] for i = i0, i0 + P, ... < nss, in that order, eight loads in flight at a time.
-__device__ __forceinline__ void rms_tail(const float *__restrict__ ss, int B, int b, int i0, int P,
-                                         int nss, float &v) {
-  int i = i0;
-  for (; i + 7 * P < nss; i += 8 * P) {
-    float t[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) t[u] = ss[(size_t)(i + u * P) * B + b];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) v += t[u];
-  }
-  for (; i < nss; i += P) v += ss[(size_t)i * B + b];
-}
-
-// RMSNorm scales r_b = 1 / sqrt(mean(x_b^2) + eps) from the per-row-block sums of squares
-// ss[i][b], by one wave (B <= 8), without LDS or barriers: with Bq = B rounded up to a power
-// of two, lane l sums rows l / Bq, l / Bq + 64 / Bq, ... of candidate l % Bq (32 loads issued by
-// wave_rms_load, any further rows in wave_rms_finish), a butterfly over the lanes of equal
-// l % Bq completes the sums (identical in every lane and block), and each lane takes its own
-// candidate's.
-struct WaveRmsLoads {
-  float v[32];
-};
-
-__device__ __forceinline__ void wave_rms_load(const float *__restrict__ ss, int nss, int B,
-                                              WaveRmsLoads &ld) {
-  const int lane = threadIdx.x & 63;
-  int Bq = 1;
-  while (Bq < B) Bq <<= 1;
-  const int P = 64 / Bq;
-  const int bl = lane & (Bq - 1), part = lane / Bq;
-  const bool ok = bl < B;
-#pragma unroll
-  for (int u = 0; u < 32; ++u) {
-    const int i = part + u * P;
-    const bool in = ok && i < nss;
-    const float t = ss[(size_t)(in ? i : 0) * B + (ok ? bl : 0)];
-    ld.v[u] = in ? t : 0.f;
-  }
-}
-
-__device__ __forceinline__ float wave_rms_finish(const float *__restrict__ ss, int nss, int B, int b,
-                                                 int H, float eps, const WaveRmsLoads &ld) {
-  const int lane = threadIdx.x & 63;
-  int Bq = 1;
-  while (Bq < B) Bq <<= 1;
-  const int P = 64 / Bq;
-  const int bl = lane & (Bq - 1), part = lane / Bq;
-  float v = 0.f;
-#pragma unroll
-  for (int u = 0; u < 32; ++u) v += ld.v[u];
-  if (bl < B) rms_tail(ss, B, bl, part + 32 * P, P, nss, v);
-  for (int off = Bq; off < 64; off <<= 1) v += __shfl_xor(v, off, 64);
-  const float tot = __shfl(v, b, 64);
-  return 1.0f / sqrtf(tot / (float)H + eps);
-}
-
-// r_b = 1 / sqrt(mean(x_b^2) + eps) for every candidate, computed by a whole block of NTHR
-// threads from the per-row-block sums of squares ss[i][b] into inv_s[b]: with Bq = B rounded up
-// to a power of two, thread t sums rows t / Bq, t / Bq + NTHR / Bq, ... of candidate t % Bq,
-// and the NTHR / Bq partial sums of each candidate are added in a fixed order (a butterfly over a
-// wave's lanes of one candidate, then the waves in order), so every block gets identical values.
-// (One thread adding them all took 6 us of the 7B gate/up kernel's 49 for a single candidate.) rms_load issues a thread's first 16 loads (unconditional, clamped,
-// zero past the end) so that callers can start them early; rms_finish adds any further rows,
-// reduces, and contains two barriers.
+// RMSNorm scales r_b = 1 / sqrt(mean(x_b^2) + eps) for every candidate by a block of NTHR threads,
+// from the per-row-block sums of squares ss[i][b]: candidates in quads, Q = their number rounded
+// up to a power of two; thread t sums rows t / Q, t / Q + NTHR / Q, ... of quad t % Q with 16-byte
+// loads, and the partial sums of a candidate are added in a fixed order (a butterfly over a wave's
+// lanes of one quad, then the waves in order), so every block gets identical values. rms_load issues
+// the first four loads, to be called first; rms_partial adds them and any further rows and leaves each
+// wave's sums in part_s (NTHR / 64 x 4 Q floats); after a barrier of the caller's, rms_scale
+// gives a candidate's scale to any thread. (One thread adding every partial sum took 6 us of the
+// 7B gate/up kernel's 49 for a single candidate.) The last quad of a row may reach into the next
+// one, and past the last row into the workspace's next piece: values that no one uses.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 struct RmsLoads {
-  float v[16];
+  f32x4u v[4];
 };
 
+__device__ __forceinline__ int rms_quads(int B) {
+  int Q = 1;
+  while (4 * Q < B) Q <<= 1;
+  return Q;
+}
+
 template <int NTHR>
-__device__ __forceinline__ void rms_load(const float *__restrict__ ss, int nss, int B,
+__device__ __forceinline__ void rms_load(const float *__restrict__ ss, int nss, int B, int i0,
                                          RmsLoads &ld) {
-  const int t = threadIdx.x;
-  int Bq = 1;
-  while (Bq < B) Bq <<= 1;
-  const int P = NTHR / Bq;
-  const int b = t & (Bq - 1), part = t / Bq;
-  const bool ok = b < B;
+  const int Q = rms_quads(B), P = NTHR / Q;
+  const int q = threadIdx.x & (Q - 1), part = threadIdx.x / Q;
 #pragma unroll
-  for (int u = 0; u < 16; ++u) {
-    const int i = part + u * P;
-    const bool in = ok && i < nss;
-    const float x = ss[(size_t)(in ? i : 0) * B + (ok ? b : 0)];
-    ld.v[u] = in ? x : 0.f;
+  for (int u = 0; u < 4; ++u) {
+    const int i = i0 + part + u * P;
+    ld.v[u] = *(const f32x4u *)(ss + (i < nss && 4 * q < B ? i * B + 4 * q : 0));
   }
 }
 
 template <int NTHR>
-__device__ __forceinline__ void rms_finish(const float *__restrict__ ss, int nss, int B, int H,
-                                           float eps, const RmsLoads &ld, float *part_s,
-                                           float *inv_s) {
-  const int t = threadIdx.x;
-  int Bq = 1;
-  while (Bq < B) Bq <<= 1;
-  const int P = NTHR / Bq;
-  const int b = t & (Bq - 1), part = t / Bq;
-  float v = 0.f;
+__device__ __forceinline__ void rms_partial(const float *__restrict__ ss, int nss, int B,
+                                            RmsLoads &ld, float *part_s) {
+  const int Q = rms_quads(B), P = NTHR / Q;
+  const int q = threadIdx.x & (Q - 1), part = threadIdx.x / Q;
+  floatx4 v = {0.f, 0.f, 0.f, 0.f};
+  for (int i0 = 0;; i0 += 4 * P) {  // block-uniform
 #pragma unroll
-  for (int u = 0; u < 16; ++u) v += ld.v[u];
-  if (b < B) rms_tail(ss, B, b, part + 16 * P, P, nss, v);
-  for (int off = Bq; off < 64; off <<= 1) v += __shfl_xor(v, off, 64);
-  if ((t & 63) < Bq) part_s[(t >> 6) * Bq + b] = v;
-  __syncthreads();
-  if (t < B) {
-    float s = 0.f;
+    for (int u = 0; u < 4; ++u)
+      if (i0 + part + u * P < nss)
 #pragma unroll
-    for (int k = 0; k < NTHR / 64; ++k) s += part_s[k * Bq + t];
-    inv_s[t] = 1.0f / sqrtf(s / (float)H + eps);
+        for (int e = 0; e < 4; ++e) v[e] += ld.v[u][e];
+    if (i0 + 4 * P >= nss) break;
+    rms_load<NTHR>(ss, nss, B, i0 + 4 * P, ld);
   }
-  __syncthreads();
+  for (int off = Q; off < 64; off <<= 1)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] += __shfl_xor(v[e], off, 64);
+  if ((threadIdx.x & 63) < Q)
+    *(floatx4 *)(part_s + ((threadIdx.x >> 6) * Q + q) * 4) = v;
+}
+
+template <int NTHR>
+__device__ __forceinline__ float rms_scale(const float *part_s, int B, int b, int H, float eps) {
+  const int Q = rms_quads(B);
+  float s = 0.f;
+#pragma unroll
+  for (int k = 0; k < NTHR / 64; ++k) s += part_s[k * Q * 4 + b];
+  return 1.0f / sqrtf(s / (float)H + eps);
 }
 
 // ------------------------------------------------------------- GEMV with fused epilogue
@@ -410,13 +362,21 @@ struct FusedArgs {
   int nq, nkv, d;
 };
 
+// gate / up pre-activations f .. f + 3 of candidate b, where the call keeps them
+__device__ __forceinline__ void save_gate_up(const FusedArgs &a, int b, int f, const float (&gv)[4],
+                                             const float (&uv)[4]) {
+  if (!a.save) return;
+  float *p = a.save + (size_t)b * 2 * a.F + f;
+  *(float4 *)p = make_float4(gv[0], gv[1], gv[2], gv[3]);
+  *(float4 *)(p + a.F) = make_float4(uv[0], uv[1], uv[2], uv[3]);
+}
+
 template <int MT, int NT, int WPB, int U, int EPI>
 __global__ __launch_bounds__(64 * WPB) void k_gemv_fused(FusedArgs a) {
   constexpr int NG = NT == 1 ? 1 : NT / 2;  // candidate groups
   static_assert(NG <= WPB, "one wave per candidate group in the epilogue");
   __shared__ floatx4 red_s[WPB][MT][NG][64];
-  __shared__ float part_s[64 * WPB];
-  __shared__ float inv_s[64];
+  __shared__ __align__(16) float part_s[64 * WPB];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int B = a.B;
   // global row tiles of this block
@@ -449,13 +409,34 @@ __global__ __launch_bounds__(64 * WPB) void k_gemv_fused(FusedArgs a) {
   const int per = (nkb + WPB - 1) / WPB;
   const int kb0 = min(nkb, wave * per), kb1 = min(nkb, kb0 + per);
   const uint4 *ap = a.act + lane;
-  // the epilogue's sums of squares are fetched now and used after the product: by wave 0
-  // alone for one column tile (B <= 8), by the whole block for two
-  WaveRmsLoads wl;
+  // What the epilogue reads is fetched now and used after the product: the sums of squares by the
+  // whole block, the residual and the gain, or the rotary table, by the wave that will need them
+  // (lane (n, cq): rows 4 cq .. 4 cq + 3 of candidate n of group `wave`). Loaded in the epilogue
+  // they were eight memory round trips in a row, as its stores may alias them.
   RmsLoads rl;
   constexpr bool RMS = EPI == EPI_SWIGLU || EPI == EPI_ROPE;  // RMSNorm scale in the epilogue
-  if (RMS && NT == 1 && wave == 0) wave_rms_load(a.ss, a.nss, B, wl);
-  if (RMS && NT >= 2) rms_load<64 * WPB>(a.ss, a.nss, B, rl);
+  const int n = lane & 15, cq = lane >> 4;
+  const int cand = NT == 1 ? n : 16 * wave + n;
+  const bool cand_ok = wave < NG && (NT == 1 ? (n < 8 && n < B) : cand < B);
+  const int b = cand_ok ? cand : 0;
+  float4 ex[EPI == EPI_ROPE ? 2 : MT];  // residual rows; rotary pairs (cos, sin) x 4
+  float eg[MT][4];                      // gains
+  if (wave < NG && EPI == EPI_RESID) {
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      const int r = tile[m] * 16 + 4 * cq;
+      ex[m] = *(const float4 *)(a.x + (size_t)b * a.H + r);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) eg[m][i] = a.gamma ? ld_bf16(a.gamma, r + i) : 0.f;
+    }
+  }
+  if (wave < NG && EPI == EPI_ROPE) {
+    const int di = (tile[0] % (a.d / 16)) * 16 + 4 * cq;
+    const float4 *rp = (const float4 *)(a.rope + ((size_t)b * (a.d / 2) + di) * 2);
+    ex[0] = rp[0];
+    ex[EPI == EPI_ROPE ? 1 : 0] = rp[1];
+  }
+  if (RMS) rms_load<64 * WPB>(a.ss, a.nss, B, 0, rl);
   floatx4 acc[MT][NT];
 #pragma unroll
   for (int m = 0; m < MT; ++m)
@@ -532,20 +513,17 @@ __global__ __launch_bounds__(64 * WPB) void k_gemv_fused(FusedArgs a) {
                        : acc[m][gi][i] + acc[m][gi + NG][i];
       red_s[wave][m][gi][lane] = v;
     }
+  if (RMS) rms_partial<64 * WPB>(a.ss, a.nss, B, rl, part_s);
   __syncthreads();
-  if (RMS && NT >= 2) rms_finish<64 * WPB>(a.ss, a.nss, B, a.H, a.eps, rl, part_s, inv_s);
   if (wave >= NG) return;
-  const int gi = wave;
-  // fixed-order sum over the waves; lane (n, cq) holds rows 4 cq .. 4 cq + 3 of candidate n of
-  // group gi
-  const int n = lane & 15, cq = lane >> 4;
+  // fixed-order sum over the waves
   float y[MT][4];
 #pragma unroll
   for (int m = 0; m < MT; ++m) {
-    floatx4 tt = red_s[0][m][gi][lane];
+    floatx4 tt = red_s[0][m][wave][lane];
 #pragma unroll
     for (int w = 1; w < WPB; ++w) {
-      const floatx4 v = red_s[w][m][gi][lane];
+      const floatx4 v = red_s[w][m][wave][lane];
       tt[0] += v[0];
       tt[1] += v[1];
       tt[2] += v[2];
@@ -554,59 +532,64 @@ __global__ __launch_bounds__(64 * WPB) void k_gemv_fused(FusedArgs a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) y[m][i] = tt[i];
   }
-  const int cand = NT == 1 ? n : 16 * gi + n;
-  const bool cand_ok = NT == 1 ? (n < 8 && n < B) : cand < B;
-  const int b = cand_ok ? cand : 0;
   if (EPI == EPI_RESID) {
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
+      const int r = tile[m] * 16 + 4 * cq;
+      const float xv[4] = {ex[m].x + y[m][0], ex[m].y + y[m][1], ex[m].z + y[m][2],
+                           ex[m].w + y[m][3]};
+      // rows of the tile: the lane's 4, then the 4 lane groups cq, in a fixed order
       float sq = 0.f;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int r = tile[m] * 16 + 4 * cq + i;
-        float xv = 0.f;
-        if (cand_ok) {
-          xv = a.x[(size_t)b * a.H + r] + y[m][i];
-          a.x[(size_t)b * a.H + r] = xv;
-          if (a.xsave) a.xsave[(size_t)b * a.H + r] = xv;
-          if (a.gamma) store_operand(a.op, a.NT, a.Bp, r, b, xv * ld_bf16(a.gamma, r));
+      for (int i = 0; i < 4; ++i) sq += xv[i] * xv[i];
+      sq = column_sum(sq);
+      if (cand_ok) {
+        const float4 xn = make_float4(xv[0], xv[1], xv[2], xv[3]);
+        *(float4 *)(a.x + (size_t)b * a.H + r) = xn;
+        if (a.xsave) *(float4 *)(a.xsave + (size_t)b * a.H + r) = xn;
+        if (a.gamma) {
+          const float u[4] = {xv[0] * eg[m][0], xv[1] * eg[m][1], xv[2] * eg[m][2],
+                              xv[3] * eg[m][3]};
+          store_operand4(a.op, a.NT, a.Bp, r, b, u);
         }
-        sq += xv * xv;
+        if (cq == 0) a.ss[(size_t)tile[m] * B + b] = sq;
       }
-      // rows of the tile: the 4 lane groups cq, in a fixed order
-      sq += __shfl_xor(sq, 16, 64);
-      sq += __shfl_xor(sq, 32, 64);
-      if (cand_ok && cq == 0) a.ss[(size_t)tile[m] * B + b] = sq;
     }
   } else if (EPI == EPI_ROPE) {
-    const float inv = NT == 1 ? wave_rms_finish(a.ss, a.nss, B, b, a.H, a.eps, wl) : inv_s[b];
+    const float inv = rms_scale<64 * WPB>(part_s, B, b, a.H, a.eps);
     const int d = a.d, hd = d / 2;
     const int head = tile[0] / (d / 16);
+    const int di = tile[0] * 16 + 4 * cq - head * d;  // the lane's first dimension (first half)
     const bool rot = head < a.nq + a.nkv;  // q and k heads rotate, v heads do not
     float *dst = head < a.nq ? a.q + ((size_t)b * a.nq + head) * d
                  : head < a.nq + a.nkv ? a.ks + ((size_t)b * a.nkv + head - a.nq) * d
                                        : a.vs + ((size_t)b * a.nkv + head - a.nq - a.nkv) * d;
+    const float4 r0 = ex[0], r1 = ex[EPI == EPI_ROPE ? 1 : 0];
+    const float cs[4] = {r0.x, r0.z, r1.x, r1.z}, sn[4] = {r0.y, r0.w, r1.y, r1.w};
+    float o1[4], o2[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int di = tile[0] * 16 + 4 * cq + i - head * d;  // dimension in the first half
       const float y1 = y[0][i] * inv, y2 = y[MT - 1][i] * inv;
-      const float2 csn = *(const float2 *)(a.rope + ((size_t)b * hd + di) * 2);
-      if (cand_ok) {
-        dst[di] = rot ? y1 * csn.x - y2 * csn.y : y1;
-        dst[di + hd] = rot ? y2 * csn.x + y1 * csn.y : y2;
-      }
+      o1[i] = rot ? y1 * cs[i] - y2 * sn[i] : y1;
+      o2[i] = rot ? y2 * cs[i] + y1 * sn[i] : y2;
+    }
+    if (cand_ok) {
+      *(float4 *)(dst + di) = make_float4(o1[0], o1[1], o1[2], o1[3]);
+      *(float4 *)(dst + di + hd) = make_float4(o2[0], o2[1], o2[2], o2[3]);
     }
   } else {  // EPI_SWIGLU
-    const float inv = NT == 1 ? wave_rms_finish(a.ss, a.nss, B, b, a.H, a.eps, wl) : inv_s[b];
+    const float inv = rms_scale<64 * WPB>(part_s, B, b, a.H, a.eps);
+    const int f = tile[0] * 16 + 4 * cq;
+    float gv[4], uv[4], hv[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int f = tile[0] * 16 + 4 * cq + i;
-      const float gv = y[0][i] * inv, uv = y[MT - 1][i] * inv;
-      if (cand_ok) store_operand(a.op, a.NT, a.Bp, f, b, gv / (1.0f + expf(-gv)) * uv);
-      if (cand_ok && a.save) {
-        a.save[(size_t)b * 2 * a.F + f] = gv;
-        a.save[(size_t)b * 2 * a.F + a.F + f] = uv;
-      }
+      gv[i] = y[0][i] * inv;
+      uv[i] = y[MT - 1][i] * inv;
+      hv[i] = gv[i] / (1.0f + expf(-gv[i])) * uv[i];
+    }
+    if (cand_ok) {
+      store_operand4(a.op, a.NT, a.Bp, f, b, hv);
+      save_gate_up(a, b, f, gv, uv);
     }
   }
 }
@@ -635,8 +618,7 @@ __global__ __launch_bounds__(64 * WPB, 4) void k_gateup_wide(FusedArgs a) {
   // 64 16-byte entries)
   static_assert(2 * U * NT >= HALF * NG, "the up sums fit in the operand buffers");
   __shared__ uint4 op_s[2][U * NT * 64];
-  __shared__ float part_s[64 * WPB];
-  __shared__ float inv_s[64];
+  __shared__ __align__(16) float part_s[64 * WPB];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int B = a.B;
   const int ntf = a.F / 16;
@@ -648,7 +630,7 @@ __global__ __launch_bounds__(64 * WPB, 4) void k_gateup_wide(FusedArgs a) {
   const uint4 *wp = (const uint4 *)a.w[up ? 1 : 0] + (size_t)tl * 64 + lane;
   const int nbat = (a.K >> 5) / U;  // the launcher guarantees K / 32 % U == 0
   RmsLoads rl;
-  rms_load<64 * WPB>(a.ss, a.nss, B, rl);
+  rms_load<64 * WPB>(a.ss, a.nss, B, 0, rl);
   floatx4 acc[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -686,12 +668,13 @@ __global__ __launch_bounds__(64 * WPB, 4) void k_gateup_wide(FusedArgs a) {
   // weights two batches before they are used, so that each load has a whole batch of products
   // and a barrier to arrive
   load_op(0, ov);
-  store_op(0, ov);
   load_w(0, wa);
+  store_op(0, ov);
   if (nbat > 1) {
     load_op(1, ov);
     load_w(1, wb);
   }
+  rms_partial<64 * WPB>(a.ss, a.nss, B, rl, part_s);
   __syncthreads();
   for (int bat = 0; bat < nbat; bat += 2) {  // block-uniform trip counts and barriers
     mma(0, wa);
@@ -735,27 +718,26 @@ __global__ __launch_bounds__(64 * WPB, 4) void k_gateup_wide(FusedArgs a) {
     for (int gi = 0; gi < NG; ++gi)
       xch[((wave - HALF) * NG + gi) * 64 + lane] = make_float4(hl[gi][0], hl[gi][1], hl[gi][2], hl[gi][3]);
   }
-  rms_finish<64 * WPB>(a.ss, a.nss, B, a.H, a.eps, rl, part_s, inv_s);  // has barriers
+  __syncthreads();
   if (up || !own) return;
   const int n = lane & 15, cq = lane >> 4;
 #pragma unroll
   for (int gi = 0; gi < NG; ++gi) {
     const int cand = NT == 1 ? n : 16 * gi + n;
     if (cand >= B || (NT == 1 && n >= 8)) continue;
-    const float inv = inv_s[cand];
+    const float inv = rms_scale<64 * WPB>(part_s, B, cand, a.H, a.eps);
     const float4 uvv = xch[(wave * NG + gi) * 64 + lane];
     const float uv4[4] = {uvv.x, uvv.y, uvv.z, uvv.w};
+    const int f = tl * 16 + 4 * cq;
+    float gv[4], uv[4], hv[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int f = tl * 16 + 4 * cq + i;
-      const float gv = hl[gi][i] * inv;
-      const float uv = uv4[i] * inv;
-      store_operand(a.op, a.NT, a.Bp, f, cand, gv / (1.0f + expf(-gv)) * uv);
-      if (a.save) {
-        a.save[(size_t)cand * 2 * a.F + f] = gv;
-        a.save[(size_t)cand * 2 * a.F + a.F + f] = uv;
-      }
+      gv[i] = hl[gi][i] * inv;
+      uv[i] = uv4[i] * inv;
+      hv[i] = gv[i] / (1.0f + expf(-gv[i])) * uv[i];
     }
+    store_operand4(a.op, a.NT, a.Bp, f, cand, hv);
+    save_gate_up(a, cand, f, gv, uv);
   }
 }
 
@@ -772,8 +754,7 @@ __global__ __launch_bounds__(64 * WPB, 1) void k_gateup_pair(FusedArgs a) {
   constexpr int PER = (PIECES + 64 * WPB - 1) / (64 * WPB);
   constexpr bool EVEN = PER * 64 * WPB == PIECES;
   __shared__ uint4 op_s[2][U * NT * 64];
-  __shared__ float part_s[64 * WPB];
-  __shared__ float inv_s[64];
+  __shared__ __align__(16) float part_s[64 * WPB];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int B = a.B;
   const int ntf = a.F / 16;
@@ -785,7 +766,7 @@ __global__ __launch_bounds__(64 * WPB, 1) void k_gateup_pair(FusedArgs a) {
   const uint4 *wpu = (const uint4 *)a.w[1] + (size_t)tl * 64 + lane;
   const int nbat = (a.K >> 5) / U;  // the launcher guarantees K / 32 % U == 0
   RmsLoads rl;
-  rms_load<64 * WPB>(a.ss, a.nss, B, rl);
+  rms_load<64 * WPB>(a.ss, a.nss, B, 0, rl);
   floatx4 acc[2][NT];
 #pragma unroll
   for (int m = 0; m < 2; ++m)
@@ -842,12 +823,14 @@ __global__ __launch_bounds__(64 * WPB, 1) void k_gateup_pair(FusedArgs a) {
     }
   };
   load_op(0, ov);
-  store_op(0, ov);
   load_w(0, wa);
+  store_op(0, ov);
   if (nbat > 1) {
     load_op(1, ov);
     load_w(1, wb);
   }
+  // (before the loop, whose accumulators leave no registers for its loads)
+  rms_partial<64 * WPB>(a.ss, a.nss, B, rl, part_s);
   __syncthreads();
   for (int bat = 0; bat < nbat; bat += 2) {  // block-uniform trip counts and barriers
     mma(0, wa, bat + 2);
@@ -874,25 +857,23 @@ __global__ __launch_bounds__(64 * WPB, 1) void k_gateup_pair(FusedArgs a) {
       }
     }
   }
-  rms_finish<64 * WPB>(a.ss, a.nss, B, a.H, a.eps, rl, part_s, inv_s);  // has barriers
   if (!own) return;
   const int n = lane & 15, cq = lane >> 4;
 #pragma unroll
   for (int gi = 0; gi < NG; ++gi) {
     const int cand = 16 * gi + n;
     if (cand >= B) continue;
-    const float inv = inv_s[cand];
+    const float inv = rms_scale<64 * WPB>(part_s, B, cand, a.H, a.eps);
+    const int f = tl * 16 + 4 * cq;
+    float gv[4], uv[4], hv[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int f = tl * 16 + 4 * cq + i;
-      const float gv = (acc[0][gi][i] + acc[0][gi + NG][i]) * inv;
-      const float uv = (acc[1][gi][i] + acc[1][gi + NG][i]) * inv;
-      store_operand(a.op, a.NT, a.Bp, f, cand, gv / (1.0f + expf(-gv)) * uv);
-      if (a.save) {
-        a.save[(size_t)cand * 2 * a.F + f] = gv;
-        a.save[(size_t)cand * 2 * a.F + a.F + f] = uv;
-      }
+      gv[i] = (acc[0][gi][i] + acc[0][gi + NG][i]) * inv;
+      uv[i] = (acc[1][gi][i] + acc[1][gi + NG][i]) * inv;
+      hv[i] = gv[i] / (1.0f + expf(-gv[i])) * uv[i];
     }
+    store_operand4(a.op, a.NT, a.Bp, f, cand, hv);
+    save_gate_up(a, cand, f, gv, uv);
   }
 }
 
@@ -1037,13 +1018,15 @@ __global__ __launch_bounds__(256) void k_resid_split_fin(const float *__restrict
   if (e >= B * H) return;  // (whole 16-lane groups: H is a multiple of 16)
   const int b = e / H, r = e - b * H;
   const size_t stride = (size_t)B * H;
+  // (every load before the first store, which may alias them)
+  const float x0 = x[e], gm = gamma ? ld_bf16(gamma, r) : 0.f;
   float y = 0.f;
 #pragma unroll 8
   for (int k = 0; k < ksplit; ++k) y += part[(size_t)k * stride + e];
-  const float xv = x[e] + y;
+  const float xv = x0 + y;
   x[e] = xv;
   if (xsave) xsave[e] = xv;
-  if (gamma) store_operand(op, NT, Bp, r, b, xv * ld_bf16(gamma, r));
+  if (gamma) store_operand(op, NT, Bp, r, b, xv * gm);
   float sq = xv * xv;
   sq += __shfl_xor(sq, 1, 64);
   sq += __shfl_xor(sq, 2, 64);
@@ -1075,6 +1058,7 @@ __global__ __launch_bounds__(256) void k_qkv_split_fin(const float *__restrict__
   const size_t stride = (size_t)B * rows;
   float y1 = 0.f, y2 = 0.f;
   const float *p1 = part + (size_t)b * rows + r;
+  const float2 csn = *(const float2 *)(rope + ((size_t)b * hd + i) * 2);
 #pragma unroll 8
   for (int k = 0; k < ksplit; ++k) {
     y1 += p1[(size_t)k * stride];
@@ -1095,7 +1079,6 @@ __global__ __launch_bounds__(256) void k_qkv_split_fin(const float *__restrict__
   s1 = wsum(s1);
   const float inv = 1.0f / sqrtf((b == b0 ? s0 : s1) / (float)H + eps);
   if (!act) return;
-  const float2 csn = *(const float2 *)(rope + ((size_t)b * hd + i) * 2);
   const float x1 = y1 * inv, x2 = y2 * inv;
   const bool rot = head < nq + nkv;
   float *dst = head < nq ? q + ((size_t)b * nq + head) * d
@@ -1237,7 +1220,7 @@ __global__ __launch_bounds__(256) void k_qkv_fin_mx(const float *__restrict__ pa
                                                     int nkv, int d, const float *__restrict__ rope,
                                                     float *__restrict__ q, float *__restrict__ ks,
                                                     float *__restrict__ vs) {
-  __shared__ float part_s[256], inv_s[64];
+  __shared__ __align__(16) float part_s[256];
   const int hd = d / 2;
   const int e = blockIdx.x * 256 + threadIdx.x;
   const bool act = e < (nq + 2 * nkv) * hd * B;
@@ -1251,12 +1234,13 @@ __global__ __launch_bounds__(256) void k_qkv_fin_mx(const float *__restrict__ pa
   ksum_load<NMAX>(part, ksp, i2, v2);
   const float2 csn = *(const float2 *)(rope + ((size_t)b * hd + i) * 2);
   RmsLoads rl;
-  rms_load<256>(ss, nss, B, rl);
-  rms_finish<256>(ss, nss, B, H, eps, rl, part_s, inv_s);  // has barriers: every thread
+  rms_load<256>(ss, nss, B, 0, rl);
+  rms_partial<256>(ss, nss, B, rl, part_s);
+  __syncthreads();
   const float x1 = ksum_add<NMAX>(part, ksp, ksplit, i1, v1);
   const float x2 = ksum_add<NMAX>(part, ksp, ksplit, i2, v2);
   if (!act) return;
-  const float inv = inv_s[b];
+  const float inv = rms_scale<256>(part_s, B, b, H, eps);
   const float y1 = x1 * inv, y2 = x2 * inv;
   const bool rot = head < nq + nkv;
   float *dst = head < nq ? q + ((size_t)b * nq + head) * d

@@ -80,6 +80,19 @@ __device__ __forceinline__ void store_operand(uint16_t *op, int NT, int Bp, int 
   op[((size_t)((kb * NT + (col >> 4)) * 64 + c * 16 + (col & 15))) * 8 + i] = (uint16_t)lo;
 }
 
+// The same for inputs k .. k + 3 (k a multiple of 4): two 8-byte stores.
+__device__ __forceinline__ void store_operand4(uint16_t *op, int NT, int Bp, int k, int cand,
+                                               const float (&v)[4]) {
+  uint2 hi, lo;
+  split2(v[0], v[1], hi.x, lo.x);
+  split2(v[2], v[3], hi.y, lo.y);
+  const int kb = k >> 5, c = (k >> 3) & 3, i = k & 7;
+  int col = cand;
+  *(uint2 *)(op + (size_t)((kb * NT + (col >> 4)) * 64 + c * 16 + (col & 15)) * 8 + i) = hi;
+  col = cand + Bp;
+  *(uint2 *)(op + (size_t)((kb * NT + (col >> 4)) * 64 + c * 16 + (col & 15)) * 8 + i) = lo;
+}
+
 __device__ __forceinline__ float wsum(float v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
