@@ -215,6 +215,14 @@ static kvprm_status plan_for(const kvprm_handle h, const kvprm_batch *b, int ran
   return KVPRM_OK;
 }
 
+// Short caches take the one-launch attention up to a block (candidate x kv-head) per compute unit
+// and kShortPages pages, with fp32 caches one page per wave (their pages are bound by products,
+// which more waves than one block's share better). Per layer, one launch / chunks and merge:
+// H = 256, 8 candidates: 300 tokens fp8 29.5 / 34.3 us, bf16 29.4 / 32.6, 512 tokens 31.0 / 32.8,
+// fp32 100 tokens 27.0 / 28.8 but 512 32.7 / 30.1; H = 1024 with 8 kv-heads, 100 tokens, 256 blocks
+// 46.9 / 49.0 but 512 blocks 61.3 / 58.6; 7B shape, 64 candidates of 300 148.8 / 154.8.
+constexpr int kShortBlocks = 256;
+
 // Shared-prefix chunk: the longest of 16, 32, 64 pages that leaves at least 160 work items for
 // `pages` pages.
 static int chunk_shift_for(long long pages) {
@@ -269,10 +277,15 @@ static GroupTable group_table(const kvprm_handle h, const kvprm_batch *b, const 
   gt.heads_per_block = pc.heads_per_block;
   const int CP = 1 << pc.shift;
   gt.private_chunks = 1;
+  int longest = 0;
   for (int i = 0; i < b->batch; ++i) {
     const int ch = (priv[i] + CP - 1) / CP;
     if (ch > gt.private_chunks) gt.private_chunks = ch;
+    if (priv[i] > longest) longest = priv[i];
   }
+  // (a prefix group's shared pages are read by the chunk kernels)
+  gt.one_launch = gt.n == 0 && longest <= (h->dm.kvdt == 0 ? kShortWaves : kShortPages) &&
+                  b->batch * h->dm.nkv <= kShortBlocks;
   return gt;
 }
 
@@ -366,11 +379,8 @@ static kvprm_status score_mx(const kvprm_handle h, const kvprm_kv_cache *cache,
     HIP_TRY(launch_qkv_mx(dm, p, wl, W.wq, W.wk, W.wv, t_qkv, s), "qkv projection");
     HIP_TRY(launch_attention(dm, p, w, l, cache->k_pages, cache->v_pages, cache->k_scale,
                              cache->v_scale, cache->num_pages, b->page_table, b->lengths, gt, wl.q,
-                             s),
+                             wl.kself, wl.vself, o_save, w.opO, s, lse_save),
             "attention");
-    HIP_TRY(launch_merge_mx(dm, p, w, b->lengths, gt, wl.q, wl.kself, wl.vself, o_save, w.opO, s,
-                            lse_save),
-            "attention merge");
     if (lora && t_o.tkb) {
       const void *a_o[3] = {lora->layers[l].o.a, nullptr, nullptr};
       HIP_TRY(launch_lora_a(dm, p, w, LORA_O, a_o, lora->scale, w.opO, s), "output adapter");
@@ -450,7 +460,7 @@ static kvprm_status score_impl(kvprm_handle h, const kvprm_kv_cache *cache, cons
       return st;
     return ok();
   }
-  // fp32 pipeline: six launches per layer
+  // fp32 pipeline: five or six launches per layer
   HIP_TRY(launch_init_f32(dm, p, w, wts->verify_embed, wts->layers[0].attn_norm, b->lengths, s),
           "init");
   for (int l = 0; l < dm.layers; ++l) {
@@ -458,10 +468,9 @@ static kvprm_status score_impl(kvprm_handle h, const kvprm_kv_cache *cache, cons
     const void *gamma_next = l + 1 < dm.layers ? wts->layers[l + 1].attn_norm : nullptr;
     HIP_TRY(launch_qkv_f32(dm, p, w, W.wq, W.wk, W.wv, s), "qkv projection");
     HIP_TRY(launch_attention(dm, p, w, l, cache->k_pages, cache->v_pages, nullptr, nullptr,
-                             cache->num_pages, b->page_table, b->lengths, gt, w.q, s),
+                             cache->num_pages, b->page_table, b->lengths, gt, w.q, w.kself,
+                             w.vself, w.o, nullptr, s),
             "attention");
-    HIP_TRY(launch_merge_mx(dm, p, w, b->lengths, gt, w.q, w.kself, w.vself, w.o, nullptr, s),
-            "attention merge");
     HIP_TRY(launch_resid_f32(dm, p, w, W.wo, w.o, dm.nq * dm.d, W.ffn_norm, s),
             "output projection");
     HIP_TRY(launch_gateup_f32(dm, p, w, W.w_gate, W.w_up, s), "gate/up projection");
@@ -765,11 +774,8 @@ kvprm_status kvprm_attention(kvprm_handle h, const kvprm_kv_cache *cache, const 
   const GroupTable gt = group_table(h, b, p);
   HIP_TRY(launch_attention(dm, p, w, layer, cache->k_pages, cache->v_pages, cache->k_scale,
                            cache->v_scale, cache->num_pages, b->page_table, b->lengths, gt, q,
-                           (hipStream_t)stream),
+                           k_self, v_self, o, nullptr, (hipStream_t)stream),
           "attention");
-  HIP_TRY(launch_merge_mx(dm, p, w, b->lengths, gt, q, k_self, v_self, o, nullptr,
-                          (hipStream_t)stream),
-          "attention merge");
   return ok();
 }
 
@@ -792,7 +798,8 @@ kvprm_status kvprm_attention_partials(kvprm_handle h, const kvprm_kv_cache *cach
   const Workspace w = carve(dm, p, workspace);
   HIP_TRY(launch_attention(dm, p, w, layer, cache->k_pages, cache->v_pages, cache->k_scale,
                            cache->v_scale, cache->num_pages, b->page_table, b->lengths,
-                           group_table(h, b, p), q, (hipStream_t)stream),
+                           group_table(h, b, p), q, nullptr, nullptr, nullptr, nullptr,
+                           (hipStream_t)stream, nullptr, true),
           "attention partials");
   return ok();
 }

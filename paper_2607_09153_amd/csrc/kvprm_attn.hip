@@ -252,54 +252,23 @@ struct AttnArgs {
                   // candidate, group ranges in rows
 };
 
-// One block per (chunk of pages, candidate b, group of kv-heads) over the candidate's private
-// pages, one wave per kv-head j (with every head in one block the n_kv tiles of a page,
-// contiguous in the pool, are read together; the call's GroupTable says how many heads).
-// Each wave walks the chunk two pages (32 tokens) at a time: S = K Q^T on the matrix cores
-// (A = the K tile, 16 tokens x 32 dims; B = the g query heads of j as columns, in three bf16
-// terms), online softmax per head in registers (a lane holds 4 tokens of one head per page),
-// then O^T += V^T P^T (A = V^T, 16 dims x 32 tokens; the V tile stores 4 consecutive slots of
-// a dimension together, so one 16-byte load per lane feeds 2 (bf16) or 4 (fp8) A operands; B =
-// P^T hi and lo). The wave writes its unnormalised partial (acc, m, l) per q-head.
-// Slots at or beyond L_b are masked in S and zeroed in V (they may hold anything, NaN included).
-// The start of a block (query, lengths, page ids, first pair) is a serial chain that every block
-// pays once: with one branch-guarded 4-byte load per query element and the bf16 split in integer
-// arithmetic it took 1.5-2 us more than with 16-byte loads issued first and the hardware
-// pack-convert (7B batch of 16: 26.9 -> 25.2 us a layer, ragged 32k 67.9 -> 66.4, private pages of
-// the 64-candidate beam 34.6 -> 32.3, shared prefix 52.7 -> 49.9).
+// A wave's walk over pages [p0, p0 + np) (1 to 64) of candidate b and kv-head j, two pages (32
+// tokens) at a time: S = K Q^T on the matrix cores (A = the K tile, 16 tokens x 32 dims; B = the
+// query columns, in three bf16 terms), online softmax per column in registers (a lane holds 4
+// tokens of one column per page), then O^T += V^T P^T (A = V^T, 16 dims x 32 tokens; the V tile
+// stores 4 consecutive slots of a dimension together, so one 16-byte load per lane feeds 2 (bf16)
+// or 4 (fp8) A operands; B = P^T hi and lo). Slots at or beyond L are masked in S and zeroed in V
+// (they may hold anything, NaN included). m_run (log2 units), l_run (this lane's tokens) and acc
+// come in as an empty state.
 template <int KVT, int D>
-__global__ __launch_bounds__(64 * kMaxKvHeadsMx) void k_attn_mx(AttnArgs a) {
+__device__ __forceinline__ void walk_pages(const AttnArgs &a, int b, int j, int L, int npages, int p0,
+                                           int np, const QueryRaw<D> &qraw, bool colv, float &m_run,
+                                           float &l_run, floatx4 (&acc)[D / 16]) {
   constexpr int NKB = D / 32;  // 32-dim blocks of q.k
   constexpr int NDB = D / 16;  // 16-dim blocks of the output
-  constexpr int EB = KVT == 1 ? 2 : 1;
-  constexpr size_t TILE = (size_t)kPage * D * EB;
-  const int c = blockIdx.x, b = blockIdx.y;  // chunk, candidate
-  // (the wave index as a scalar, so that tile addresses are scalar too)
-  const int j =
-      __builtin_amdgcn_readfirstlane((int)(blockIdx.z * (blockDim.x >> 6) + (threadIdx.x >> 6)));
-  const int nkv = a.nkv, g = a.g, nq = a.nq, kq = a.kq;
-  const int L = a.lengths[b];
-  const int lane = threadIdx.x & 63;
-  const int n = lane & 15, cq = lane >> 4;
-  // column n: verify token n / g of this candidate, q-head j g + n % g (kq g <= 16 columns; the
-  // division by multiplication: n < 16, g <= 16)
-  const bool colv = n < kq * g;
-  const int ti = colv ? (n * a.ginv) >> 16 : 0, hh = colv ? n - ti * g : 0;
-  const size_t row = (size_t)b * kq + ti;
-  // the query is the one load that depends on nothing: issued first, split into operands while
-  // the first page pair is in flight
-  QueryRaw<D> qraw;
-  load_query<KVT, D>(a.q + (row * nq + (size_t)j * g + hh) * D, cq, qraw);
-  __builtin_amdgcn_sched_barrier(0);
-  const int npages = (L + kPage - 1) / kPage;
-  int first = 0;
-  for (int gi = 0; gi < a.gt.n; ++gi)
-    if (b * kq >= a.gt.start[gi] && b * kq < a.gt.start[gi + 1]) first = a.gt.prefix_pages[gi];
-  const int CP = 1 << a.gt.cshift_private;
-  const int ncp = (first + (1 << a.gt.cshift_prefix) - 1) >> a.gt.cshift_prefix;  // prefix chunks
-  const int p0 = first + c * CP;
-  if (p0 >= npages) return;
-  const int np = min(npages, p0 + CP) - p0;
+  constexpr size_t TILE = (size_t)kPage * D * (KVT == 1 ? 2 : 1);
+  const int nkv = a.nkv;
+  const int lane = threadIdx.x & 63, cq = lane >> 4;
   // each wave reads the chunk's page ids itself into lane registers (lane i holds page i, lanes
   // past the chunk its last page, and for fp8 their scales) and fetches them with scalar lane
   // reads: no LDS, no barrier
@@ -325,11 +294,6 @@ __global__ __launch_bounds__(64 * kMaxKvHeadsMx) void k_attn_mx(AttnArgs a) {
   uint4 q0[NKB], q1[NKB], q2[NKB];
   query_ops<D>(qraw, colv, q0, q1, q2);
   const float rs = kLog2e / sqrtf((float)D);  // scores in log2 units
-  float m_run = -INFINITY, l_run = 0.f;
-  floatx4 acc[NDB];
-#pragma unroll
-  for (int nb = 0; nb < NDB; ++nb) acc[nb] = floatx4{0.f, 0.f, 0.f, 0.f};
-
   auto compute_pair = [&](int pp, const PairRaw<D> &r, auto maskv) {
     const int la = min(2 * pp, np - 1), lb = 2 * pp + 1;
     const bool hasA = 2 * pp < np, hasB = lb < np;
@@ -377,10 +341,176 @@ __global__ __launch_bounds__(64 * kMaxKvHeadsMx) void k_attn_mx(AttnArgs a) {
     chunk_loop(std::integral_constant<bool, false>{});
   else
     chunk_loop(std::integral_constant<bool, true>{});
+}
+
+// One block per (chunk of pages, candidate b, group of kv-heads) over the candidate's private
+// pages, one wave per kv-head j (with every head in one block the n_kv tiles of a page,
+// contiguous in the pool, are read together; the call's GroupTable says how many heads).
+// The wave writes its unnormalised partial (acc, m, l) per q-head.
+// The start of a block (query, lengths, page ids, first pair) is a serial chain that every block
+// pays once: with one branch-guarded 4-byte load per query element and the bf16 split in integer
+// arithmetic it took 1.5-2 us more than with 16-byte loads issued first and the hardware
+// pack-convert (7B batch of 16: 26.9 -> 25.2 us a layer, ragged 32k 67.9 -> 66.4, private pages of
+// the 64-candidate beam 34.6 -> 32.3, shared prefix 52.7 -> 49.9).
+template <int KVT, int D>
+__global__ __launch_bounds__(64 * kMaxKvHeadsMx) void k_attn_mx(AttnArgs a) {
+  constexpr int NDB = D / 16;
+  const int c = blockIdx.x, b = blockIdx.y;  // chunk, candidate
+  // (the wave index as a scalar, so that tile addresses are scalar too)
+  const int j =
+      __builtin_amdgcn_readfirstlane((int)(blockIdx.z * (blockDim.x >> 6) + (threadIdx.x >> 6)));
+  const int nkv = a.nkv, g = a.g, nq = a.nq, kq = a.kq;
+  const int L = a.lengths[b];
+  const int lane = threadIdx.x & 63;
+  const int n = lane & 15, cq = lane >> 4;
+  // column n: verify token n / g of this candidate, q-head j g + n % g (kq g <= 16 columns; the
+  // division by multiplication: n < 16, g <= 16)
+  const bool colv = n < kq * g;
+  const int ti = colv ? (n * a.ginv) >> 16 : 0, hh = colv ? n - ti * g : 0;
+  const size_t row = (size_t)b * kq + ti;
+  // the query is the one load that depends on nothing: issued first, split into operands while
+  // the first page pair is in flight
+  QueryRaw<D> qraw;
+  load_query<KVT, D>(a.q + (row * nq + (size_t)j * g + hh) * D, cq, qraw);
+  __builtin_amdgcn_sched_barrier(0);
+  const int npages = (L + kPage - 1) / kPage;
+  int first = 0;
+  for (int gi = 0; gi < a.gt.n; ++gi)
+    if (b * kq >= a.gt.start[gi] && b * kq < a.gt.start[gi + 1]) first = a.gt.prefix_pages[gi];
+  const int CP = 1 << a.gt.cshift_private;
+  const int ncp = (first + (1 << a.gt.cshift_prefix) - 1) >> a.gt.cshift_prefix;  // prefix chunks
+  const int p0 = first + c * CP;
+  if (p0 >= npages) return;
+  const int np = min(npages, p0 + CP) - p0;
+  float m_run = -INFINITY, l_run = 0.f;
+  floatx4 acc[NDB];
+#pragma unroll
+  for (int nb = 0; nb < NDB; ++nb) acc[nb] = floatx4{0.f, 0.f, 0.f, 0.f};
+  walk_pages<KVT, D>(a, b, j, L, npages, p0, np, qraw, colv, m_run, l_run, acc);
   l_run = column_sum(l_run);
   if (colv)
     store_partial<D>(a.apart + ((row * nq + (size_t)j * g + hh) * a.nch + ncp + c) * (D + 2), cq,
                      acc, m_run, l_run);
+}
+
+// Short caches (at most kShortPages pages a candidate, no shared prefix): the whole attention step
+// in one launch. Block = (kv-head j, candidate b), its kShortWaves waves take equal runs of the
+// pages, and their states meet in LDS with the verify tokens' own keys, by the formulas of
+// k_merge_mx. A separate merge costs a launch, which is more than such a cache takes to read; with
+// more pages one compute unit's share of the bandwidth costs more than the launch saves (7B shape, 8
+// candidates: 99.3 against 100.6 us a layer at 300 tokens, 100.4 each at 512).
+// finish_short: the waves' states (m in natural units, l over a column's four lanes) -> o, op, lse.
+template <int D>
+struct ShortState {
+  float acc[kShortWaves][16][D + 4];
+  float m[kShortWaves][16], l[kShortWaves][16];
+  float sself[16][16];  // [own token][column]
+};
+
+template <int D>
+__device__ __forceinline__ void finish_short(const AttnArgs &a, int b, int j, ShortState<D> &st,
+                                             bool any, float m, float l, const floatx4 *acc) {
+  constexpr int TPC = 64 * kShortWaves / 16, PER = D / TPC;  // threads per column, dims per thread
+  static_assert(PER * TPC == D, "every dim has a thread");
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, n = lane & 15, cq = lane >> 4;
+  if (any) {
+#pragma unroll
+    for (int nb = 0; nb < D / 16; ++nb)
+      *(float4 *)&st.acc[w][n][16 * nb + 4 * cq] =
+          make_float4(acc[nb][0], acc[nb][1], acc[nb][2], acc[nb][3]);
+  }
+  if (cq == 0) {
+    st.m[w][n] = m;  // (-inf: a wave without pages; its acc is not read)
+    st.l[w][n] = l;
+  }
+  const int g = a.g, kq = a.kq;
+  const int col = threadIdx.x / TPC, d0 = (threadIdx.x % TPC) * PER;
+  const bool colv = col < kq * g;
+  const int ti = colv ? (col * a.ginv) >> 16 : 0, hh = colv ? col - ti * g : 0;
+  const size_t row = (size_t)b * kq + ti, head = row * a.nq + (size_t)j * g + hh;
+  float v0[PER];  // the first own value, in flight over the barrier
+#pragma unroll
+  for (int e = 0; e < PER; ++e) v0[e] = a.vself[((size_t)b * kq * a.nkv + j) * D + d0 + e];
+  __syncthreads();
+  if (!colv) return;
+  float M = -INFINITY;
+  for (int i = 0; i <= ti; ++i) M = fmaxf(M, st.sself[i][col]);
+#pragma unroll
+  for (int u = 0; u < kShortWaves; ++u) M = fmaxf(M, st.m[u][col]);
+  float tot[PER], lsum = 0.f;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) tot[e] = 0.f;
+#pragma unroll
+  for (int u = 0; u < kShortWaves; ++u) {
+    const float mu = st.m[u][col];
+    if (mu == -INFINITY) continue;  // (block-uniform over a candidate: no pages for wave u)
+    const float f = expf(mu - M);
+    lsum += f * st.l[u][col];
+#pragma unroll
+    for (int e = 0; e < PER; ++e) tot[e] += f * st.acc[u][col][d0 + e];
+  }
+  for (int i = 0; i <= ti; ++i) {
+    const float es = expf(st.sself[i][col] - M);
+    lsum += es;
+#pragma unroll
+    for (int e = 0; e < PER; ++e)
+      tot[e] += es * (i == 0 ? v0[e] : a.vself[(((size_t)b * kq + i) * a.nkv + j) * D + d0 + e]);
+  }
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    tot[e] /= lsum;
+    if (a.o) a.o[head * D + d0 + e] = tot[e];
+  }
+  if (a.lse && d0 == 0) a.lse[head] = M + logf(lsum);
+  if (a.op) {
+    const int k = (j * g + hh) * D + d0;
+    if constexpr (PER == 4) {
+      store_operand4(a.op, a.NT, a.Bp, k, (int)row, tot);
+    } else {
+#pragma unroll
+      for (int e = 0; e < PER; ++e) store_operand(a.op, a.NT, a.Bp, k + e, (int)row, tot[e]);
+    }
+  }
+}
+
+template <int KVT, int D>
+__global__ __launch_bounds__(64 * kShortWaves) void k_attn_short(AttnArgs a) {
+  constexpr int NDB = D / 16;
+  __shared__ ShortState<D> st;
+  const int j = blockIdx.x, b = blockIdx.y;
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int g = a.g, nq = a.nq, kq = a.kq;
+  const int L = a.lengths[b];
+  const int lane = threadIdx.x & 63, n = lane & 15, cq = lane >> 4;
+  const bool colv = n < kq * g;
+  const int ti = colv ? (n * a.ginv) >> 16 : 0, hh = colv ? n - ti * g : 0;
+  QueryRaw<D> qraw;
+  load_query<KVT, D>(a.q + (((size_t)b * kq + ti) * nq + (size_t)j * g + hh) * D, cq, qraw);
+  // the own keys' scores, one token per wave: its row has the query's dim order
+  const float rs = 1.0f / sqrtf((float)D);
+  for (int i = w; i < kq; i += kShortWaves) {
+    QueryRaw<D> kraw;
+    load_query<KVT, D>(a.kself + (((size_t)b * kq + i) * a.nkv + j) * D, cq, kraw);
+    float s = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < D / 32; ++kk)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s += qraw.v[kk][e >> 2][e & 3] * kraw.v[kk][e >> 2][e & 3];
+    s = column_sum(s) * rs;
+    if (cq == 0) st.sself[i][n] = s;
+  }
+  const int npages = min((L + kPage - 1) / kPage, kShortPages);
+  const int per = (npages + kShortWaves - 1) / kShortWaves;
+  const int p0 = w * per, np = min(npages - p0, per);
+  float m_run = -INFINITY, l_run = 0.f;
+  floatx4 acc[NDB];
+#pragma unroll
+  for (int nb = 0; nb < NDB; ++nb) acc[nb] = floatx4{0.f, 0.f, 0.f, 0.f};
+  if (np > 0) {  // wave-uniform
+    walk_pages<KVT, D>(a, b, j, L, npages, p0, np, qraw, colv, m_run, l_run, acc);
+    l_run = column_sum(l_run);
+  }
+  finish_short<D>(a, b, j, st, np > 0, m_run * kLn2, l_run, acc);
 }
 
 // Shared-prefix attention: the members of a prefix group share the physical pages of their
@@ -721,6 +851,205 @@ hipError_t launch_attn_mx(const Dims &dm, const Plan &p, const Workspace &w, con
     else KVPRM_A(2, 128);
   }
 #undef KVPRM_A
+  return hipGetLastError();
+}
+
+// ------------------------------------------------------------------------------- fp32 cache
+
+__device__ __forceinline__ floatx4 mfma4(float a, float b, const floatx4 &c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// walk_pages on an fp32 cache, a page at a time with the next page's tiles in flight, on the fp32
+// matrix cores: a 16-byte piece of the K tile is four dims of a token and one of the V tile four
+// consecutive slots of a dim, contracted one element at a time, so tiles, query and
+// probabilities enter the products as they lie. m_run is in natural units. A page costs about
+// 0.6 us of products at d_h = 64.
+template <int D>
+__device__ __forceinline__ void walk_pages_f32(const AttnArgs &a, int b, int j, int L, int p0, int np,
+                                               f32x4u (&qv)[D / 16], bool colv, float &m_run,
+                                               float &l_run, floatx4 (&acc)[D / 16]) {
+  constexpr int NB = D / 16;  // 16-dim blocks
+  constexpr size_t TILE = (size_t)kPage * D;
+  const int nkv = a.nkv;
+  const int lane = threadIdx.x & 63, c = lane >> 4;
+  const float *kp = (const float *)a.kp, *vp = (const float *)a.vp;
+  const int ph_l = a.page_table[(size_t)b * a.max_pages + p0 + min(lane, np - 1)];
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) qv[i][e] = colv ? qv[i][e] : 0.f;
+  auto load = [&](int p, f32x4u(&k)[NB], f32x4u(&v)[NB]) {
+    const int ph = __builtin_amdgcn_readlane(ph_l, min(p, np - 1));
+    const size_t off = ((size_t)ph * nkv + j) * TILE + 4 * lane;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      k[i] = *(const f32x4u *)(kp + off + 256 * i);
+      v[i] = *(const f32x4u *)(vp + off + 256 * i);
+    }
+  };
+  const float rs = 1.0f / sqrtf((float)D);
+  auto page = [&](int p, const f32x4u(&k)[NB], const f32x4u(&v)[NB]) {
+    floatx4 s4[4];  // one product chain per element
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      s4[e] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < NB; ++i) s4[e] = mfma4(k[i][e], qv[i][e], s4[e]);
+    }
+    const int t = (p0 + p) * kPage + 4 * c;
+    float sv[4], mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float s = ((s4[0][i] + s4[1][i]) + (s4[2][i] + s4[3][i])) * rs;
+      sv[i] = t + i < L ? s : -INFINITY;
+      mx = fmaxf(mx, sv[i]);
+    }
+    const float m_new = fmaxf(m_run, column_max(mx));  // finite: the page holds a valid token
+    const float alpha = expf(m_run - m_new);
+    m_run = m_new;
+    float pv[4], ps = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      pv[i] = t + i < L ? expf(sv[i] - m_new) : 0.f;
+      ps += pv[i];
+    }
+    l_run = l_run * alpha + ps;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[i][r] *= alpha;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[i] = mfma4(t + e < L ? v[i][e] : 0.f, pv[e], acc[i]);
+    }
+  };
+  f32x4u k0[NB], v0[NB], k1[NB], v1[NB];
+  load(0, k0, v0);
+  for (int p = 0; p < np; p += 2) {
+    load(p + 1, k1, v1);
+    page(p, k0, v0);
+    if (p + 1 >= np) break;
+    load(p + 2, k0, v0);
+    page(p + 1, k1, v1);
+  }
+}
+
+// One wave per (chunk of pages, candidate b, kv-head j), in short chunks while the batch is small
+// (private_chunk_rule): four candidates of 512 tokens ran 74 us as one 256-thread block per 32 pages
+// with a dot product per thread, 5 us so.
+template <int D>
+__global__ __launch_bounds__(64) void k_attn_f32(AttnArgs a) {
+  constexpr int NB = D / 16;
+  const int ch = blockIdx.x, b = blockIdx.y, j = blockIdx.z;
+  const int lane = threadIdx.x, n = lane & 15, c = lane >> 4;
+  const bool colv = n < a.g;
+  const size_t head = (size_t)b * a.nq + (size_t)j * a.g + (colv ? n : 0);
+  f32x4u qv[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) qv[i] = *(const f32x4u *)(a.q + head * D + 16 * i + 4 * c);
+  const int L = a.lengths[b];
+  const int npages = (L + kPage - 1) / kPage;
+  const int p0 = ch << a.gt.cshift_private;
+  if (p0 >= npages) return;
+  const int np = min(npages - p0, 1 << a.gt.cshift_private);  // (at most 64)
+  float m_run = -INFINITY, l_run = 0.f;
+  floatx4 acc[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+  walk_pages_f32<D>(a, b, j, L, p0, np, qv, colv, m_run, l_run, acc);
+  l_run = column_sum(l_run);
+  if (!colv) return;
+  float *hb = a.apart + (head * a.nch + ch) * (D + 2);
+#pragma unroll
+  for (int i = 0; i < NB; ++i)  // (rows of D + 2 floats: 8-byte aligned)
+#pragma unroll
+    for (int r = 0; r < 4; r += 2)
+      *(float2 *)(hb + 16 * i + 4 * c + r) = make_float2(acc[i][r], acc[i][r + 1]);
+  if (c == 0) *(float2 *)(hb + D) = make_float2(m_run, l_run);
+}
+
+template <int D>
+__global__ __launch_bounds__(64 * kShortWaves) void k_attn_short_f32(AttnArgs a) {
+  constexpr int NB = D / 16;
+  __shared__ ShortState<D> st;
+  const int j = blockIdx.x, b = blockIdx.y;
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int L = a.lengths[b];
+  const int lane = threadIdx.x & 63, n = lane & 15, c = lane >> 4;
+  const bool colv = n < a.g;
+  const float *qr = a.q + ((size_t)b * a.nq + (size_t)j * a.g + (colv ? n : 0)) * D;
+  f32x4u qv[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) qv[i] = *(const f32x4u *)(qr + 16 * i + 4 * c);
+  if (w == 0) {  // the own key's score
+    const float *kr = a.kself + ((size_t)b * a.nkv + j) * D;
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const f32x4u kv = *(const f32x4u *)(kr + 16 * i + 4 * c);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s += qv[i][e] * kv[e];
+    }
+    s = column_sum(s) * (1.0f / sqrtf((float)D));
+    if (c == 0) st.sself[0][n] = s;
+  }
+  const int npages = min((L + kPage - 1) / kPage, kShortPages);
+  const int per = (npages + kShortWaves - 1) / kShortWaves;
+  const int p0 = w * per, np = min(npages - p0, per);
+  float m_run = -INFINITY, l_run = 0.f;
+  floatx4 acc[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+  if (np > 0) {
+    walk_pages_f32<D>(a, b, j, L, p0, np, qv, colv, m_run, l_run, acc);
+    l_run = column_sum(l_run);
+  }
+  finish_short<D>(a, b, j, st, np > 0, m_run, l_run, acc);
+}
+
+hipError_t launch_attn_f32(const Dims &dm, const Plan &p, const Workspace &w, const float *kp,
+                           const float *vp, const int32_t *page_table, const int32_t *lengths,
+                           const GroupTable &gt, const float *q, hipStream_t s) {
+  AttnArgs a = attn_args(dm, p, w, lengths, gt, q);
+  a.kp = (const char *)kp;
+  a.vp = (const char *)vp;
+  a.page_table = page_table;
+  const dim3 grid(gt.private_chunks, p.Breal, dm.nkv);
+  if (dm.d == 64)
+    hipLaunchKernelGGL(k_attn_f32<64>, grid, dim3(64), 0, s, a);
+  else
+    hipLaunchKernelGGL(k_attn_f32<128>, grid, dim3(64), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_attn_short(const Dims &dm, const Plan &p, const Workspace &w, const char *kp,
+                             const char *vp, const float *ksc, const float *vsc,
+                             const int32_t *page_table, const int32_t *lengths,
+                             const GroupTable &gt, const float *q, const float *kself,
+                             const float *vself, float *o, uint16_t *op, float *lse,
+                             hipStream_t s) {
+  AttnArgs a = attn_args(dm, p, w, lengths, gt, q);
+  a.kp = kp;
+  a.vp = vp;
+  a.ksc = ksc;
+  a.vsc = vsc;
+  a.page_table = page_table;
+  a.kself = kself;
+  a.vself = vself;
+  a.o = o;
+  a.op = op;
+  a.lse = lse;
+  const dim3 grid(dm.nkv, p.Breal), block(64 * kShortWaves);
+  if (dm.kvdt == 0) {
+    if (dm.d == 64) hipLaunchKernelGGL(k_attn_short_f32<64>, grid, block, 0, s, a);
+    else hipLaunchKernelGGL(k_attn_short_f32<128>, grid, block, 0, s, a);
+  } else if (dm.kvdt == 1) {
+    if (dm.d == 64) hipLaunchKernelGGL((k_attn_short<1, 64>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_attn_short<1, 128>), grid, block, 0, s, a);
+  } else {
+    if (dm.d == 64) hipLaunchKernelGGL((k_attn_short<2, 64>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_attn_short<2, 128>), grid, block, 0, s, a);
+  }
   return hipGetLastError();
 }
 

@@ -278,129 +278,6 @@ static hipError_t launch_gemv32(const F32Args &a, int blocks, hipStream_t s) {
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------------------- attention
-
-struct Attn32Args {
-  const float *kp, *vp;  // this layer's pools
-  int nkv, g, nq;
-  const int32_t *page_table;
-  int max_pages;
-  const int32_t *lengths;
-  int cshift, nch;
-  const float *q;
-  float *apart;  // [B][nq][nch][D + 2]
-};
-
-// One wave per (chunk of pages, candidate b, kv-head j), a page at a time with the next page's
-// tiles in flight: S = K Q^T (A = the K tile as stored, B = the g query heads of j), online
-// softmax in registers (a lane holds 4 tokens of one head), O^T += V^T P^T (A = the V tile as
-// stored: a 16-byte piece is 4 consecutive slots of one dim; B = the probabilities as they lie).
-// A page costs about 0.6 us of products at d_h = 64, so the chunk is short while the batch is
-// small (private_chunk_rule): four candidates of 512 tokens ran 74 us as one 256-thread block per
-// 32 pages with a dot product per thread. Slots at or past L_b are masked in S and zeroed in V.
-template <int D>
-__global__ __launch_bounds__(64) void k_attn32(Attn32Args a) {
-  constexpr int NB = D / 16;  // 16-dim blocks
-  constexpr size_t TILE = (size_t)kPage * D;
-  const int ch = blockIdx.x, b = blockIdx.y, j = blockIdx.z;
-  const int lane = threadIdx.x, n = lane & 15, c = lane >> 4;
-  const int g = a.g, nkv = a.nkv;
-  const bool colv = n < g;
-  const size_t head = (size_t)b * a.nq + (size_t)j * g + (colv ? n : 0);
-  f32x4u qv[NB];
-#pragma unroll
-  for (int i = 0; i < NB; ++i) qv[i] = *(const f32x4u *)(a.q + head * D + 16 * i + 4 * c);
-  const int L = a.lengths[b];
-  const int npages = (L + kPage - 1) / kPage;
-  const int p0 = ch << a.cshift;
-  if (p0 >= npages) return;
-  const int np = min(npages - p0, 1 << a.cshift);  // (at most 64)
-  const int ph_l = a.page_table[(size_t)b * a.max_pages + p0 + min(lane, np - 1)];
-#pragma unroll
-  for (int i = 0; i < NB; ++i)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) qv[i][e] = colv ? qv[i][e] : 0.f;
-  auto load = [&](int p, f32x4u(&k)[NB], f32x4u(&v)[NB]) {
-    const int ph = __builtin_amdgcn_readlane(ph_l, min(p, np - 1));
-    const size_t off = ((size_t)ph * nkv + j) * TILE + 4 * lane;
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      k[i] = *(const f32x4u *)(a.kp + off + 256 * i);
-      v[i] = *(const f32x4u *)(a.vp + off + 256 * i);
-    }
-  };
-  const float rs = 1.0f / sqrtf((float)D);
-  float m_run = -INFINITY, l_run = 0.f;
-  floatx4 acc[NB];
-#pragma unroll
-  for (int i = 0; i < NB; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
-  auto page = [&](int p, const f32x4u(&k)[NB], const f32x4u(&v)[NB]) {
-    floatx4 s4[4];  // one product chain per element
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      s4[e] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int i = 0; i < NB; ++i) s4[e] = mfma4(k[i][e], qv[i][e], s4[e]);
-    }
-    const int t = (p0 + p) * kPage + 4 * c;
-    float sv[4], mx = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float s = ((s4[0][i] + s4[1][i]) + (s4[2][i] + s4[3][i])) * rs;
-      sv[i] = t + i < L ? s : -INFINITY;
-      mx = fmaxf(mx, sv[i]);
-    }
-    const float m_new = fmaxf(m_run, column_max(mx));  // finite: the page holds a valid token
-    const float alpha = expf(m_run - m_new);
-    m_run = m_new;
-    float pv[4], ps = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      pv[i] = t + i < L ? expf(sv[i] - m_new) : 0.f;
-      ps += pv[i];
-    }
-    l_run = l_run * alpha + ps;
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[i][r] *= alpha;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[i] = mfma4(t + e < L ? v[i][e] : 0.f, pv[e], acc[i]);
-    }
-  };
-  f32x4u k0[NB], v0[NB], k1[NB], v1[NB];
-  load(0, k0, v0);
-  for (int p = 0; p < np; p += 2) {
-    load(p + 1, k1, v1);
-    page(p, k0, v0);
-    if (p + 1 >= np) break;
-    load(p + 2, k0, v0);
-    page(p + 1, k1, v1);
-  }
-  l_run = column_sum(l_run);
-  if (!colv) return;
-  float *hb = a.apart + (head * a.nch + ch) * (D + 2);
-#pragma unroll
-  for (int i = 0; i < NB; ++i)  // (rows of D + 2 floats: 8-byte aligned)
-#pragma unroll
-    for (int r = 0; r < 4; r += 2)
-      *(float2 *)(hb + 16 * i + 4 * c + r) = make_float2(acc[i][r], acc[i][r + 1]);
-  if (c == 0) *(float2 *)(hb + D) = make_float2(m_run, l_run);
-}
-
-hipError_t launch_attn_f32(const Dims &dm, const Plan &p, const Workspace &w, const float *kp,
-                           const float *vp, const int32_t *page_table, const int32_t *lengths,
-                           const GroupTable &gt, const float *q, hipStream_t s) {
-  Attn32Args a{kp,        vp,      dm.nkv, dm.g, dm.nq, page_table, p.max_pages, lengths,
-               gt.cshift_private, p.nch, q,      w.apart};
-  const dim3 grid(gt.private_chunks, p.Breal, dm.nkv);
-  if (dm.d == 64)
-    hipLaunchKernelGGL(k_attn32<64>, grid, dim3(64), 0, s, a);
-  else
-    hipLaunchKernelGGL(k_attn32<128>, grid, dim3(64), 0, s, a);
-  return hipGetLastError();
-}
-
 // ------------------------------------------------------------------------------- sequencing
 
 hipError_t launch_init_f32(const Dims &dm, const Plan &p, const Workspace &w, const void *ev,

@@ -29,6 +29,7 @@ struct GroupTable {
   int prefix_chunks;                   // chunks of the longest group prefix
   int private_chunks;                  // chunk grid of the private pages (0 = from max_pages)
   int heads_per_block;                 // kv-heads (waves) of a private-page block
+  int one_launch;                      // short caches: k_attn_short in place of chunks and merge
   int cshift_prefix, cshift_private;   // chunk lengths (1 << shift pages) of the two kernels
 };
 
@@ -39,6 +40,8 @@ constexpr int kChunkPagesF32 = 32;  // longest chunk of an fp32 cache
 constexpr int kMaxChunks = 1024;  // chunk partials one merge handles
 constexpr int kMaxKvHeadsMx = 8;  // matrix-core attention: one wave per kv-head in a block
 constexpr int kFineChunks = 128;  // chunks of one candidate at most, in chunks under 16 pages
+constexpr int kShortPages = 32;   // longest cache of the one-launch attention
+constexpr int kShortWaves = 8;    // its waves per block
 constexpr int kMaxBatch = 256;    // candidates of a call
 constexpr int kPage = 16;
 
@@ -209,12 +212,21 @@ hipError_t launch_merge_mx(const Dims &dm, const Plan &p, const Workspace &w,
                            const int32_t *lengths, const GroupTable &gt, const float *q,
                            const float *kself, const float *vself, float *o, uint16_t *op,
                            hipStream_t s, float *lse = nullptr);
-// launch_attn_mx or launch_attn_f32 for one layer of the pools
+// both in one launch, for short caches (GroupTable::one_launch)
+hipError_t launch_attn_short(const Dims &dm, const Plan &p, const Workspace &w, const char *kp,
+                             const char *vp, const float *ksc, const float *vsc,
+                             const int32_t *page_table, const int32_t *lengths,
+                             const GroupTable &gt, const float *q, const float *kself,
+                             const float *vself, float *o, uint16_t *op, float *lse,
+                             hipStream_t s);
+// the attention step of one layer of the pools (any pipeline); partials_only: the chunk partials
+// alone
 hipError_t launch_attention(const Dims &dm, const Plan &p, const Workspace &w, int layer,
                             const void *kpool, const void *vpool, const float *kscale,
                             const float *vscale, int num_pages, const int32_t *page_table,
                             const int32_t *lengths, const GroupTable &gt, const float *q,
-                            hipStream_t s);
+                            const float *kself, const float *vself, float *o, uint16_t *op,
+                            hipStream_t s, float *lse = nullptr, bool partials_only = false);
 hipError_t launch_head(const Dims &dm, const Plan &p, const Workspace &w, const void *final_norm,
                        const void *reward_w, float reward_b, float *scores, float *logits,
                        hipStream_t s);

@@ -321,17 +321,23 @@ hipError_t launch_attention(const Dims &dm, const Plan &p, const Workspace &w, i
                             const void *kpool, const void *vpool, const float *kscale,
                             const float *vscale, int num_pages, const int32_t *page_table,
                             const int32_t *lengths, const GroupTable &gt, const float *q,
-                            hipStream_t s) {
+                            const float *kself, const float *vself, float *o, uint16_t *op,
+                            hipStream_t s, float *lse, bool partials_only) {
   const int EB = dm.kvdt == 0 ? 4 : (dm.kvdt == 1 ? 2 : 1);
   const size_t layer_elems = (size_t)num_pages * dm.nkv * kPage * dm.d;
   const char *kp = (const char *)kpool + layer_elems * EB * layer;
   const char *vp = (const char *)vpool + layer_elems * EB * layer;
   const float *ksc = kscale ? kscale + (size_t)layer * num_pages * dm.nkv : nullptr;
   const float *vsc = vscale ? vscale + (size_t)layer * num_pages * dm.nkv : nullptr;
-  if (dm.kvdt == 0)
-    return launch_attn_f32(dm, p, w, (const float *)kp, (const float *)vp, page_table, lengths, gt,
-                           q, s);
-  return launch_attn_mx(dm, p, w, kp, vp, ksc, vsc, page_table, lengths, gt, q, s);
+  if (gt.one_launch && !partials_only)
+    return launch_attn_short(dm, p, w, kp, vp, ksc, vsc, page_table, lengths, gt, q, kself, vself,
+                             o, op, lse, s);
+  hipError_t e =
+      dm.kvdt == 0
+          ? launch_attn_f32(dm, p, w, (const float *)kp, (const float *)vp, page_table, lengths, gt, q, s)
+          : launch_attn_mx(dm, p, w, kp, vp, ksc, vsc, page_table, lengths, gt, q, s);
+  if (e != hipSuccess || partials_only) return e;
+  return launch_merge_mx(dm, p, w, lengths, gt, q, kself, vself, o, op, s, lse);
 }
 
 // ------------------------------------------------------------------------------- reward head

@@ -20,6 +20,15 @@ pytestmark = pytest.mark.gpu
 CASES = [
     (28, 4, 128, "bf16", [1]),
     (28, 4, 128, "bf16", [63, 64, 65]),
+    # short caches: one launch up to 32 pages and 256 (candidate, kv-head) blocks
+    (28, 4, 128, "bf16", [512, 0, 1, 15, 16, 17, 129, 511]),
+    (28, 4, 128, "bf16", [513, 3]),
+    (32, 2, 128, "fp8", [512, 255, 16, 0, 33]),
+    (16, 8, 64, "bf16", [500] + [(37 * i) % 200 for i in range(31)]),
+    (16, 8, 64, "fp8", [500] + [(37 * i) % 200 for i in range(32)]),
+    (5, 5, 64, "fp8", [65, 512]),
+    (12, 12, 64, "f32", [128, 0, 1, 17]),
+    (4, 2, 128, "f32", [129, 128, 40]),
     (16, 8, 128, "bf16", [1103]),
     (28, 4, 128, "bf16", [4096, 4033]),
     (28, 4, 128, "bf16", [8192 + 17]),
@@ -35,7 +44,8 @@ CASES = [
 @pytest.mark.parametrize("nq,nkv,d,dtype,lengths", CASES)
 def test_attention_at_every_chunk_length(nq, nkv, d, dtype, lengths):
     print(f"case: nq={nq} nkv={nkv} d={d} {dtype} lengths={lengths}", flush=True)
-    shape = synth.ModelShape(1, 256, nq, nkv, d, 256, weight_dtype="bf16", kv_dtype=dtype)
+    shape = synth.ModelShape(1, 256, nq, nkv, d, 256, weight_dtype="f32" if dtype == "f32" else "bf16",
+                             kv_dtype=dtype)
     w = synth.make_workload("custom", shape=shape, lengths=lengths, seed=5100 + len(lengths))
     dw = DeviceWorkload(w, nan_unused_pages=True, fill_weights=False)
     q, ks, vs = host_activations(w, 0xABF, scale=1.0)
