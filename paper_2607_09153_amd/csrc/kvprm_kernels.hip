@@ -413,42 +413,59 @@ hipError_t launch_head(const Dims &dm, const Plan &p, const Workspace &w, const 
 
 // ------------------------------------------------------------------------------- cache packing
 
+// 16 bytes that a call reads or writes once: non-temporal
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint4 ld_once(const uint4 *p) {
+  return __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4 *)p));
+}
+__device__ __forceinline__ void st_once(uint4 *p, const uint4 &v) {
+  __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), (u32x4 *)p);
+}
+
 // Token-major cache tiles ([page_size][d] values, slot-major) -> the stored K or V tile layout.
-// One block per tile (grid-stride over tiles): the tile is read into LDS with 16-byte loads,
-// then every thread assembles 16-byte output groups in output order and stores them, so both
-// the reads and the writes are contiguous. EB = element bytes; x = 16 / EB values per group.
+// One block per 4 KiB of tiles, or per tile where that is larger (grid-stride): the tiles are read
+// into LDS with 16-byte loads, then every thread assembles 16-byte output groups in output order
+// and stores them, so both the reads and the writes are contiguous and a small tile (1 KiB: fp8,
+// d_h = 64) leaves no thread of the block without work. EB = element bytes; x = 16 / EB values per group.
 //   K group (m / x) * 16 + s holds dims m .. m + x - 1 of slot s (a contiguous source run);
 //   V group ((m / (16 r)) * 4 + s / 4) * 16 + m % 16 holds slots 4 (s / 4) .. + 3 of the r dims
 //   m % 16 + 16 i (i < r) of the 16 r-dim block, as [i][slot % 4] (r = x / 4).
-template <int EB, bool V>
+template <int EB, bool V, bool ONCE>
 __global__ __launch_bounds__(256) void k_pack_kv(const uint4 *__restrict__ src, uint4 *__restrict__ dst,
                                                  int64_t ntiles, int d) {
   extern __shared__ uint4 tile_s[];
   constexpr int X = 16 / EB, R = X / 4;
-  const int groups = 16 * d / X;  // 16-byte groups per tile
-  const unsigned char *tb = (const unsigned char *)tile_s;
-  for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    const uint4 *sp = src + t * groups;
-    for (int i = threadIdx.x; i < groups; i += 256) tile_s[i] = sp[i];
+  const int groups = d * EB;  // 16-byte groups per tile (64 to 512, a power of two)
+  const int per = groups < 256 ? 256 / groups : 1;  // tiles at a time
+  for (int64_t t0 = (int64_t)blockIdx.x * per; t0 < ntiles; t0 += (int64_t)gridDim.x * per) {
+    const int n = (int)(ntiles - t0 < per ? ntiles - t0 : per) * groups;
+    const uint4 *sp = src + t0 * groups;
+    for (int i = threadIdx.x; i < n; i += 256) tile_s[i] = ONCE ? ld_once(sp + i) : sp[i];
     __syncthreads();
-    for (int gi = threadIdx.x; gi < groups; gi += 256) {
+    for (int i = threadIdx.x; i < n; i += 256) {
+      const int gi = i & (groups - 1);
+      const uint4 *ts = tile_s + (i - gi);
       uint4 out;
       if (!V) {
         const int s = gi & 15, mb = gi >> 4;  // slot, x-dim block
-        out = tile_s[s * (d / X) + mb];
+        out = ts[s * (d / X) + mb];
       } else {
+        const unsigned char *tb = (const unsigned char *)ts;
         const int mm = gi & 15, sq = (gi >> 4) & 3, blk = gi >> 6;
         unsigned char *ob = (unsigned char *)&out;
 #pragma unroll
-        for (int i = 0; i < R; ++i)
+        for (int q = 0; q < R; ++q)
 #pragma unroll
           for (int k = 0; k < 4; ++k) {
-            const int m = blk * 16 * R + i * 16 + mm, sl = 4 * sq + k;
+            const int m = blk * 16 * R + q * 16 + mm, sl = 4 * sq + k;
 #pragma unroll
-            for (int e = 0; e < EB; ++e) ob[(i * 4 + k) * EB + e] = tb[(sl * d + m) * EB + e];
+            for (int e = 0; e < EB; ++e) ob[(q * 4 + k) * EB + e] = tb[(sl * d + m) * EB + e];
           }
       }
-      dst[t * groups + gi] = out;
+      if (ONCE)
+        st_once(dst + t0 * groups + i, out);
+      else
+        dst[t0 * groups + i] = out;
     }
     __syncthreads();
   }
@@ -456,14 +473,27 @@ __global__ __launch_bounds__(256) void k_pack_kv(const uint4 *__restrict__ src, 
 
 hipError_t launch_pack_kv(const void *src, void *dst, int64_t ntiles, int d, int eb, bool v,
                           hipStream_t s) {
-  const size_t lds = (size_t)16 * d * eb;
-  int64_t blocks = ntiles < 65536 ? ntiles : 65536;
+  const int groups = d * eb, per = groups < 256 ? 256 / groups : 1;
+  const size_t lds = (size_t)16 * groups * per;
+  int64_t blocks = (ntiles + per - 1) / per;
+  blocks = blocks < 65536 ? blocks : 65536;
   const dim3 grid((unsigned)blocks), block(256);
   const uint4 *a = (const uint4 *)src;
   uint4 *b = (uint4 *)dst;
-#define KVPRM_PK(E_)                                                                    \
-  if (v) hipLaunchKernelGGL((k_pack_kv<E_, true>), grid, block, lds, s, a, b, ntiles, d); \
-  else hipLaunchKernelGGL((k_pack_kv<E_, false>), grid, block, lds, s, a, b, ntiles, d)
+  // Non-temporal from 128 MiB read and written: keys and values together then exceed the 256 MiB
+  // memory-side cache, and leaving it alone is faster (28 layers of 8192 tokens at the 7B shape:
+  // 194 -> 185 us for both parts); below, the packed tiles stay there for their first reader (4 layers
+  // of 4000 fp32 tokens, 164 MB in all: 26.1 us plain, 29.6 non-temporal).
+  const bool once = ntiles * (int64_t)groups * 32 >= (int64_t)128 << 20;
+#define KVPRM_PK2(E_, V_)                                                                              \
+  if (once) hipLaunchKernelGGL((k_pack_kv<E_, V_, true>), grid, block, lds, s, a, b, ntiles, d);        \
+  else hipLaunchKernelGGL((k_pack_kv<E_, V_, false>), grid, block, lds, s, a, b, ntiles, d)
+#define KVPRM_PK(E_)          \
+  if (v) {                    \
+    KVPRM_PK2(E_, true);      \
+  } else {                    \
+    KVPRM_PK2(E_, false);     \
+  }
   switch (eb) {
     case 4: KVPRM_PK(4); break;
     case 2: KVPRM_PK(2); break;
@@ -471,6 +501,7 @@ hipError_t launch_pack_kv(const void *src, void *dst, int64_t ntiles, int d, int
     default: return hipErrorInvalidValue;
   }
 #undef KVPRM_PK
+#undef KVPRM_PK2
   return hipGetLastError();
 }
 
