@@ -29,7 +29,8 @@
 // Activation operand of a GEMV ("operand buffer"): for k-block kb (32 inputs), column tile t
 // and lane, 8 bf16 = inputs 32 kb + 8 (lane / 16) + i of column 16 t + lane % 16. Columns: with
 // Bp == 8 (batch <= 8, one tile) columns 0..7 hold the hi halves and 8..15 the lo halves of
-// candidates 0..7; otherwise columns [0, Bp) are hi and [Bp, 2 Bp) lo (Bp = batch rounded up
+// candidates 0..7; with Bp == 4 (batch <= 4) columns 0..3, 4..7 and 8..11 hold the first, second
+// and third bf16 terms of candidates 0..3; otherwise columns [0, Bp) are hi and [Bp, 2 Bp) lo (Bp = batch rounded up
 // to 16). Columns of absent candidates only ever reach outputs that are discarded.
 #include <math.h>
 #include <string.h>
@@ -45,7 +46,7 @@ int gemv_nt(int B) { return B <= 8 ? 1 : 2 * ((B + 15) / 16); }
 // row tiles per wave of the split-K GEMV: two (sharing each operand load) for several operand
 // column tiles and many rows; one otherwise (more waves for the short projections)
 int gemv_mt(int nt, int rows) { return nt >= 2 && rows >= 8192 ? 2 : 1; }
-int gemv_bp(int B) { return B <= 8 ? 8 : 16 * ((B + 15) / 16); }
+int gemv_bp(int B) { return B <= 4 ? 4 : B <= 8 ? 8 : 16 * ((B + 15) / 16); }
 
 // ------------------------------------------------------------------------------- init
 
@@ -92,7 +93,7 @@ struct GemvArgs {
   int nseg;
   int rows, K, kslice, ksplit;
   const uint4 *act;  // operand buffer of the input
-  int B;
+  int B, Bp;
   float *part;  // [rows][B][ksp] k-partials, ksp = ksplit rounded up to 4
   int ksp;
 };
@@ -196,7 +197,7 @@ __global__ __launch_bounds__(64 * WPB) void k_gemv_mx(GemvArgs a) {
     if (NT == 1) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float v = acc[m][0][i] + __shfl_xor(acc[m][0][i], 8, 64);
+        const float v = sum_terms(acc[m][0][i], a.Bp);
         if (n < 8 && n < B) a.part[((size_t)(rbase + i) * B + n) * a.ksp + ks] = v;
       }
     } else {
@@ -509,7 +510,7 @@ __global__ __launch_bounds__(64 * WPB) void k_gemv_fused(FusedArgs a) {
       floatx4 v;
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        v[i] = NT == 1 ? acc[m][0][i] + __shfl_xor(acc[m][0][i], 8, 64)
+        v[i] = NT == 1 ? sum_terms(acc[m][0][i], a.Bp)
                        : acc[m][gi][i] + acc[m][gi + NG][i];
       red_s[wave][m][gi][lane] = v;
     }
@@ -712,7 +713,7 @@ __global__ __launch_bounds__(64 * WPB, 4) void k_gateup_wide(FusedArgs a) {
   for (int gi = 0; gi < NG; ++gi)
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      hl[gi][i] = NT == 1 ? acc[0][i] + __shfl_xor(acc[0][i], 8, 64) : acc[gi][i] + acc[gi + NG][i];
+      hl[gi][i] = NT == 1 ? sum_terms(acc[0][i], a.Bp) : acc[gi][i] + acc[gi + NG][i];
   if (up) {
 #pragma unroll
     for (int gi = 0; gi < NG; ++gi)
@@ -894,7 +895,7 @@ struct SplitArgs {
   int rows, nkb;     // row count (all segments), input blocks of 32
   int kb_per;        // input blocks per slice (a multiple of U)
   const uint4 *act;  // operand [K / 32][NT][64]
-  int B;
+  int B, Bp;
   float *part;       // [ksplit (+ 1 with an adapter)][B][rows]
   // adapter tail (tkb > 0): slice ksplit (the grid's last) runs the tkb input blocks of the
   // segments' B factors (packed [rows_i][32 tkb], null = no adapter) against operand slot i of
@@ -999,7 +1000,7 @@ __global__ __launch_bounds__(64 * WPB) void k_resid_split(SplitArgs a) {
     float hl[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      hl[i] = NT == 1 ? acc[0][i] + __shfl_xor(acc[0][i], 8, 64) : acc[gi][i] + acc[gi + NG][i];
+      hl[i] = NT == 1 ? sum_terms(acc[0][i], a.Bp) : acc[gi][i] + acc[gi + NG][i];
     const int cand = NT == 1 ? n : 16 * gi + n;
     if (cand >= a.B || (NT == 1 && n >= 8)) continue;
     *(float4 *)(a.part + ((size_t)ks * a.B + cand) * a.rows + tile * 16 + 4 * cq) =
@@ -1136,6 +1137,7 @@ static hipError_t launch_gemv_mx(const Plan &p, const GemvPlan &gp, const void *
   a.ksplit = gp.ksplit;
   a.act = (const uint4 *)act;
   a.B = p.B;
+  a.Bp = p.bp;
   a.part = part;
   a.ksp = (gp.ksplit + 3) & ~3;
   const int mt = gemv_mt(p.nt, gp.rows);
@@ -1404,6 +1406,7 @@ static hipError_t launch_split(const Plan &p, const Workspace &w, const GemvPlan
   a.kb_per = g.kslice / 32;
   a.act = (const uint4 *)act;
   a.B = p.B;
+  a.Bp = p.bp;
   a.part = w.part;
   a.ksplit = g.ksplit;
   for (int i = 0; i < 3; ++i) a.tw[i] = tail.b[i];

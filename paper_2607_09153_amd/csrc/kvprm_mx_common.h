@@ -3,6 +3,8 @@
 // splitting of fp32 operands, the operand-buffer store and wave/block reductions.
 #pragma once
 
+#include <type_traits>
+
 #include "kvprm_internal.h"
 
 namespace kvprm {
@@ -24,20 +26,6 @@ __device__ __forceinline__ floatx4 mfma16(const uint4 &a, const uint4 &b, const 
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
                                                  __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
-
-// round-to-nearest-even fp32 -> bf16 bits (finite inputs)
-__device__ __forceinline__ uint32_t bf16_rne(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return u >> 16;
-}
-
-__device__ __forceinline__ void split_hi_lo(float x, uint32_t &hi, uint32_t &lo) {
-  hi = bf16_rne(x);
-  lo = bf16_rne(x - __uint_as_float(hi << 16));
-}
-
-__device__ __forceinline__ uint32_t pack2(uint32_t a, uint32_t b) { return a | (b << 16); }
 
 // Two fp32 values -> packed bf16 pairs hi (RNE) and lo = RNE(x - hi) (the hardware pack-convert,
 // one instruction per pair): hi + lo carries 16 significant bits of each value.
@@ -68,29 +56,48 @@ __device__ __forceinline__ float ld_w(const void *p, size_t i, int wdt) {
   return wdt ? __uint_as_float((uint32_t)((const uint16_t *)p)[i] << 16) : ((const float *)p)[i];
 }
 
-// Store v for input k of candidate cand into an operand buffer (hi and lo halves).
+// Store v for input k of candidate cand into an operand buffer: columns cand and cand + Bp hold
+// its hi and lo halves. Bp = 4 (one column tile, at most 4 candidates) leaves room for a third
+// term at cand + 2 Bp, so that a few candidates' activations keep 24 bits at no cost.
 __device__ __forceinline__ void store_operand(uint16_t *op, int NT, int Bp, int k, int cand,
                                               float v) {
-  uint32_t hi, lo;
-  split_hi_lo(v, hi, lo);
   const int kb = k >> 5, c = (k >> 3) & 3, i = k & 7;
-  int col = cand;
-  op[((size_t)((kb * NT + (col >> 4)) * 64 + c * 16 + (col & 15))) * 8 + i] = (uint16_t)hi;
-  col = cand + Bp;
-  op[((size_t)((kb * NT + (col >> 4)) * 64 + c * 16 + (col & 15))) * 8 + i] = (uint16_t)lo;
+  auto put = [&](int col, uint32_t w) {
+    op[((size_t)((kb * NT + (col >> 4)) * 64 + c * 16 + (col & 15))) * 8 + i] = (uint16_t)w;
+  };
+  uint32_t hi, mid, lo;
+  split3(v, 0.f, hi, mid, lo);
+  put(cand, hi);
+  put(cand + Bp, mid);
+  if (Bp == 4) put(cand + 8, lo);
 }
 
-// The same for inputs k .. k + 3 (k a multiple of 4): two 8-byte stores.
+// The same for inputs k .. k + 3 (k a multiple of 4): 8-byte stores.
 __device__ __forceinline__ void store_operand4(uint16_t *op, int NT, int Bp, int k, int cand,
                                                const float (&v)[4]) {
-  uint2 hi, lo;
-  split2(v[0], v[1], hi.x, lo.x);
-  split2(v[2], v[3], hi.y, lo.y);
   const int kb = k >> 5, c = (k >> 3) & 3, i = k & 7;
-  int col = cand;
-  *(uint2 *)(op + (size_t)((kb * NT + (col >> 4)) * 64 + c * 16 + (col & 15)) * 8 + i) = hi;
-  col = cand + Bp;
-  *(uint2 *)(op + (size_t)((kb * NT + (col >> 4)) * 64 + c * 16 + (col & 15)) * 8 + i) = lo;
+  auto put = [&](int col, const uint2 &w) {
+    *(uint2 *)(op + (size_t)((kb * NT + (col >> 4)) * 64 + c * 16 + (col & 15)) * 8 + i) = w;
+  };
+  uint2 hi, mid, lo;
+  split3(v[0], v[1], hi.x, mid.x, lo.x);
+  split3(v[2], v[3], hi.y, mid.y, lo.y);
+  put(cand, hi);
+  put(cand + Bp, mid);
+  if (Bp == 4) put(cand + 8, lo);
+}
+
+// The sum of a candidate's terms over the columns of one column tile (lane l, column l % 16),
+// valid in columns below Bp: columns n, n + 8 and, with three terms, n + 4, by row rotations (lane i
+// of 16 receives lane i - r; one vector instruction, where an LDS permute costs a round trip).
+__device__ __forceinline__ float sum_terms(float v, int Bp) {
+  auto ror = [](float x, auto r) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x120 + decltype(r)::value, 0xF,
+                                                   0xF, false));
+  };
+  float s = v + ror(v, std::integral_constant<int, 8>{});
+  if (Bp == 4) s += ror(v, std::integral_constant<int, 12>{});
+  return s;
 }
 
 __device__ __forceinline__ float wsum(float v) {
