@@ -1,6 +1,7 @@
-// Matrix-core attention of the verify-token pass for gfx950 (bf16 or fp8 e4m3 caches): the
-// split-L paged chunk kernel over private pages (k_attn_mx), the shared-prefix kernel
-// (k_prefix_mx) and the log-sum-exp merge with the token's own key (k_merge_mx).
+// Matrix-core attention of the verify-token pass for gfx950: the split-L paged chunk kernels over
+// private pages (k_attn_mx for bf16 and fp8 e4m3 caches, k_attn_f32), the shared-prefix kernel
+// (k_prefix_mx), the log-sum-exp merge with the token's own key (k_merge_mx), and the whole step of
+// a short cache in one launch (k_attn_short, k_attn_short_f32).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <string.h>
@@ -108,7 +109,6 @@ __device__ __forceinline__ void unpack_pair(const PairRaw<D> &r, uint4 *KA, uint
 // dim order of the cache dtype's K operand. The loads are unconditional 16-byte ones (a caller's
 // array may be aligned to 4 bytes only, which global loads take) from a row that exists; absent
 // columns are zeroed when the operands are built, so no lane branches around its loads.
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 template <int D>
 struct QueryRaw {
   f32x4u v[D / 32][2];
@@ -855,10 +855,6 @@ hipError_t launch_attn_mx(const Dims &dm, const Plan &p, const Workspace &w, con
 }
 
 // ------------------------------------------------------------------------------- fp32 cache
-
-__device__ __forceinline__ floatx4 mfma4(float a, float b, const floatx4 &c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
 
 // walk_pages on an fp32 cache, a page at a time with the next page's tiles in flight, on the fp32
 // matrix cores: a 16-byte piece of the K tile is four dims of a token and one of the V tile four

@@ -2,7 +2,7 @@
 // cores (v_mfma_f32_16x16x4_f32: exact products of fp32 operands, fp32 sums). Per layer:
 //
 //   q/k/v projection, RMSNorm scale and rotary in its epilogue      -> q, k_self, v_self
-//   attention (split-L paged partials) -> merge with the token's own key (k_merge_mx)
+//   attention (k_attn_f32 -> k_merge_mx, or k_attn_short_f32; kvprm_attn.hip)
 //   output projection + residual (x += .., sums of squares, u = x * gamma_ffn)
 //   gate/up projection + SwiGLU (RMSNorm scale)
 //   down projection + residual (x += .., sums of squares, u = x * gamma_attn of the next layer)
@@ -14,8 +14,7 @@
 // reduction slot c; D holds rows 4c .. 4c+3 of column n. A 16-byte load gives a lane four
 // consecutive inputs 4c .. 4c+3 of a 16-input block, which four products then contract one
 // element at a time: any assignment of inputs to slots works if A and B use the same one, so both
-// operands are read straight from row-major memory, and a product's D layout is the next
-// product's B layout (the probabilities of the attention).
+// operands are read straight from row-major memory.
 #include <math.h>
 #include <string.h>
 
@@ -23,17 +22,6 @@
 #include "kvprm_mx_common.h"
 
 namespace kvprm {
-
-namespace {
-
-// (callers' fp32 arrays may be aligned to 4 bytes only, which 16-byte global loads take)
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-
-__device__ __forceinline__ floatx4 mfma4(float a, float b, const floatx4 &c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-}  // namespace
 
 // ------------------------------------------------------------------------------- init
 

@@ -16,7 +16,8 @@
 //
 // Precision: weights and cache values enter the matrix cores exactly (bf16, or e4m3 widened to
 // bf16, which is exact). The fp32 operands on the other side are split into bf16 terms,
-// x = hi + lo (three terms for queries), and every term is multiplied, so products keep about
+// x = hi + lo (three terms for queries and for the activations of at most 4 rows), and every term
+// is multiplied, so products keep about
 // fp32 accuracy and accumulate in fp32.
 //
 // MFMA 16x16x32 operand layout used throughout (lane l, c = l / 16, n = l % 16):
@@ -263,7 +264,6 @@ static int ksum_nmax(int ksp) {
 // gives a candidate's scale to any thread. (One thread adding every partial sum took 6 us of the
 // 7B gate/up kernel's 49 for a single candidate.) The last quad of a row may reach into the next
 // one, and past the last row into the workspace's next piece: values that no one uses.
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 struct RmsLoads {
   f32x4u v[4];
 };

@@ -14,6 +14,10 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+// four floats of a caller's array, which may be aligned to 4 bytes only (16-byte global loads take
+// that)
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
 // 16-byte load of data that a call reads exactly once (cache pages of the private ranges, weight
 // tiles): non-temporal, so the stream does not allocate in the caches and displace lines that
 // are reused. Measured on the paged K/V read pattern: 6.5 TB/s instead of 5.6 with plain loads.
@@ -25,6 +29,10 @@ __device__ __forceinline__ uint4 ld_stream(const uint4 *p) {
 __device__ __forceinline__ floatx4 mfma16(const uint4 &a, const uint4 &b, const floatx4 &c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
                                                  __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+__device__ __forceinline__ floatx4 mfma4(float a, float b, const floatx4 &c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
 // Two fp32 values -> packed bf16 pairs hi (RNE) and lo = RNE(x - hi) (the hardware pack-convert,
