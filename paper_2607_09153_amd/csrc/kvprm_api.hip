@@ -232,9 +232,9 @@ static int chunk_shift_for(long long pages) {
 }
 
 // Launch table of the attention kernels. The prefix-sharing hint is used by the matrix-core
-// attention only (the fp32 attention reads every page per candidate)
-// and only for up to kMaxGroups groups; otherwise it is ignored, which changes nothing but
-// speed. With lengths on the host, the chunk lengths are chosen from the pages each kernel
+// attention only (the fp32 attention reads every page per candidate), only for up to kMaxGroups
+// groups and only if one of them has a prefix (the prefix kernel's grid is its chunks, and a grid
+// of none is a launch error); otherwise it is ignored, which changes nothing but speed. With lengths on the host, the chunk lengths are chosen from the pages each kernel
 // actually reads (private pages; group prefixes times their column blocks and kv-heads), and
 // the chunk grid of the private pages is sized to the longest private range; without them the
 // private chunk is that of a batch which fills its page table.
@@ -242,7 +242,9 @@ static GroupTable group_table(const kvprm_handle h, const kvprm_batch *b, const 
   GroupTable gt;
   memset(&gt, 0, sizeof gt);
   gt.cshift_prefix = 4;  // (without a prefix: of no effect)
-  const bool share = h->dm.kvdt != 0 && b->num_groups > 0 && b->num_groups <= kMaxGroups;
+  bool share = false;
+  if (h->dm.kvdt != 0 && b->num_groups <= kMaxGroups)
+    for (int i = 0; i < b->num_groups; ++i) share = share || b->group_prefix_len_host[i] > 0;
   const int kq = p.kq;  // group ranges are kept in rows (candidates x verify tokens)
   if (share) {
     gt.n = b->num_groups;

@@ -6,6 +6,8 @@ depends on the keys and values its page-table row names, in row order, and on no
   unchanged, with and without a shared-prefix group; unused pages hold NaN throughout.
 * The same for the KV Steering gradient (appendix, KV Steering algorithm), which is written per
   physical page: after the move it equals the first gradient moved the same way, bit for bit.
+* A prefix-sharing hint whose groups share nothing yet (all prefixes 0: the first step of a beam)
+  is no hint, bit for bit.
 * Candidate independence: each candidate scored alone (a batch of one, same pools and row)
   equals its score inside the batch up to the summation order of the attention chunks, which
   the plan sizes from the batch.
@@ -92,6 +94,19 @@ def test_physical_page_placement_is_bitwise_invisible(kv_dtype, groups):
     p1, z1 = run_score(dw)
     _say(f"  P(+) = {np.round(p0, 5)}; max|dz| after the move = {np.max(np.abs(z1 - z0)):.3e}")
     assert np.all(np.isfinite(p0)) and np.all(np.isfinite(z0))
+    assert np.array_equal(p0, p1) and np.array_equal(z0, z1)
+
+
+@pytest.mark.parametrize("kv_dtype", ["bf16", "fp8"])
+@pytest.mark.parametrize("lengths", [[300, 0, 17, 512], [4100, 0, 700, 2049]])
+def test_hint_without_shared_pages_is_no_hint(kv_dtype, lengths):
+    _say(f"case: groups without a prefix, {kv_dtype} lengths={lengths}")
+    w = synth.make_workload("custom", shape=dataclasses.replace(SHAPE, kv_dtype=kv_dtype),
+                            lengths=lengths, seed=8150, groups=([0, 3, 4], [0, 0]))
+    dw = DeviceWorkload(w, nan_unused_pages=True)
+    p0, z0 = run_score(dw, with_hint=False)
+    p1, z1 = run_score(dw, with_hint=True)
+    assert np.all(np.isfinite(z0))
     assert np.array_equal(p0, p1) and np.array_equal(z0, z1)
 
 
