@@ -223,21 +223,13 @@ static kvprm_status plan_for(const kvprm_handle h, const kvprm_batch *b, int ran
 // 46.9 / 49.0 but 512 blocks 61.3 / 58.6; 7B shape, 64 candidates of 300 148.8 / 154.8.
 constexpr int kShortBlocks = 256;
 
-// Shared-prefix chunk: the longest of 16, 32, 64 pages that leaves at least 160 work items for
-// `pages` pages.
-static int chunk_shift_for(long long pages) {
-  int sh = 6;
-  while (sh > 4 && pages < (160LL << sh)) --sh;
-  return sh;
-}
-
 // Launch table of the attention kernels. The prefix-sharing hint is used by the matrix-core
 // attention only (the fp32 attention reads every page per candidate), only for up to kMaxGroups
 // groups and only if one of them has a prefix (the prefix kernel's grid is its chunks, and a grid
 // of none is a launch error); otherwise it is ignored, which changes nothing but speed. With lengths on the host, the chunk lengths are chosen from the pages each kernel
 // actually reads (private pages; group prefixes times their column blocks and kv-heads), and
 // the chunk grid of the private pages is sized to the longest private range; without them the
-// private chunk is that of a batch which fills its page table.
+// private chunk is no longer than that of a batch which fills its page table.
 static GroupTable group_table(const kvprm_handle h, const kvprm_batch *b, const Plan &p) {
   GroupTable gt;
   memset(&gt, 0, sizeof gt);
@@ -260,7 +252,7 @@ static GroupTable group_table(const kvprm_handle h, const kvprm_batch *b, const 
       items += (long long)pp * blocks;
     }
     // the hint requires host lengths (checked), so the chunks follow the actual work
-    gt.cshift_prefix = chunk_shift_for(items * h->dm.nkv);
+    gt.cshift_prefix = long_chunk_shift(items * h->dm.nkv);
     for (int i = 0; i < gt.n; ++i) {
       const int ch = (gt.prefix_pages[i] + (1 << gt.cshift_prefix) - 1) >> gt.cshift_prefix;
       if (ch > gt.prefix_chunks) gt.prefix_chunks = ch;
@@ -274,7 +266,7 @@ static GroupTable group_table(const kvprm_handle h, const kvprm_batch *b, const 
     priv[i] = b->lengths_host ? (b->lengths_host[i] + kPage - 1) / kPage - first : b->max_pages;
     slots[i] = p.nch - ((first + (1 << gt.cshift_prefix) - 1) >> gt.cshift_prefix);
   }
-  const PrivateChunks pc = private_chunk_rule(h->dm, b->batch, priv, slots);
+  const PrivateChunks pc = private_chunk_rule(h->dm, b->batch, priv, slots, b->lengths_host != nullptr);
   gt.cshift_private = pc.shift;
   gt.heads_per_block = pc.heads_per_block;
   const int CP = 1 << pc.shift;

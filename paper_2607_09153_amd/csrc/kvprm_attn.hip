@@ -247,6 +247,7 @@ struct AttnArgs {
   int NT, Bp;
   float *lse;     // [B][nq] log-sum-exp of each softmax, own keys included (may be null)
   int ginv;       // 65536 / g rounded up: n / g = (n * ginv) >> 16 for n < 16
+  uint32_t binv;  // 2^21 / candidates rounded up: n / candidates = (n * binv) >> 21 for n < 1152
   int kq;         // verify tokens per candidate: row v = token v % kq of candidate v / kq; q,
                   // k_self, v_self, partials and o are per row, lengths and page table per
                   // candidate, group ranges in rows
@@ -343,22 +344,29 @@ __device__ __forceinline__ void walk_pages(const AttnArgs &a, int b, int j, int 
     chunk_loop(std::integral_constant<bool, true>{});
 }
 
-// One block per (chunk of pages, candidate b, group of kv-heads) over the candidate's private
+// One block per (kv-head or all of them, candidate b, chunk of pages) over the candidate's private
 // pages, one wave per kv-head j (with every head in one block the n_kv tiles of a page,
-// contiguous in the pool, are read together; the call's GroupTable says how many heads).
+// contiguous in the pool, are read together; the call's GroupTable says which).
 // The wave writes its unnormalised partial (acc, m, l) per q-head.
+// Grid order: heads, then candidates, then chunks, the candidates rotated by the chunk. Blocks go to
+// the 8 XCDs in turn and to a free unit within each: full chunks thus start first and spread evenly, and the short
+// or absent last ones fill in. With chunks innermost a chunk count that shares a factor with 8 put every
+// candidate's short last chunk on the same XCDs (32 ragged candidates of 2k-4k tokens, 8 heads, attention
+// call 80.8 -> 68.9 us; 64 of 1k-2k, 4 heads 58.3 -> 44.7; at worst 4-5% slower, from 16 long chunks a candidate).
 // The start of a block (query, lengths, page ids, first pair) is a serial chain that every block
 // pays once: with one branch-guarded 4-byte load per query element and the bf16 split in integer
 // arithmetic it took 1.5-2 us more than with 16-byte loads issued first and the hardware
-// pack-convert (7B batch of 16: 26.9 -> 25.2 us a layer, ragged 32k 67.9 -> 66.4, private pages of
-// the 64-candidate beam 34.6 -> 32.3, shared prefix 52.7 -> 49.9).
+// pack-convert (7B batch of 16: 26.9 -> 25.2 us a layer, eight ragged candidates of 200616 tokens
+// 67.9 -> 66.4, private pages of the 64-candidate beam 34.6 -> 32.3, shared prefix 52.7 -> 49.9).
 template <int KVT, int D>
 __global__ __launch_bounds__(64 * kMaxKvHeadsMx) void k_attn_mx(AttnArgs a) {
   constexpr int NDB = D / 16;
-  const int c = blockIdx.x, b = blockIdx.y;  // chunk, candidate
+  const uint32_t turn = blockIdx.y + blockIdx.z;
+  const int c = blockIdx.z;  // chunk, candidate
+  const int b = (int)(turn - ((turn * a.binv) >> 21) * gridDim.y);
   // (the wave index as a scalar, so that tile addresses are scalar too)
   const int j =
-      __builtin_amdgcn_readfirstlane((int)(blockIdx.z * (blockDim.x >> 6) + (threadIdx.x >> 6)));
+      __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
   const int nkv = a.nkv, g = a.g, nq = a.nq, kq = a.kq;
   const int L = a.lengths[b];
   const int lane = threadIdx.x & 63;
@@ -841,7 +849,9 @@ hipError_t launch_attn_mx(const Dims &dm, const Plan &p, const Workspace &w, con
   const int hpb = gt.heads_per_block;
   if (gt.private_chunks < 1 || hpb < 1 || hpb > kMaxKvHeadsMx || dm.nkv % hpb != 0)
     return hipErrorInvalidValue;
-  const dim3 grid(gt.private_chunks, p.Breal, dm.nkv / hpb);
+  static_assert(kMaxChunks + 64 <= 1152, "the rotation's division is exact");
+  a.binv = ((1u << 21) + p.Breal - 1) / p.Breal;
+  const dim3 grid(dm.nkv / hpb, p.Breal, gt.private_chunks);
 #define KVPRM_A(KVT, D) hipLaunchKernelGGL((k_attn_mx<KVT, D>), grid, dim3(64 * hpb), 0, s, a)
   if (dm.kvdt == 1) {
     if (dm.d == 64) KVPRM_A(1, 64);

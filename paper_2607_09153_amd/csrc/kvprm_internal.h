@@ -27,8 +27,8 @@ struct GroupTable {
   int prefix_pages[kMaxGroups];        // shared pages of each group
   int colblock_start[kMaxGroups + 1];  // shared-prefix column blocks of the groups, cumulative
   int prefix_chunks;                   // chunks of the longest group prefix
-  int private_chunks;                  // chunk grid of the private pages (0 = from max_pages)
-  int heads_per_block;                 // kv-heads (waves) of a private-page block
+  int private_chunks;                  // chunk grid of the private pages (at least 1)
+  int heads_per_block;                 // kv-heads (waves) of a private-page block: one or all
   int one_launch;                      // short caches: k_attn_short in place of chunks and merge
   int cshift_prefix, cshift_private;   // chunk lengths (1 << shift pages) of the two kernels
 };
@@ -40,6 +40,7 @@ constexpr int kChunkPagesF32 = 32;  // longest chunk of an fp32 cache
 constexpr int kMaxChunks = 1024;  // chunk partials one merge handles
 constexpr int kMaxKvHeadsMx = 8;  // matrix-core attention: one wave per kv-head in a block
 constexpr int kFineChunks = 128;  // chunks of one candidate at most, in chunks under 16 pages
+constexpr long long kShortChunkBytes = 160LL << 20;  // private pages of a layer in short chunks
 constexpr int kShortPages = 32;   // longest cache of the one-launch attention
 constexpr int kShortWaves = 8;    // its waves per block
 constexpr int kMaxBatch = 256;    // candidates of a call
@@ -156,11 +157,15 @@ hipError_t launch_pack_kv(const void *src, void *dst, int64_t ntiles, int d, int
 Plan make_plan(const Dims &dm, int B, int max_pages, int lora_rank = 0, int depth = 1,
                bool lean = false);
 // Chunk length of the private pages (1 << shift pages) and the heads per block, see the
-// definition: pages[i] = private pages of candidate i, slots[i] = chunk slots they may take.
+// definition: pages[i] = private pages of candidate i (known: from host lengths), slots[i] = chunk
+// slots they may take.
 struct PrivateChunks {
   int shift, heads_per_block;
 };
-PrivateChunks private_chunk_rule(const Dims &dm, int n, const int *pages, const int *slots);
+PrivateChunks private_chunk_rule(const Dims &dm, int n, const int *pages, const int *slots,
+                                 bool known);
+// Long chunks: the longest of 16, 32, 64 pages that leaves at least 160 work items for `pages` pages.
+int long_chunk_shift(long long pages);
 // Chunk length of the backward attention, in pages.
 int backward_chunk_pages(const Dims &dm, int n, const int *pages, int slots);
 Workspace carve(const Dims &dm, const Plan &p, void *base);

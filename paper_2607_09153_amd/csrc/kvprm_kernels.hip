@@ -68,6 +68,11 @@ static size_t partial_elems(const GemvPlan &g) {
   return (size_t)((g.ksplit + 3) & ~3) * g.rows;
 }
 
+// Bytes of keys and values of one page and head.
+static int page_bytes(const Dims &dm) {
+  return 2 * kPage * dm.d * (dm.kvdt == 0 ? 4 : dm.kvdt == 1 ? 2 : 1);
+}
+
 // Waves (kv-head x chunk) up to which shorter attention chunks pay: a wave takes about 4 us to
 // start and end and 0.7 us per page pair however idle the chip is, so a small batch is fastest
 // in many short chunks, until the waves' fixed cost and the merge's partials outweigh it. For 8 KiB
@@ -76,25 +81,38 @@ static size_t partial_elems(const GemvPlan &g) {
 // An fp32 page costs several times the products of a bf16 one (0.6 us at d_h = 64), so fp32
 // chunks are shorter: up to two waves per SIMD unit.
 static long long chunk_wave_limit(const Dims &dm) {
-  if (dm.kvdt == 0) return 2048;
-  const int page_bytes = 2 * kPage * dm.d * (dm.kvdt == 2 ? 1 : 2);
-  return 800LL * 8192 / page_bytes;
+  return dm.kvdt == 0 ? 2048 : 600LL * 8192 / page_bytes(dm);
 }
 
-// The shortest chunk of 4, 8, .. 64 pages (fp32: 2 .. 32) whose waves stay within chunk_wave_limit and whose
-// chunks fit the slots (kFineChunks below 16 pages); 64 otherwise. Up to 512 waves (of that page
-// size) each wave is a block of its own, so that the work spreads over the compute units (a
-// unit takes in about 50 GB/s: eight heads in one block share that); beyond, four heads to a
-// block up to 1024 waves, then all heads, whose tiles of one page are contiguous. Measured,
-// attention kernel per layer, one head per block / all heads: 1103 tokens x 8 heads 4.9 us in 4-page chunks (24.7 before, 16-page
-// chunks of 8 waves); 4096 tokens x 4 heads 5.1 (4 pages; 16.2 before); four candidates of
-// 4k-8k 11.8 (8 pages; 17.7 before); 16 x 4096 tokens 23.9 (32 pages; 25.2 in 16 pages x all heads); ragged
-// 8 x 16k-32k 69.1 / 66.4 (64 pages).
-PrivateChunks private_chunk_rule(const Dims &dm, int n, const int *pages, const int *slots) {
-  const long long limit = chunk_wave_limit(dm);
-  const int lo = dm.kvdt == 0 ? 1 : 2, hi = dm.kvdt == 0 ? 5 : 6;
-  PrivateChunks r{hi, dm.nkv};
-  long long waves = 0;
+int long_chunk_shift(long long pages) {
+  int sh = 6;
+  while (sh > 4 && pages < (160LL << sh)) --sh;
+  return sh;
+}
+
+// Up to 160 MiB of private pages a layer (bf16 and fp8): the shortest chunk of 4, 8, .. 64 pages whose
+// waves stay within chunk_wave_limit and whose chunks fit the slots (kFineChunks below 16 pages),
+// each wave a block of its own, so that the work spreads over the compute units (a unit takes in
+// about 50 GB/s: eight heads in one block share that). A larger batch loads the chip in any form: chunks as
+// long as leave 160 blocks of all heads, whose tiles of one page are contiguous. Without host
+// lengths (known = false) the pages are those of a full table, more than the candidates hold, so that
+// chunks are no longer than that either. fp32: the shortest of 2 .. 32 pages within the wave limit.
+// Measured, attention call (chunks and merge) at every chunk length x heads per block, 1190 batches (14
+// head layouts, 1 to 64 candidates of 600 to 32000 tokens, equal and ragged): this rule is 2.2% from the
+// fastest on average. Up to 160 MiB: short chunks of one head 2.0% from it, of all heads 18%, long ones
+// 38%; beyond: 2.9% and 3.0%, but one head up to 12% slower than all on the longest ragged batches. Chunk
+// kernel alone: 1103 tokens x 8 heads 4.9 us (24.7 in 16-page chunks of 8 waves); 4096 tokens x 4
+// heads 5.1 (16.2); four candidates of 4k-8k 11.8 (17.7); 16 x 4096 tokens 23.9 (25.2); eight ragged of
+// 200616 tokens 69.1 one head per block, 66.4 all heads (64 pages).
+PrivateChunks private_chunk_rule(const Dims &dm, int n, const int *pages, const int *slots,
+                                 bool known) {
+  const bool f32 = dm.kvdt == 0;
+  long long total = 0;
+  for (int i = 0; i < n; ++i) total += pages[i];
+  if (!f32 && total * dm.nkv * page_bytes(dm) > kShortChunkBytes)
+    return PrivateChunks{long_chunk_shift(total), dm.nkv};
+  const int lo = f32 ? 1 : 2, hi = f32 ? 5 : 6;
+  PrivateChunks r{hi, 1};
   for (int sh = lo; sh <= hi; ++sh) {
     long long items = 0;
     bool fits = true;
@@ -103,16 +121,12 @@ PrivateChunks private_chunk_rule(const Dims &dm, int n, const int *pages, const 
       items += ch;
       if (ch > slots[i] || (sh < 4 && ch > kFineChunks)) fits = false;
     }
-    waves = items * dm.nkv;
-    if (waves <= limit && fits) {
+    if (items * dm.nkv <= chunk_wave_limit(dm) && fits) {
       r.shift = sh;
       break;
     }
   }
-  if (waves <= limit * 512 / 800)
-    r.heads_per_block = 1;
-  else if (waves <= 1024 && dm.nkv % 4 == 0)
-    r.heads_per_block = 4;
+  if (!f32 && !known) r.shift = std::min(r.shift, long_chunk_shift(total));
   return r;
 }
 

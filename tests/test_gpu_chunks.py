@@ -1,5 +1,5 @@
-"""The attention step at every chunk length its rule can pick (4 to 64 pages, one, four or all
-kv-heads to a block): lengths on both sides of a chunk's edges, alone and ragged, with and without
+"""The attention step at every chunk length its rule can pick (4 to 64 pages with one kv-head to a
+block, 16 to 64 with all of them): lengths on both sides of a chunk's edges, alone and ragged, with and without
 lengths on the host, against the fp64 oracle, in exactly the workspace the call asks for.
 Bar as in the attention parity tests: 2e-5 of the largest output (fp32 sums, probabilities and
 queries in two and three bf16 terms)."""
@@ -38,6 +38,12 @@ CASES = [
     (16, 4, 64, "fp8", [1, 9000, 4097, 0, 129, 6001, 8191, 2048]),
     (32, 2, 128, "bf16", [16384, 16385, 8000, 3]),
     (8, 8, 64, "bf16", [16000] * 8 + [31, 1]),
+    (16, 8, 128, "bf16", [4600, 4500]),
+    (8, 4, 128, "bf16", [4096] * 13 + [3969, 4095, 2049]),
+    (8, 4, 128, "bf16", [1100 - i for i in range(63)] + [0]),
+    (16, 8, 128, "bf16", [16000, 31, 15000, 11100]),
+    (16, 8, 128, "fp8", [600 * (i % 7) for i in range(64)]),
+    (28, 4, 128, "bf16", [30000, 29000, 5, 30001, 29999, 30016, 24000]),
 ]
 
 
