@@ -1,5 +1,5 @@
-"""The workspace sizes never fall when a batch grows, in candidates or in page-table width: a
-workspace sized for the largest batch serves every smaller one."""
+"""The workspace sizes never fall when a batch grows, in candidates or in page-table width, with any
+of the readout's options: a workspace sized for the largest batch serves every smaller one."""
 import pytest
 
 import paper_2607_09153_amd as kv
@@ -16,6 +16,13 @@ def test_workspace_never_falls(shape, wdt, kvdt):
     calls = [(kv.kvprm_workspace_size, (1, 2, 3, 7, 8, 9, 16, 17, 33, 34, 64))]
     if kvdt == "bf16":
         calls.append((kv.kvprm_workspace_size_grad, range(1, 9)))
+    if wdt == "bf16":
+        for rank in (32, 256, 512):
+            calls.append((lambda h, b, r=rank: kv.kvprm_workspace_size_lora(h, b, r), calls[0][1]))
+        for depth in (2, 3, 4, 8):
+            if depth * shape[2] // shape[3] <= 16:
+                size = lambda h, b, o=kv.make_options(depth=depth): kv.kvprm_workspace_size_ex(h, b, o)
+                calls.append((size, [B for B in calls[0][1] if B * depth <= 64]))
     try:
         for size, batches in calls:
             last = {}
