@@ -205,24 +205,40 @@ Plan make_plan(const Dims &dm, int Breal, int max_pages, int lora_rank, int dept
     // rows over the whole input and reads the whole operand (NT KiB per input block) from L2,
     // for H / 16 row tiles (224 at the 7B shape, under one block per compute unit); the split
     // blocks share each operand batch over 8 row tiles and cover all compute units, at the cost
-    // of one more launch. Measured per call: the down projection for every batch size (ragged
-    // 32k 4.79-4.82 -> 4.73-4.76 ms, 7B batch of 16 3.86 -> 3.59), q/k/v too for 9-16 rows (3.57),
-    // all three for 9-16 rows with at least 512 row tiles (large fp8 24.6 -> 23.7) and for more
-    // than 16 rows (beam 7.92 -> 6.74 with output and down, 6.8 -> 6.75 with q/k/v). Short products
-    // lose more to the second launch than they gain, us per layer fused / split: q/k/v up to 16 M
-    // weights (H = 1024: 56 / 61 at 48 rows, 47 / 52 at 16; H = 2560, 15.7 M: 122.4 / 124.2 at 64),
-    // the output projection from fewer than 1024 inputs (H = 256: 33.9 / 40.2 at 32 rows), and with
-    // one column tile the down projection of up to 8192 inputs over at least 128 row tiles
-    // (H = 2048, F = 2048: 45.4 / 47.4 at one row; H = 256, F = 1024: 32.8 / 30.8).
+    // of one more launch. Measured per call: the down projection (ragged
+    // 32k 4.79-4.82 -> 4.73-4.76 ms, 7B batch of 16 3.86 -> 3.59); output and q/k/v too for 9-16 rows
+    // with at least 512 row tiles (large fp8 24.6 -> 23.7) and for more than 16 rows (beam
+    // 7.92 -> 6.74 with output and down, 6.8 -> 6.75 with q/k/v). Short products lose more to the
+    // second launch (3 to 4 us) than they gain. By how much the fused kernel is faster (-: slower),
+    // us a layer, mean of eager and replayed calls of 2 to 28 layers, spread up to 1:
+    //   down, inputs F      1024        2048        4096        8192        16384
+    //   1-8 rows, H = 256   2.2..2.8    0.5..1.0    -1.1..-1.8  -4.1..-5.0  -10.5..-11.7
+    //             H = 512   3.3..3.8    2.5..3.1    -0.2..0.4   -2.9..-3.9  -9.3..-10.0
+    //             H = 1024  3.3..4.0    2.6..3.2    0.3..1.0    -1.8..-3.0  -6.9..-8.2
+    //             H = 2048  2.9..4.0    2.1..3.5    0.1..1.9    0.5..1.7    -1.8..0.8
+    //             H = 3072  2.9..3.9    2.2..3.3    0.3..1.1    0.1..1.3    -3.8..0.3
+    //             H = 4096  3.5..3.8    2.0..2.7    1.7..3.0    2.8..3.7    2.5..3.4
+    //   16 rows, any H      0.9..2.7    0.1..2.4    -2.1..2.7   -6.5..2.2   -16.0..-0.7
+    //   48 rows, any H      0.7..4.1    -2.0..3.7   -8.2..0.7   -18..-4     -41..-18
+    //   (H = 3584, 5120, 8192 with 18944, 17408, 28672 inputs, 1-8 rows: -1.9..-3.0, -11, -5..-7)
+    //   q/k/v, up to 256 rotary tile pairs, 30 shapes of 24 to 48 heads:
+    //   inputs H            2048        2560        3072        3584        4096        5120
+    //   1-8 rows            0.9..2.8    0.5..2.1    1.8..2.9    0.9..2.8    0.7..2.8    2.5..3.8
+    //   9-16 rows           -0.6..4.2   -1.3..0.8   0.4..4.2    -1.2..2.9   -1.9..2.5   -0.7..3.2
+    //   17-64 rows          -0.3..5.1   -1.3..3.2   -2.4..1.2   -3.2..1.5   -4.4..0.9   -7.1..-1.3
+    //   (smaller H: faster at all rows, 1.4..6.7.) More pairs than compute units take a second round of
+    //   blocks: H = 8192, 320 pairs -7 at 9 rows, -35 at 64.
+    // The output projection has fewer than 1024 inputs (H = 256: 33.9 / 40.2 at 32 rows fused / split).
     {
       // input blocks per batch of k_resid_split; with one column tile 16 where the input widths
       // divide (ragged 32k 4.75 -> 4.69 ms per call against 8), else 8
       int U = 4;
       if (p.nt == 1) U = (dm.nq * dm.d / 32) % 16 == 0 && (dm.F / 32) % 16 == 0 ? 16 : 8;
-      const bool down = !(p.nt == 1 && dm.H >= 2048 && dm.F <= 8192);
+      const int down_fused = p.nt >= 4 ? 1024 : p.nt == 2 ? 2048  // inputs up to which it pays
+                             : dm.H >= 2048 ? 8192 : dm.H >= 512 ? 4096 : 2048;
+      const bool down = dm.F > down_fused;
       const bool out = p.nt >= 4 ? dm.nq * dm.d >= 1024 : p.nt == 2 && dm.H / 16 >= 512;
-      const long long qkv_weights = (long long)(dm.nq + 2 * dm.nkv) * dm.d * dm.H;
-      const bool qkv = p.nt >= 2 && (pairs > 256 || qkv_weights > 16000000);
+      const bool qkv = pairs > 256 ? p.nt >= 2 : p.nt >= 4 && dm.H >= 3072;
       if ((dm.nq * dm.d / 32) % U == 0 && (dm.F / 32) % U == 0) {
         // (8 row tiles per block measured faster than 16: 6.74 against 6.79 ms per call of the
         // 64-candidate beam)
