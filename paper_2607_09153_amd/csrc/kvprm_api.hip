@@ -226,10 +226,11 @@ constexpr int kShortBlocks = 256;
 // Launch table of the attention kernels. The prefix-sharing hint is used by the matrix-core
 // attention only (the fp32 attention reads every page per candidate), only for up to kMaxGroups
 // groups and only if one of them has a prefix (the prefix kernel's grid is its chunks, and a grid
-// of none is a launch error); otherwise it is ignored, which changes nothing but speed. With lengths on the host, the chunk lengths are chosen from the pages each kernel
-// actually reads (private pages; group prefixes times their column blocks and kv-heads), and
-// the chunk grid of the private pages is sized to the longest private range; without them the
-// private chunk is no longer than that of a batch which fills its page table.
+// of none is a launch error); otherwise it is ignored, which changes nothing but speed. With
+// lengths on the host, the chunk lengths are chosen from the pages each kernel actually reads
+// (private pages; group prefixes times their column blocks and kv-heads), and the chunk grid of the
+// private pages is sized to the longest private range; without them the private chunk is no longer
+// than that of a batch which fills its page table.
 static GroupTable group_table(const kvprm_handle h, const kvprm_batch *b, const Plan &p) {
   GroupTable gt;
   memset(&gt, 0, sizeof gt);
@@ -323,11 +324,11 @@ static kvprm_status check_lora(const kvprm_handle h, const kvprm_lora *lora, con
 }
 
 // The matrix-core pipeline (bf16 weights), per layer: the q/k/v projection with the RMSNorm
-// scale and the rotary embedding in its epilogue, the attention chunk kernel(s) and their merge,
-// then the output, gate/up and down projections with their element-wise steps fused. The down
-// projection (all batch sizes), q/k/v (more than 8 rows) and the output projection (more than 16
-// rows, or large shapes) run instead as split-K products with a finish kernel each: seven to
-// nine launches per layer (one more with shared prefixes). With an adapter, each
+// scale and the rotary embedding in its epilogue, the attention chunk kernel(s) and their merge
+// (short caches: one kernel), then the output, gate/up and down projections with their element-wise
+// steps fused. Where make_plan's rules say so, q/k/v, the output and the down projection run as
+// split-K products with a finish kernel each: five to nine launches per layer (one more with
+// shared prefixes). With an adapter, each
 // projection group that has one first computes scale * A u (a split-K GEMV and its finish) and
 // the projection adds B (scale * A u) as a tail of its input range.
 // With sv, the activations the backward pass needs are kept per layer (GradSave).

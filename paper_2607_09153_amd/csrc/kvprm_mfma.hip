@@ -878,8 +878,8 @@ __global__ __launch_bounds__(64 * WPB, 1) void k_gateup_pair(FusedArgs a) {
   }
 }
 
-// Split-K projection (q/k/v, output, down) for more than 16 candidates. At NT >= 4 column tiles
-// every input block brings NT KiB of operand for each 1 KiB weight tile, and a block that owns
+// Split-K projection (q/k/v, output, down; make_plan says for which rows and shapes). Every input
+// block brings NT KiB of operand for each 1 KiB weight tile, and a block that owns
 // one row tile (or tile pair) over the whole input (k_gemv_fused) pulls its whole operand from
 // L2 for a few hundredth of the weights. Here block (g, ks) owns row tiles g WPB .. g WPB + WPB
 // - 1 (one per wave; the rows may stack up to three weight segments) over input slice ks: each
