@@ -4,7 +4,8 @@
 * gate/up: one tile pair per block (up to 256 pairs, up to 512 above 16 rows) and, beyond, 2 to 8
   pairs per block with whole and partial last blocks, at 1 to 64 rows (one to eight operand column
   tiles), with and without an adapter's tail, and for inputs that are no whole number of batches;
-* q/k/v: the split product and its finish with an adapter on some of q, k and v.
+* q/k/v: the split product and its finish with an adapter on some of q, k and v;
+* q/k/v and down on both sides of each limit between the fused and the split form.
 
 Wide models with random weights of a few layers: bars |dP(+)| <= 2e-3 and |dz| <= 2e-2 as in the
 parity tests, which a misplaced tile exceeds.
@@ -83,6 +84,16 @@ def test_split_qkv_adapter_tail(targets, B):
     shape = synth.ModelShape(1, 256, 64, 8, 128, 512)
     w = synth.make_workload("custom", shape=shape, lengths=_lengths(B), seed=8600 + B)
     _lora_parity(w, 96, targets)
+
+
+@pytest.mark.parametrize("H,F,B", [
+    (256, 2048, 1), (256, 2304, 5), (512, 4096, 8), (512, 4608, 3), (2048, 8192, 4), (2048, 8704, 8),
+    (256, 2048, 9), (256, 2176, 16), (320, 1024, 17), (320, 1152, 64),   # down
+    (2944, 512, 17), (3072, 512, 33), (3072, 512, 16), (3072, 512, 64)])  # q/k/v
+def test_each_side_of_the_split_limits(H, F, B):
+    print(f"case: H={H} F={F} B={B}", flush=True)
+    shape = synth.ModelShape(2, H, 4, 2, 64, F)
+    _parity(synth.make_workload("custom", shape=shape, lengths=_lengths(B), seed=8650 + B))
 
 
 def _bf16(x):
