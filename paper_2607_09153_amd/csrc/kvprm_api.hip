@@ -228,9 +228,9 @@ constexpr int kShortBlocks = 256;
 // groups and only if one of them has a prefix (the prefix kernel's grid is its chunks, and a grid
 // of none is a launch error); otherwise it is ignored, which changes nothing but speed. With
 // lengths on the host, the chunk lengths are chosen from the pages each kernel actually reads
-// (private pages; group prefixes times their column blocks and kv-heads), and the chunk grid of the
-// private pages is sized to the longest private range; without them the private chunk is no longer
-// than that of a batch which fills its page table.
+// (private pages; group prefixes times their column blocks and kv-heads), and the grid of the
+// private pages is sized to their chunks; without them it is sized to a batch which fills its page
+// table, and the private chunk is no longer than that batch's.
 static GroupTable group_table(const kvprm_handle h, const kvprm_batch *b, const Plan &p) {
   GroupTable gt;
   memset(&gt, 0, sizeof gt);
@@ -268,14 +268,16 @@ static GroupTable group_table(const kvprm_handle h, const kvprm_batch *b, const 
     slots[i] = p.nch - ((first + (1 << gt.cshift_prefix) - 1) >> gt.cshift_prefix);
   }
   const PrivateChunks pc = private_chunk_rule(h->dm, b->batch, priv, slots, b->lengths_host != nullptr);
+  const int CP = 1 << pc.shift;
   gt.cshift_private = pc.shift;
   gt.heads_per_block = pc.heads_per_block;
-  const int CP = 1 << pc.shift;
   gt.private_chunks = 1;
+  gt.private_items = b->batch;
   int longest = 0;
   for (int i = 0; i < b->batch; ++i) {
     const int ch = (priv[i] + CP - 1) / CP;
     if (ch > gt.private_chunks) gt.private_chunks = ch;
+    gt.private_items += priv[i] >> pc.shift;
     if (priv[i] > longest) longest = priv[i];
   }
   // (a prefix group's shared pages are read by the chunk kernels)

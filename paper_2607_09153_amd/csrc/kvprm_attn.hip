@@ -247,7 +247,7 @@ struct AttnArgs {
   int NT, Bp;
   float *lse;     // [B][nq] log-sum-exp of each softmax, own keys included (may be null)
   int ginv;       // 65536 / g rounded up: n / g = (n * ginv) >> 16 for n < 16
-  uint32_t binv;  // 2^21 / candidates rounded up: n / candidates = (n * binv) >> 21 for n < 1152
+  int B;          // candidates
   int kq;         // verify tokens per candidate: row v = token v % kq of candidate v / kq; q,
                   // k_self, v_self, partials and o are per row, lengths and page table per
                   // candidate, group ranges in rows
@@ -344,51 +344,84 @@ __device__ __forceinline__ void walk_pages(const AttnArgs &a, int b, int j, int 
     chunk_loop(std::integral_constant<bool, true>{});
 }
 
-// One block per (kv-head or all of them, candidate b, chunk of pages) over the candidate's private
-// pages, one wave per kv-head j (with every head in one block the n_kv tiles of a page,
-// contiguous in the pool, are read together; the call's GroupTable says which).
-// The wave writes its unnormalised partial (acc, m, l) per q-head.
-// Grid order: heads, then candidates, then chunks, the candidates rotated by the chunk. Blocks go to
-// the 8 XCDs in turn and to a free unit within each: full chunks thus start first and spread evenly, and the short
-// or absent last ones fill in. With chunks innermost a chunk count that shares a factor with 8 put every
-// candidate's short last chunk on the same XCDs (32 ragged candidates of 2k-4k tokens, 8 heads, attention
-// call 80.8 -> 68.9 us; 64 of 1k-2k, 4 heads 58.3 -> 44.7; at worst 4-5% slower, from 16 long chunks a candidate).
-// The start of a block (query, lengths, page ids, first pair) is a serial chain that every block
+// Inclusive sum over the lanes of a wave.
+__device__ __forceinline__ int lane_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row shifts by 1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row 0 into 1, 2 into 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // rows 0 and 1 into 2 and 3
+  return v;
+}
+
+// One wave per kv-head j and chunk of a candidate's private pages, over the whole batch; it writes its
+// unnormalised partial (acc, m, l) per q-head. A wave is a block of its own, or the waves of all
+// kv-heads are one (private_chunk_rule).
+// Grid order: heads, then the chunks that exist, full ones of every candidate first and its short last one
+// at the end. Blocks go to the 8 XCDs in turn and to a free unit within each, so that equal work spreads
+// evenly and the short chunks fill in. Each wave finds its candidate and chunk from all lengths (one per
+// lane, at most 64; a scan, a ballot). A grid of (chunk, candidate), chunks of the longest one
+// for each, leaves blocks without work in a regular pattern, and those with work on part of the units: with
+// chunks outermost 12 ragged candidates of 10k-26k, 8 heads, took 214 us a call (149 chunks innermost),
+// now 148; 4 of 1-32k, 4 heads 31.5 (23.4), now 21.7; with chunks innermost 32 of 2k-4k, 8 heads 80.8, now 50.
+// The start of a block (query, page ids, first pair) is a serial chain that every block
 // pays once: with one branch-guarded 4-byte load per query element and the bf16 split in integer
 // arithmetic it took 1.5-2 us more than with 16-byte loads issued first and the hardware
 // pack-convert (7B batch of 16: 26.9 -> 25.2 us a layer, eight ragged candidates of 200616 tokens
 // 67.9 -> 66.4, private pages of the 64-candidate beam 34.6 -> 32.3, shared prefix 52.7 -> 49.9).
-template <int KVT, int D>
+// ONE: a batch of one candidate, whose chunks are the grid's.
+template <int KVT, int D, bool ONE>
 __global__ __launch_bounds__(64 * kMaxKvHeadsMx) void k_attn_mx(AttnArgs a) {
   constexpr int NDB = D / 16;
-  const uint32_t turn = blockIdx.y + blockIdx.z;
-  const int c = blockIdx.z;  // chunk, candidate
-  const int b = (int)(turn - ((turn * a.binv) >> 21) * gridDim.y);
   // (the wave index as a scalar, so that tile addresses are scalar too)
   const int j =
       __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
   const int nkv = a.nkv, g = a.g, nq = a.nq, kq = a.kq;
-  const int L = a.lengths[b];
   const int lane = threadIdx.x & 63;
   const int n = lane & 15, cq = lane >> 4;
+  const int id = blockIdx.y;
+  int b = 0, c = id, L, first = 0;  // candidate, chunk, its length and shared pages
+  if constexpr (ONE) {
+    L = a.lengths[0];
+    if (a.gt.n > 0) first = a.gt.prefix_pages[0];
+  } else {
+    // lane i: candidate i's length, shared pages and full private chunks
+    const int bl = min(lane, a.B - 1);
+    const int L_l = a.lengths[bl];
+    int first_l = 0;
+    for (int gi = 0; gi < a.gt.n; ++gi)
+      if (bl * kq >= a.gt.start[gi] && bl * kq < a.gt.start[gi + 1]) first_l = a.gt.prefix_pages[gi];
+    const int full_l =
+        lane < a.B ? max(0, (L_l + kPage - 1) / kPage - first_l) >> a.gt.cshift_private : 0;
+    const int cum_l = lane_scan(full_l);
+    const int total = __builtin_amdgcn_readlane(cum_l, 63);
+    if (id < total) {
+      b = __builtin_popcountll(__ballot(id >= cum_l));
+      c = id - (__builtin_amdgcn_readlane(cum_l, b) - __builtin_amdgcn_readlane(full_l, b));
+    } else {
+      b = id - total;
+      if (b >= a.B) return;
+      c = __builtin_amdgcn_readlane(full_l, b);
+    }
+    L = __builtin_amdgcn_readlane(L_l, b);
+    first = __builtin_amdgcn_readlane(first_l, b);
+  }
   // column n: verify token n / g of this candidate, q-head j g + n % g (kq g <= 16 columns; the
   // division by multiplication: n < 16, g <= 16)
   const bool colv = n < kq * g;
   const int ti = colv ? (n * a.ginv) >> 16 : 0, hh = colv ? n - ti * g : 0;
   const size_t row = (size_t)b * kq + ti;
-  // the query is the one load that depends on nothing: issued first, split into operands while
-  // the first page pair is in flight
+  // the query first: split into operands while the first page pair is in flight
   QueryRaw<D> qraw;
   load_query<KVT, D>(a.q + (row * nq + (size_t)j * g + hh) * D, cq, qraw);
   __builtin_amdgcn_sched_barrier(0);
   const int npages = (L + kPage - 1) / kPage;
-  int first = 0;
-  for (int gi = 0; gi < a.gt.n; ++gi)
-    if (b * kq >= a.gt.start[gi] && b * kq < a.gt.start[gi + 1]) first = a.gt.prefix_pages[gi];
   const int CP = 1 << a.gt.cshift_private;
   const int ncp = (first + (1 << a.gt.cshift_prefix) - 1) >> a.gt.cshift_prefix;  // prefix chunks
   const int p0 = first + c * CP;
-  if (p0 >= npages) return;
+  // (a device length above its host mirror must not reach past the candidate's slots)
+  if (p0 >= npages || ncp + c >= a.nch) return;
   const int np = min(npages, p0 + CP) - p0;
   float m_run = -INFINITY, l_run = 0.f;
   floatx4 acc[NDB];
@@ -847,18 +880,28 @@ hipError_t launch_attn_mx(const Dims &dm, const Plan &p, const Workspace &w, con
     if (e != hipSuccess) return e;
   }
   const int hpb = gt.heads_per_block;
-  if (gt.private_chunks < 1 || hpb < 1 || hpb > kMaxKvHeadsMx || dm.nkv % hpb != 0)
+  // (one lane per candidate; the grid's y dimension takes 65535)
+  if (p.Breal > 64 || gt.private_items > 65535 || (hpb != 1 && hpb != dm.nkv))
     return hipErrorInvalidValue;
-  static_assert(kMaxChunks + 64 <= 1152, "the rotation's division is exact");
-  a.binv = ((1u << 21) + p.Breal - 1) / p.Breal;
-  const dim3 grid(dm.nkv / hpb, p.Breal, gt.private_chunks);
-#define KVPRM_A(KVT, D) hipLaunchKernelGGL((k_attn_mx<KVT, D>), grid, dim3(64 * hpb), 0, s, a)
+  a.B = p.Breal;
+  const dim3 grid(dm.nkv / hpb, gt.private_items);
+#define KVPRM_A(KVT, D)                                                                        \
+  if (p.Breal == 1)                                                                            \
+    hipLaunchKernelGGL((k_attn_mx<KVT, D, true>), grid, dim3(64 * hpb), 0, s, a);              \
+  else                                                                                         \
+    hipLaunchKernelGGL((k_attn_mx<KVT, D, false>), grid, dim3(64 * hpb), 0, s, a)
   if (dm.kvdt == 1) {
-    if (dm.d == 64) KVPRM_A(1, 64);
-    else KVPRM_A(1, 128);
+    if (dm.d == 64) {
+      KVPRM_A(1, 64);
+    } else {
+      KVPRM_A(1, 128);
+    }
   } else {
-    if (dm.d == 64) KVPRM_A(2, 64);
-    else KVPRM_A(2, 128);
+    if (dm.d == 64) {
+      KVPRM_A(2, 64);
+    } else {
+      KVPRM_A(2, 128);
+    }
   }
 #undef KVPRM_A
   return hipGetLastError();

@@ -29,6 +29,7 @@ struct GroupTable {
   int prefix_chunks;                   // chunks of the longest group prefix
   int private_chunks;                  // chunk grid of the private pages (at least 1)
   int heads_per_block;                 // kv-heads (waves) of a private-page block: one or all
+  int private_items;                   // chunks of all candidates: full ones and a slot for each last one
   int one_launch;                      // short caches: k_attn_short in place of chunks and merge
   int cshift_prefix, cshift_private;   // chunk lengths (1 << shift pages) of the two kernels
 };
@@ -38,9 +39,8 @@ struct GroupTable {
 // private_chunk_rule).
 constexpr int kChunkPagesF32 = 32;  // longest chunk of an fp32 cache
 constexpr int kMaxChunks = 1024;  // chunk partials one merge handles
-constexpr int kMaxKvHeadsMx = 8;  // matrix-core attention: one wave per kv-head in a block
+constexpr int kMaxKvHeadsMx = 8;  // kv-heads with bf16 and fp8 caches
 constexpr int kFineChunks = 128;  // chunks of one candidate at most, in chunks under 16 pages
-constexpr long long kShortChunkBytes = 160LL << 20;  // private pages of a layer in short chunks
 constexpr int kShortPages = 32;   // longest cache of the one-launch attention
 constexpr int kShortWaves = 8;    // its waves per block
 constexpr int kMaxBatch = 256;    // candidates of a call

@@ -75,13 +75,19 @@ static int page_bytes(const Dims &dm) {
 
 // Waves (kv-head x chunk) up to which shorter attention chunks pay: a wave takes about 4 us to
 // start and end and 0.7 us per page pair however idle the chip is, so a small batch is fastest
-// in many short chunks, until the waves' fixed cost and the merge's partials outweigh it. For 8 KiB
-// of keys and values per page and head (bf16, d_h = 128; smaller tiles take proportionally more
-// waves to load the memory system).
+// in many short chunks, until the waves' fixed cost and the merge's partials outweigh it; smaller tiles
+// take more waves to load the memory system. 525 attention batches (six head layouts, bf16 and fp8, 1 to 64
+// candidates of up to 32k tokens, equal, ragged and very ragged), distance from each one's fastest
+// chunk length by this limit:
+//   8 KiB of keys and values per page and head (bf16, d_h = 128)  500 1.8%, 600 1.0, 680 0.8, 800 1.7
+//   4 KiB (bf16, 64; fp8, 128)                                     900 1.7%, 1000 1.2, 1100 1.4, 1280 2.3
+//   2 KiB (fp8, 64)                                                2200 3.4%, 2560 1.5, 2850 0.9, 3600 2.4
 // An fp32 page costs several times the products of a bf16 one (0.6 us at d_h = 64), so fp32
 // chunks are shorter: up to two waves per SIMD unit.
 static long long chunk_wave_limit(const Dims &dm) {
-  return dm.kvdt == 0 ? 2048 : 600LL * 8192 / page_bytes(dm);
+  if (dm.kvdt == 0) return 2048;
+  const int bytes = page_bytes(dm);
+  return bytes >= 8192 ? 680 : bytes >= 4096 ? 1080 : 2850;
 }
 
 int long_chunk_shift(long long pages) {
@@ -90,32 +96,28 @@ int long_chunk_shift(long long pages) {
   return sh;
 }
 
-// Up to 160 MiB of private pages a layer (bf16 and fp8): the shortest chunk of 4, 8, .. 64 pages whose
-// waves stay within chunk_wave_limit and whose chunks fit the slots (kFineChunks below 16 pages),
-// each wave a block of its own, so that the work spreads over the compute units (a unit takes in
-// about 50 GB/s: eight heads in one block share that). A larger batch loads the chip in any form: chunks as
-// long as leave 160 blocks of all heads, whose tiles of one page are contiguous. Without host
+// The shortest chunk of 4, 8, .. 64 pages (fp32: 2 .. 32) whose waves stay within chunk_wave_limit and
+// whose chunks fit the slots (kFineChunks below 16 pages); the longest otherwise. Without host
 // lengths (known = false) the pages are those of a full table, more than the candidates hold, so that
-// chunks are no longer than that either. fp32: the shortest of 2 .. 32 pages within the wave limit.
-// Measured, attention call (chunks and merge) at every chunk length x heads per block, 1190 batches (14
-// head layouts, 1 to 64 candidates of 600 to 32000 tokens, equal and ragged): this rule is 2.2% from the
-// fastest on average. Up to 160 MiB: short chunks of one head 2.0% from it, of all heads 18%, long ones
-// 38%; beyond: 2.9% and 3.0%, but one head up to 12% slower than all on the longest ragged batches. Chunk
-// kernel alone: 1103 tokens x 8 heads 4.9 us (24.7 in 16-page chunks of 8 waves); 4096 tokens x 4
-// heads 5.1 (16.2); four candidates of 4k-8k 11.8 (17.7); 16 x 4096 tokens 23.9 (25.2); eight ragged of
-// 200616 tokens 69.1 one head per block, 66.4 all heads (64 pages).
+// chunks are no longer than a full table's long ones. Chunk
+// kernel alone: 1103 tokens x 8 heads 4.9 us (24.7 in 16-page chunks); 4096 tokens x 4
+// heads 5.1 (16.2); four candidates of 4k-8k 11.8 (17.7).
+// A wave is a block of its own, so that the work spreads over the compute units, except where 64-page
+// chunks with all of 4 or more kv-heads in one block (whose tiles of a page are contiguous) fill most
+// of one or two rounds of the chip, a block to each compute unit. The same 525 batches, all heads in a block
+// against one: 13-18% slower at any chunk length, 1.4% faster on the 63 that this rule picks; eight of
+// 200616 tokens in all, 4 heads 66.4 against 76 us (as waves of their own some units get four, others
+// two or three), but 24 of 4096, 8 heads 96.5 against 65.1.
 PrivateChunks private_chunk_rule(const Dims &dm, int n, const int *pages, const int *slots,
                                  bool known) {
   const bool f32 = dm.kvdt == 0;
-  long long total = 0;
-  for (int i = 0; i < n; ++i) total += pages[i];
-  if (!f32 && total * dm.nkv * page_bytes(dm) > kShortChunkBytes)
-    return PrivateChunks{long_chunk_shift(total), dm.nkv};
   const int lo = f32 ? 1 : 2, hi = f32 ? 5 : 6;
   PrivateChunks r{hi, 1};
+  long long total = 0, items = 0;
+  for (int i = 0; i < n; ++i) total += pages[i];
   for (int sh = lo; sh <= hi; ++sh) {
-    long long items = 0;
     bool fits = true;
+    items = 0;
     for (int i = 0; i < n; ++i) {
       const int ch = (pages[i] + (1 << sh) - 1) >> sh;
       items += ch;
@@ -126,7 +128,13 @@ PrivateChunks private_chunk_rule(const Dims &dm, int n, const int *pages, const 
       break;
     }
   }
-  if (!f32 && !known) r.shift = std::min(r.shift, long_chunk_shift(total));
+  if (f32) return r;
+  if (!known) {
+    r.shift = std::min(r.shift, long_chunk_shift(total));
+  } else if (r.shift == hi && dm.nkv >= 4) {
+    const long long round = items <= 256 ? 256 : 512;
+    if (items <= 512 && items * 10 >= round * 7) r.heads_per_block = dm.nkv;
+  }
   return r;
 }
 

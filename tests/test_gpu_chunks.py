@@ -1,6 +1,7 @@
-"""The attention step at every chunk length its rule can pick (4 to 64 pages with one kv-head to a
-block, 16 to 64 with all of them): lengths on both sides of a chunk's edges, alone and ragged, with and without
-lengths on the host, against the fp64 oracle, in exactly the workspace the call asks for.
+"""The attention step at every chunk length its rule can pick (4 to 64 pages; 64 also with all
+kv-heads to a block): lengths on both sides of a
+chunk's edges, alone and ragged, with and without lengths on the host, against the fp64 oracle, in
+exactly the workspace the call asks for.
 Bar as in the attention parity tests: 2e-5 of the largest output (fp32 sums, probabilities and
 queries in two and three bf16 terms)."""
 import numpy as np
@@ -44,6 +45,11 @@ CASES = [
     (16, 8, 128, "bf16", [16000, 31, 15000, 11100]),
     (16, 8, 128, "fp8", [600 * (i % 7) for i in range(64)]),
     (28, 4, 128, "bf16", [30000, 29000, 5, 30001, 29999, 30016, 24000]),
+    (4, 4, 128, "bf16", [2049 + i % 40 for i in range(40)] + [0, 70] + [2090 - i for i in range(22)]),
+    # very ragged: most candidates without full chunks, the longest first, last and in the middle
+    (16, 4, 64, "fp8", [9000 * i * i // 3969 for i in range(64)]),
+    (8, 8, 128, "bf16", [14000, 0, 63, 64, 700, 0, 3, 12001, 1, 2999]),
+    (8, 2, 64, "bf16", [0] * 31 + [20000] + [0] * 31 + [1]),
 ]
 
 
