@@ -521,7 +521,7 @@ hipError_t launch_pack_kv(const void *src, void *dst, int64_t ntiles, int d, int
   uint4 *b = (uint4 *)dst;
   // Non-temporal from 128 MiB read and written: keys and values together then exceed the 256 MiB
   // memory-side cache, and leaving it alone is faster (28 layers of 8192 tokens at the 7B shape:
-  // 194 -> 185 us for both parts); below, the packed tiles stay there for their first reader (4 layers
+  // 194 -> 185 us for both parts, 180 with the tile size fixed at compile time); below, the packed tiles stay there for their first reader (4 layers
   // of 4000 fp32 tokens, 164 MB in all: 26.1 us plain, 29.6 non-temporal).
   const bool once = ntiles * (int64_t)groups * 32 >= (int64_t)128 << 20;
 #define KVPRM_PK(E_, D_, V_)                                                                          \
