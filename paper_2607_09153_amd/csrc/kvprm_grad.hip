@@ -22,6 +22,7 @@
 #include <string.h>
 
 #include "kvprm_internal.h"
+#include "kvprm_mx_common.h"
 
 namespace kvprm {
 
@@ -29,20 +30,10 @@ namespace {
 
 __device__ __forceinline__ float bf(uint32_t h) { return __uint_as_float(h << 16); }
 
-__device__ __forceinline__ float ldw(const void *p, size_t i) {
-  return bf(((const uint16_t *)p)[i]);
-}
-
 __device__ __forceinline__ uint16_t bf16_round(float f) {
   uint32_t u = __float_as_uint(f);
   u += 0x7FFFu + ((u >> 16) & 1u);
   return (uint16_t)(u >> 16);
-}
-
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
 }
 
 // sum over the N lanes of an aligned N-lane group (N a power of two <= 64)
@@ -56,8 +47,8 @@ __device__ __forceinline__ float sum_lanes(float v) {
 // Sums of u and v over a block of NTHR threads (multiple of 64), in place in every thread.
 template <int NTHR>
 __device__ __forceinline__ void block_sum2(float &u, float &v, float (*red)[NTHR / 64]) {
-  u = wave_sum(u);
-  v = wave_sum(v);
+  u = wsum(u);
+  v = wsum(v);
   if ((threadIdx.x & 63) == 0) {
     red[0][threadIdx.x >> 6] = u;
     red[1][threadIdx.x >> 6] = v;
@@ -71,41 +62,16 @@ __device__ __forceinline__ void block_sum2(float &u, float &v, float (*red)[NTHR
   }
 }
 
-__device__ __forceinline__ uint4 ld_nt(const uint4 *p) {
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-  const u32x4 v = __builtin_nontemporal_load((const u32x4 *)p);
-  return make_uint4(v.x, v.y, v.z, v.w);
-}
-
-constexpr float kLog2e = 1.4426950408889634f;
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 
 // Matrix-core products (lane l, c = l / 16, n = l % 16; D = accumulator):
-//   16x16x32: A lane holds row n, reduction slots 8c .. 8c+7; B lane holds column n, the same
+//   mfma16, 16x16x32: A lane holds row n, reduction slots 8c .. 8c+7; B lane holds column n, the same
 //             slots; D lane holds rows 4c .. 4c+3 of column n
-//   16x16x16: as above with reduction slots 4c .. 4c+3
+//   mma16, 16x16x16: as above with reduction slots 4c .. 4c+3
 // Any assignment of the contracted index to slots works if A and B use the same one.
-__device__ __forceinline__ floatx4 mma32(const uint4 &a, const uint4 &b, const floatx4 &c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
-                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
 __device__ __forceinline__ floatx4 mma16(const uint2 &a, const uint2 &b, const floatx4 &c) {
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(shortx4, a),
                                                    __builtin_bit_cast(shortx4, b), c, 0, 0, 0);
-}
-
-// Two fp32 values as packed bf16 pairs hi and lo = the rest after hi (the hardware pack-convert,
-// nearest-even)
-__device__ __forceinline__ void split_pair(float x0, float x1, uint32_t &hi, uint32_t &lo) {
-  typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
-  typedef float f32x2v __attribute__((ext_vector_type(2)));
-  const f32x2v xv = {x0, x1};
-  hi = __builtin_bit_cast(uint32_t, __builtin_convertvector(xv, bf16x2v));
-  const f32x2v rv = {x0 - __uint_as_float(hi << 16), x1 - __uint_as_float(hi & 0xFFFF0000u)};
-  lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(rv, bf16x2v));
 }
 
 }  // namespace
@@ -130,7 +96,7 @@ __global__ __launch_bounds__(1024) void k_head_bwd(const float *x, const void *g
     for (int u = 0; u < U; ++u) {
       const int i = i0 + u * 1024;
       v[u] = i < H ? xb[i] : 0.f;
-      gw[u] = i < H ? ldw(gam, i) * ldw(wr, i) : 0.f;
+      gw[u] = i < H ? ld_bf16(gam, i) * ld_bf16(wr, i) : 0.f;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -144,7 +110,7 @@ __global__ __launch_bounds__(1024) void k_head_bwd(const float *x, const void *g
   const float dz = 1.0f / (1.0f + expf(-z)) - 1.0f;
   const float c = r * r * r / (float)H * dot;
   for (int i = threadIdx.x; i < H; i += 1024) {
-    const float v = dz * (r * ldw(gam, i) * ldw(wr, i) - c * xb[i]);
+    const float v = dz * (r * ld_bf16(gam, i) * ld_bf16(wr, i) - c * xb[i]);
     dx[(size_t)b * H + i] = v;
     dxT[(size_t)i * kDPad + b] = v;
   }
@@ -167,7 +133,7 @@ __global__ __launch_bounds__(1024) void k_rms_bwd(const float *x, const void *ga
   for (int k = 0; k < PER; ++k) {
     const int i = threadIdx.x + k * 1024, ic = min(i, H - 1);
     xv[k] = x[o + ic];
-    gd[k] = ldw(gam, ic) * dy[o + ic];
+    gd[k] = ld_bf16(gam, ic) * dy[o + ic];
     rv[k] = res[o + ic];
   }
 #pragma unroll
@@ -250,7 +216,7 @@ __global__ __launch_bounds__(256) void k_tgemv_mx(TgemvArgs a) {
       const int tt = min(t + u, t1 - 1);  // past the end: repeat the last tile (its d is zero)
       const int sg = tt >= cum2 ? 2 : (tt >= cum1 ? 1 : 0);
       const int base = sg == 0 ? 0 : (sg == 1 ? cum1 : cum2);
-      wv[u] = ld_nt((const uint4 *)a.w[sg] + ((size_t)kb * a.seg_tiles[sg] + (tt - base)) * 64 + lane);
+      wv[u] = ld_stream((const uint4 *)a.w[sg] + ((size_t)kb * a.seg_tiles[sg] + (tt - base)) * 64 + lane);
     }
   };
   uint4 wa[U], wb[U];
@@ -279,8 +245,8 @@ __global__ __launch_bounds__(256) void k_tgemv_mx(TgemvArgs a) {
     for (int m = 0; m < 8; ++m) {
       uint32_t h0, h1, l0, l1;
       const bool ok = m < a.B;
-      split_pair(ok ? dv[0][m] : 0.f, ok ? dv[1][m] : 0.f, h0, l0);
-      split_pair(ok ? dv[2][m] : 0.f, ok ? dv[3][m] : 0.f, h1, l1);
+      split2(ok ? dv[0][m] : 0.f, ok ? dv[1][m] : 0.f, h0, l0);
+      split2(ok ? dv[2][m] : 0.f, ok ? dv[3][m] : 0.f, h1, l1);
       dop_s[tl][16 * q + m] = make_uint2(h0, h1);
       dop_s[tl][16 * q + 8 + m] = make_uint2(l0, l1);
     }
@@ -308,7 +274,7 @@ __global__ __launch_bounds__(256) void k_tgemv_mx(TgemvArgs a) {
       const uint2 aop = dop_s[t + u - t0][lane];
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const floatx4 tr = mma32(wv[u], sel[h], zero);  // exact: one weight per output
+        const floatx4 tr = mfma16(wv[u], sel[h], zero);  // exact: one weight per output
         const uint2 bop = make_uint2((__float_as_uint(tr[0]) >> 16) | (__float_as_uint(tr[1]) & 0xFFFF0000u),
                                      (__float_as_uint(tr[2]) >> 16) | (__float_as_uint(tr[3]) & 0xFFFF0000u));
         acc[h] = mma16(aop, bop, acc[h]);
@@ -391,9 +357,9 @@ __device__ __forceinline__ void own_key(const float *q, const float *ks, const f
       s += q[r + m] * kr[m];
       dp += dov * vr[m];
     }
-    Dv = wave_sum(Dv);
-    s = wave_sum(s);
-    dp = wave_sum(dp);
+    Dv = wsum(Dv);
+    s = wsum(s);
+    dp = wsum(dp);
     if (lane == 0) {
       const float p = expf(s * (1.0f / sqrtf((float)D)) - lse[(size_t)b * nq + h]);
       p_s[h - h0] = p;
@@ -467,11 +433,11 @@ __global__ __launch_bounds__(64 * W) void k_attn_bwd_mx(AttnBwdArgs a) {
       ov[i] = hv ? y : 0.f;
     }
     uint4 w;
-    split_pair(qv[0], qv[1], w.x, w.z);
-    split_pair(qv[2], qv[3], w.y, w.w);
+    split2(qv[0], qv[1], w.x, w.z);
+    split2(qv[2], qv[3], w.y, w.w);
     qT_s[nb][ln] = w;
-    split_pair(ov[0], ov[1], w.x, w.z);
-    split_pair(ov[2], ov[3], w.y, w.w);
+    split2(ov[0], ov[1], w.x, w.z);
+    split2(ov[2], ov[3], w.y, w.w);
     dO_s[nb][ln] = w;
   }
   // q (three terms) and dO (two) with the dims as reduction index, lane = head n
@@ -488,10 +454,8 @@ __global__ __launch_bounds__(64 * W) void k_attn_bwd_mx(AttnBwdArgs a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float x0 = hv ? qv[2 * i] : 0.f, x1 = hv ? qv[2 * i + 1] : 0.f;
-      uint32_t rest;
-      split_pair(x0, x1, h[i], rest);
-      split_pair(x0 - bf(h[i] & 0xFFFFu), x1 - __uint_as_float(h[i] & 0xFFFF0000u), md[i], lo[i]);
-      split_pair(hv ? ov[2 * i] : 0.f, hv ? ov[2 * i + 1] : 0.f, oh[i], ol[i]);
+      split3(x0, x1, h[i], md[i], lo[i]);
+      split2(hv ? ov[2 * i] : 0.f, hv ? ov[2 * i + 1] : 0.f, oh[i], ol[i]);
     }
     qa_s[0][kk][ln] = make_uint4(h[0], h[1], h[2], h[3]);
     qa_s[1][kk][ln] = make_uint4(md[0], md[1], md[2], md[3]);
@@ -534,8 +498,8 @@ __global__ __launch_bounds__(64 * W) void k_attn_bwd_mx(AttnBwdArgs a) {
   uint4 kn[TL], vn[TL];
 #pragma unroll
   for (int t = 0; t < TL; ++t) {
-    kn[t] = ld_nt(kp4 + toff / 8 + t * 64 + lane);
-    vn[t] = ld_nt(vp4 + toff / 8 + t * 64 + lane);
+    kn[t] = ld_stream(kp4 + toff / 8 + t * 64 + lane);
+    vn[t] = ld_stream(vp4 + toff / 8 + t * 64 + lane);
   }
   for (int pi = pw0; pi < pw1; ++pi) {
     const size_t tcur = toff;
@@ -549,8 +513,8 @@ __global__ __launch_bounds__(64 * W) void k_attn_bwd_mx(AttnBwdArgs a) {
       toff = ((size_t)prow[pi + 1] * a.nkv + j) * TILE;
 #pragma unroll
       for (int t = 0; t < TL; ++t) {
-        kn[t] = ld_nt(kp4 + toff / 8 + t * 64 + lane);
-        vn[t] = ld_nt(vp4 + toff / 8 + t * 64 + lane);
+        kn[t] = ld_stream(kp4 + toff / 8 + t * 64 + lane);
+        vn[t] = ld_stream(vp4 + toff / 8 + t * 64 + lane);
       }
     }
 #pragma unroll
@@ -562,9 +526,9 @@ __global__ __launch_bounds__(64 * W) void k_attn_bwd_mx(AttnBwdArgs a) {
     floatx4 st = {0.f, 0.f, 0.f, 0.f}, dpt = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kk = 0; kk < NKB; ++kk) {
-      st = mma32(qa_s[0][kk][lane], kr[kk], st);
-      st = mma32(qa_s[1][kk][lane], kr[kk], st);
-      st = mma32(qa_s[2][kk][lane], kr[kk], st);
+      st = mfma16(qa_s[0][kk][lane], kr[kk], st);
+      st = mfma16(qa_s[1][kk][lane], kr[kk], st);
+      st = mfma16(qa_s[2][kk][lane], kr[kk], st);
     }
 #pragma unroll
     for (int kk = 0; kk < NKB; ++kk) {
@@ -577,8 +541,8 @@ __global__ __launch_bounds__(64 * W) void k_attn_bwd_mx(AttnBwdArgs a) {
       }
       const uint4 vb = make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16,
                                   e[6] | e[7] << 16);
-      dpt = mma32(oa_s[0][kk][lane], vb, dpt);
-      dpt = mma32(oa_s[1][kk][lane], vb, dpt);
+      dpt = mfma16(oa_s[0][kk][lane], vb, dpt);
+      dpt = mfma16(oa_s[1][kk][lane], vb, dpt);
     }
     const int t0 = pi * kPage;
     const bool tv = t0 + n < L;
@@ -591,10 +555,10 @@ __global__ __launch_bounds__(64 * W) void k_attn_bwd_mx(AttnBwdArgs a) {
       dsv[i] = ok ? p * (dpt[i] - Dh4[i]) : 0.f;
     }
     uint2 Ph, Pl, Sh, Sl;
-    split_pair(pv[0], pv[1], Ph.x, Pl.x);
-    split_pair(pv[2], pv[3], Ph.y, Pl.y);
-    split_pair(dsv[0], dsv[1], Sh.x, Sl.x);
-    split_pair(dsv[2], dsv[3], Sh.y, Sl.y);
+    split2(pv[0], pv[1], Ph.x, Pl.x);
+    split2(pv[2], pv[3], Ph.y, Pl.y);
+    split2(dsv[0], dsv[1], Sh.x, Sl.x);
+    split2(dsv[2], dsv[3], Sh.y, Sl.y);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       dsh[(4 * c + i) * DST + n] = (uint16_t)((i < 2 ? Sh.x : Sh.y) >> (16 * (i & 1)));

@@ -6,22 +6,9 @@
 #include <algorithm>
 
 #include "kvprm_internal.h"
+#include "kvprm_mx_common.h"
 
 namespace kvprm {
-
-// ------------------------------------------------------------------------------- helpers
-
-__device__ __forceinline__ float bf16_bits_to_f32(uint32_t h) { return __uint_as_float(h << 16); }
-
-__device__ __forceinline__ float load_scalar(const void *p, size_t i, int wdt) {
-  return wdt ? bf16_bits_to_f32(((const uint16_t *)p)[i]) : ((const float *)p)[i];
-}
-
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
 
 // ------------------------------------------------------------------------------- plan
 
@@ -401,8 +388,8 @@ __global__ __launch_bounds__(kHeadThreads) void k_head(const float *x, int H, fl
     for (int u = 0; u < U; ++u) {
       if (r0 + u * kHeadThreads < H) {
         v[u] = xb[r0 + u * kHeadThreads];
-        gv[u] = load_scalar(gam, r0 + u * kHeadThreads, wdt);
-        wv[u] = load_scalar(wr, r0 + u * kHeadThreads, wdt);
+        gv[u] = ld_w(gam, r0 + u * kHeadThreads, wdt);
+        wv[u] = ld_w(wr, r0 + u * kHeadThreads, wdt);
       } else {
         v[u] = gv[u] = wv[u] = 0.f;
       }
@@ -413,8 +400,8 @@ __global__ __launch_bounds__(kHeadThreads) void k_head(const float *x, int H, fl
       dot += v[u] * (gv[u] * wv[u]);
     }
   }
-  sq = wave_sum(sq);
-  dot = wave_sum(dot);
+  sq = wsum(sq);
+  dot = wsum(dot);
   if ((threadIdx.x & 63) == 0) {
     red[0][threadIdx.x >> 6] = sq;
     red[1][threadIdx.x >> 6] = dot;
@@ -451,11 +438,7 @@ hipError_t launch_head(const Dims &dm, const Plan &p, const Workspace &w, const 
 
 // ------------------------------------------------------------------------------- cache packing
 
-// 16 bytes that a call reads or writes once: non-temporal
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uint4 ld_once(const uint4 *p) {
-  return __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4 *)p));
-}
+// 16 bytes that a call writes once: non-temporal, as ld_stream
 __device__ __forceinline__ void st_once(uint4 *p, const uint4 &v) {
   __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), (u32x4 *)p);
 }
@@ -480,7 +463,7 @@ __global__ __launch_bounds__(256) void k_pack_kv(const uint4 *__restrict__ src, 
   for (int64_t t0 = (int64_t)blockIdx.x * per; t0 < ntiles; t0 += (int64_t)gridDim.x * per) {
     const int n = (int)(ntiles - t0 < per ? ntiles - t0 : per) * groups;
     const uint4 *sp = src + t0 * groups;
-    for (int i = threadIdx.x; i < n; i += 256) tile_s[i] = ONCE ? ld_once(sp + i) : sp[i];
+    for (int i = threadIdx.x; i < n; i += 256) tile_s[i] = ONCE ? ld_stream(sp + i) : sp[i];
     __syncthreads();
     for (int i = threadIdx.x; i < n; i += 256) {
       const int gi = i & (groups - 1);
@@ -554,7 +537,6 @@ hipError_t launch_pack_kv(const void *src, void *dst, int64_t ntiles, int d, int
 // loads cannot be removed (and a test can check that every word was read once). The reference
 // ceiling for the kernels' HBM fractions.
 __global__ __launch_bounds__(256) void k_stream_read(const uint4 *buf, size_t n16, uint32_t *sink) {
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   const size_t stride = (size_t)gridDim.x * 256;
   size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   uint32_t acc = 0;
