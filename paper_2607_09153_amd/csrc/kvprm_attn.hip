@@ -362,9 +362,11 @@ __device__ __forceinline__ int lane_scan(int v) {
 // at the end. Blocks go to the 8 XCDs in turn and to a free unit within each, so that equal work spreads
 // evenly and the short chunks fill in. Each wave finds its candidate and chunk from all lengths (one per
 // lane, at most 64; a scan, a ballot). A grid of (chunk, candidate), chunks of the longest one
-// for each, leaves blocks without work in a regular pattern, and those with work on part of the units: with
-// chunks outermost 12 ragged candidates of 10k-26k, 8 heads, took 214 us a call (149 chunks innermost),
-// now 148; 4 of 1-32k, 4 heads 31.5 (23.4), now 21.7; with chunks innermost 32 of 2k-4k, 8 heads 80.8, now 50.
+// for each, leaves blocks without work in a regular pattern, and those with work on part of the units.
+// Attention call, us, with chunks outermost / innermost / this grid: 12 ragged candidates of 10k-26k,
+// 8 heads 209 / 142 / 143; 4 of 1-32k, 4 heads 30.1 / 23.3 / 21.5; 64 of 1-9k, fp8, d_h = 64, 4 heads
+// 49.0 / 39.0 / 39.4; 24 of 1-9000 fp8, d_h = 64, 4 heads 20.6 / 20.0 / 17.7; 32 of 3k-5.5k, 8 heads: 103 with
+// chunks of all heads innermost, 97.
 // The start of a block (query, page ids, first pair) is a serial chain that every block
 // pays once: with one branch-guarded 4-byte load per query element and the bf16 split in integer
 // arithmetic it took 1.5-2 us more than with 16-byte loads issued first and the hardware

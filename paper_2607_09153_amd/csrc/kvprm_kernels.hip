@@ -93,8 +93,8 @@ int long_chunk_shift(long long pages) {
 // chunks with all of 4 or more kv-heads in one block (whose tiles of a page are contiguous) fill most
 // of one or two rounds of the chip, a block to each compute unit. The same 525 batches, all heads in a block
 // against one: 13-18% slower at any chunk length, 1.4% faster on the 63 that this rule picks; eight of
-// 200616 tokens in all, 4 heads 66.4 against 76 us (as waves of their own some units get four, others
-// two or three), but 24 of 4096, 8 heads 96.5 against 65.1.
+// 200616 tokens in all, 4 heads 70.0 against 78.4 us a call (as waves of their own some units get four,
+// others two or three), but 24 of 4096, 8 heads 96.5 against 65.1.
 PrivateChunks private_chunk_rule(const Dims &dm, int n, const int *pages, const int *slots,
                                  bool known) {
   const bool f32 = dm.kvdt == 0;
