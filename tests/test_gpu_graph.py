@@ -71,3 +71,51 @@ def test_score_replayed_from_a_graph_matches_eager(shape_name, lengths):
         del g
     finally:
         m.kvprm_destroy(h)
+
+
+def test_graph_without_host_lengths_follows_the_device_lengths():
+    """Without host lengths the grids are sized from the page table, so one captured call serves any
+    lengths that are on the device when it is replayed: each replay equals the eager call on those
+    lengths bit for bit, and the call that knows them on the host (another chunk length) up to the
+    order of fp32 sums: logits within 3e-5 of the largest."""
+    import dataclasses
+    _say("case: graph replay on other device lengths")
+    longest = [9000, 5000, 3000, 16, 700, 2049]
+    w = synth.make_workload("custom", shape=dataclasses.replace(synth.B7, num_layers=1), lengths=longest,
+                            seed=502)
+    dw = DeviceWorkload(w)
+    m = kv()
+    h = m.kvprm_create(dw.desc(m))
+    try:
+        batch = dw.batch(m, lengths_host=False)
+        n = m.kvprm_workspace_size(h, batch)
+        ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+        scores, logits = (torch.empty(w.batch, device="cuda") for _ in range(2))
+        cache, ro = dw.cache(m), dw.readout(m)
+
+        def call(b):
+            m.kvprm_score(h, cache, b, ro, ws.data_ptr(), n, scores.data_ptr(), logits.data_ptr(),
+                          torch.cuda.current_stream().cuda_stream)
+
+        call(batch)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            call(batch)
+        for lengths in ([9000, 0, 1, 16, 64, 2000], longest, [63, 4999, 3000, 0, 5, 2048], [0] * 6):
+            _say(f"  lengths {lengths}")
+            dw.lengths.copy_(torch.tensor(lengths, dtype=torch.int32))
+            known = m.make_batch(w.batch, dw.page_table.data_ptr(), dw.page_table.shape[1],
+                                 dw.lengths.data_ptr(), lengths, None, None)
+            got = []
+            for run in (g.replay, lambda: call(batch), lambda: call(known)):
+                logits.fill_(float("nan"))
+                torch.cuda.synchronize()
+                run()
+                torch.cuda.synchronize()
+                got.append(logits.clone())
+            assert torch.all(torch.isfinite(got[0])) and torch.equal(got[0], got[1])
+            assert torch.max(torch.abs(got[0] - got[2])) <= 3e-5 * max(1.0, float(got[2].abs().max()))
+        del g
+    finally:
+        m.kvprm_destroy(h)
